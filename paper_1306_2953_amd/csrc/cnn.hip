@@ -33,7 +33,7 @@ namespace {
 using namespace rsred;
 
 constexpr int kW1 = 0, kW2 = 216, kW3 = 1944, kNW = 2160, kNP = 2162;
-constexpr int kWgPts = 2048;   // points per work-group in the weight gradients
+constexpr int kWgPts = 2048;   // points per work-group in the weight gradients, about
 
 __device__ __forceinline__ int wrap_or_flag(int v, int n, bool wrap, bool &ok) {
     if (wrap) return v < 0 ? v + n : (v >= n ? v - n : v);
@@ -307,64 +307,157 @@ __global__ void flip_kernel(const float *__restrict__ params, float *__restrict_
     wt[off + (ci * CO + co) * 27 + (26 - t)] = params[i];
 }
 
-// Weight gradient partials: partial[wg][co][ci][t] = sum over the
-// work-group's points p of d[p][co] x[p + off(t)][ci].
+// Weight gradient partials on the FP32 matrix cores.  With q = p + (dx - 1)
+//   dW[co][ci][dz][dy][dx] = sum_q x[q + (dz - 1, dy - 1)][ci] d[q - (dx - 1)][co],
+// a contraction over the points q of a (9 CI) x (3 CO) matrix: rows (dz, dy,
+// ci), columns (dx, co), so the nine (dz, dy) shifts come from one LDS copy
+// of x and the three dx shifts from one of d, and 8 -> 8 channels fill 72 x 24
+// of five by two 16 x 16 tiles.  A work-group stages a TZ x TY x TX block of
+// q (x with its border in z and y, d with its border in x; zero outside the
+// box), each wave takes every fourth row of 16 points, four points per
+// mfma_f32_16x16x4_f32 (FP32 products and sums, as fused multiply-adds), and
+// the waves' tiles are added in LDS in wave order.  Bound by the matrix
+// cores' 32 cycles per instruction.  A work-group takes further blocks in
+// turn where there are more than kWgMax of them, so that the partials stay
+// small, and no more than about kWgPts points, so that the FP32 sums stay
+// short; wgrad_final_kernel adds the work-groups in FP64.  One thread per (tap, ci) that
+// gathered its taps from global memory took 792-843 us a layer for 32 crops of 16^3;
+// this takes 8 (1 -> 8), 15 (8 -> 8) and 17 us (8 -> 1).
+constexpr int kWgMax = 1024;
 template <int CI, int CO>
 __global__ void __launch_bounds__(256)
-wgrad_kernel(const float *__restrict__ xin, const float *__restrict__ d, int n, int Z, int Y, int X, int wrap,
-             float *__restrict__ partial) {
-    __shared__ float dl[64][CO];
-    __shared__ int pc[64][4];
-    const int tid = threadIdx.x;
-    const bool act = tid < 27 * CI;
-    const int t = tid / CI, ci = tid % CI;
-    const int ddz = t / 9 - 1, ddy = (t / 3) % 3 - 1, ddx = t % 3 - 1;
-    const int vol = Z * Y * X, total = vol * n;
-    const int p0 = blockIdx.x * kWgPts, p1 = min(total, p0 + kWgPts);
-    float acc[CO];
+wgrad_kernel(const float *__restrict__ xin, const float *__restrict__ d, int n, int Z, int Y, int X, int ntx, int nty,
+             int ntz, float *__restrict__ partial) {
+    constexpr int HY = kTY + 2, HZ = kTZ + 2, HX = kTX + 2;
+    constexpr int MT = (9 * CI + 15) / 16, NT = (3 * CO + 15) / 16;
+    constexpr int NXS = HZ * HY * kTX * CI, NDS = kTZ * kTY * HX * CO, NRED = 3 * MT * NT * 256;
+    __shared__ __attribute__((aligned(16))) float buf[NXS + NDS > NRED ? NXS + NDS : NRED];
+    float *xs = buf, *ds = buf + NXS;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k4 = lane / 16;
+    const int vol = Z * Y * X;
+    // operand offsets of this lane's rows and columns; those past the matrix
+    // read a valid word and are dropped at the end
+    int aoff[MT], boff[NT];
 #pragma unroll
-    for (int c = 0; c < CO; ++c) acc[c] = 0.f;
-    for (int pb = p0; pb < p1; pb += 64) {
-        const int cnt = min(64, p1 - pb);
-        __syncthreads();
-        for (int e = tid; e < cnt * CO; e += 256) dl[e / CO][e % CO] = d[(int64_t)pb * CO + e];
-        if (tid < cnt) {
-            const int p = pb + tid, img = p / vol, q = p - img * vol;
-            pc[tid][0] = img;
-            pc[tid][1] = q % X;
-            pc[tid][2] = (q / X) % Y;
-            pc[tid][3] = q / (X * Y);
+    for (int i = 0; i < MT; ++i) {
+        const int m = 16 * i + lane % 16, s = m / CI;
+        aoff[i] = m < 9 * CI ? ((s / 3) * HY + s % 3) * kTX * CI + m % CI : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const int c = 16 * j + lane % 16;
+        boff[j] = c < 3 * CO ? (2 - c / CO) * CO + c % CO : 0;
+    }
+    f4 acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    const int ntile = ntx * nty * ntz * n;
+    for (int bid = blockIdx.x; bid < ntile; bid += gridDim.x) {
+        const int x0 = (bid % ntx) * kTX, y0 = (bid / ntx) % nty * kTY, z0 = (bid / (ntx * nty)) % ntz * kTZ;
+        const int64_t base = (int64_t)(bid / (ntx * nty * ntz)) * vol;
+        __syncthreads();   // the previous block's reads are done
+        for (int e = tid; e < NXS / CI; e += 256) {
+            const int x = x0 + e % kTX, y = y0 + (e / kTX) % HY - 1, z = z0 + e / (kTX * HY) - 1;
+            const bool ok = x < X && y >= 0 && y < Y && z >= 0 && z < Z;
+            const float *src = xin + (base + (int64_t)(z * Y + y) * X + x) * CI;
+            if constexpr (CI == 8) {
+                const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+                *(float4 *)(xs + e * 8) = ok ? *(const float4 *)src : zero;
+                *(float4 *)(xs + e * 8 + 4) = ok ? *(const float4 *)(src + 4) : zero;
+            } else {
+#pragma unroll
+                for (int c = 0; c < CI; ++c) xs[e * CI + c] = ok ? src[c] : 0.f;
+            }
+        }
+        for (int e = tid; e < NDS / CO; e += 256) {
+            const int x = x0 + e % HX - 1, y = y0 + (e / HX) % kTY, z = z0 + e / (HX * kTY);
+            const bool ok = x >= 0 && x < X && y < Y && z < Z;
+            const float *src = d + (base + (int64_t)(z * Y + y) * X + x) * CO;
+            if constexpr (CO == 8) {
+                const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+                *(float4 *)(ds + e * 8) = ok ? *(const float4 *)src : zero;
+                *(float4 *)(ds + e * 8 + 4) = ok ? *(const float4 *)(src + 4) : zero;
+            } else {
+#pragma unroll
+                for (int c = 0; c < CO; ++c) ds[e * CO + c] = ok ? src[c] : 0.f;
+            }
         }
         __syncthreads();
-        if (!act) continue;
-        for (int j = 0; j < cnt; ++j) {
-            bool ok = true;
-            const int xx = wrap_or_flag(pc[j][1] + ddx, X, wrap, ok);
-            const int yy = wrap_or_flag(pc[j][2] + ddy, Y, wrap, ok);
-            const int zz = wrap_or_flag(pc[j][3] + ddz, Z, wrap, ok);
-            if (!ok) continue;
-            const float xv = xin[((int64_t)pc[j][0] * vol + (zz * Y + yy) * X + xx) * CI + ci];
+        const int nk = (min(kTX, X - x0) + 3) / 4;
+        for (int row = wave; row < kTZ * kTY; row += 4) {
+            const int lz = row / kTY, ly = row % kTY;
+            if (z0 + lz >= Z || y0 + ly >= Y) continue;
+            const float *xr = xs + ((lz * HY + ly) * kTX + k4) * CI, *dr = ds + (row * HX + k4) * CO;
 #pragma unroll
-            for (int c = 0; c < CO; ++c) acc[c] = fmaf(xv, dl[j][c], acc[c]);
+            for (int k = 0; k < kTX / 4; ++k) {
+                if (k >= nk) break;
+                float a[MT], b[NT];
+#pragma unroll
+                for (int i = 0; i < MT; ++i) a[i] = xr[4 * k * CI + aoff[i]];
+#pragma unroll
+                for (int j = 0; j < NT; ++j) b[j] = dr[4 * k * CO + boff[j]];
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+            }
         }
     }
-    if (act)
+    __syncthreads();
+    if (wave > 0)
 #pragma unroll
-        for (int c = 0; c < CO; ++c) partial[(int64_t)blockIdx.x * (CO * CI * 27) + (c * CI + ci) * 27 + t] = acc[c];
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) *(f4 *)(buf + (((wave - 1) * MT * NT + i * NT + j) * 64 + lane) * 4) = acc[i][j];
+    __syncthreads();
+    if (wave > 0) return;
+    float *out = partial + (int64_t)blockIdx.x * (CO * CI * 27);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            f4 v = acc[i][j];
+#pragma unroll
+            for (int w = 0; w < 3; ++w) v += *(const f4 *)(buf + ((w * MT * NT + i * NT + j) * 64 + lane) * 4);
+            const int c = 16 * j + lane % 16;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int m = 16 * i + 4 * k4 + r;
+                if (m < 9 * CI && c < 3 * CO) out[((c % CO) * CI + m % CI) * 27 + m / CI * 3 + c / CO] = v[r];
+            }
+        }
 }
 
-// grad[off + j] = sum over work-groups of partial[wg][j] (FP64, fixed order;
-// one wave per entry).
-__global__ void __launch_bounds__(256)
-wgrad_final(const float *__restrict__ partial, int nwg, int nw, float *__restrict__ grad) {
-    const int lane = threadIdx.x & 63;
-    const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (j >= nw) return;
-    double s = 0.0;
-    for (int w = lane; w < nwg; w += 64) s += partial[(int64_t)w * nw + j];
+// Work-groups of the weight gradients for n boxes of Z x Y x X points.
+int wgrad_groups(int64_t tot, int64_t ntile) {
+    return (int)std::min<int64_t>(ntile, std::max<int64_t>(kWgMax, (tot + kWgPts - 1) / kWgPts));
+}
+
+// grad[j] = sum over work-groups of the layers' partials (FP64, fixed
+// order), all three layers in one launch; 64 entries x 16 shares of the
+// work-groups per block.
+__global__ void __launch_bounds__(1024)
+wgrad_final_kernel(const float *__restrict__ partial, int nwg, float *__restrict__ grad) {
+    __shared__ double red[16][64];
+    const int e = threadIdx.x & 63, part = threadIdx.x >> 6, j = blockIdx.x * 64 + e;
+    if (j < kNW) {
+        const int off = j < kW2 ? kW1 : j < kW3 ? kW2 : kW3, nw = j < kW2 || j >= kW3 ? 216 : 1728;
+        const float *p = partial + (int64_t)off * nwg + (j - off);
+        double s = 0.0;
+#pragma unroll 4
+        for (int w = part; w < nwg; w += 16) s += p[(int64_t)w * nw];
+        red[part][e] = s;
+    }
+    __syncthreads();
+    if (part == 0 && j < kNW) {
+        double s = 0.0;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (lane == 0) grad[j] = (float)s;
+        for (int w = 0; w < 16; ++w) s += red[w][e];
+        grad[j] = (float)s;
+    }
 }
 
 __device__ double softplus_d(double z) { return z > 0 ? z + log1p(exp(-z)) : log1p(exp(z)); }
@@ -874,12 +967,13 @@ extern "C" rs_status rs_cnn_loss_grad(rs_cnn *c, const float *u, const float *t,
     const int64_t tot = (int64_t)n * vol;
     const unsigned gsz = (unsigned)((tot + 255) / 256);
     const size_t pts = (size_t)c->max_batch * c->max_box;
-    const int nwg = (int)((tot + kWgPts - 1) / kWgPts);
+    const int ntx = (X + kTX - 1) / kTX, nty = (Y + kTY - 1) / kTY, ntz = (Z + kTZ - 1) / kTZ;
+    const int nwg = wgrad_groups(tot, (int64_t)ntx * nty * ntz * n);
     const int nch = std::max(1, std::min(64, vol / 4096));
     if ((s = ensure(c->d1, pts * 8 * sizeof(float)))) return s;
     if ((s = ensure(c->d2, pts * 8 * sizeof(float)))) return s;
     if ((s = ensure(c->df, pts * sizeof(float)))) return s;
-    if ((s = ensure(c->wpart, (size_t)((pts + kWgPts - 1) / kWgPts) * 1728 * sizeof(float)))) return s;
+    if ((s = ensure(c->wpart, std::max<size_t>(kWgMax, (pts + kWgPts - 1) / kWgPts) * kNW * sizeof(float)))) return s;
     if ((s = ensure(c->lpart, (size_t)c->max_batch * 64 * 3 * sizeof(double)))) return s;
     const float *P = c->params.as<float>();
     float *G = c->grad.as<float>(), *WT = c->wt.as<float>();
@@ -901,16 +995,19 @@ extern "C" rs_status rs_cnn_loss_grad(rs_cnn *c, const float *u, const float *t,
     hipLaunchKernelGGL(flip_kernel, dim3((kNW + 255) / 256), dim3(256), 0, st, P, WT);
     RS_HIP(hipGetLastError());
     // layer 3: weights, then delta of layer 2 (through tanh)
-    hipLaunchKernelGGL((wgrad_kernel<8, 1>), dim3(nwg), dim3(256), 0, st, a2, df, n, Z, Y, X, 0, c->wpart.as<float>());
-    hipLaunchKernelGGL(wgrad_final, dim3((216 + 3) / 4), dim3(256), 0, st, c->wpart.as<float>(), nwg, 216, G + kW3);
+    float *wp = c->wpart.as<float>();
+    const dim3 gw((unsigned)nwg);
+    hipLaunchKernelGGL((wgrad_kernel<8, 1>), gw, dim3(256), 0, st, a2, df, n, Z, Y, X, ntx, nty, ntz,
+                       wp + (int64_t)kW3 * nwg);
     conv<1, 8, 2>(df, d2, WT + kW3, a2, nullptr, n, Z, Y, X, 0, st);
     // layer 2
-    hipLaunchKernelGGL((wgrad_kernel<8, 8>), dim3(nwg), dim3(256), 0, st, a1, d2, n, Z, Y, X, 0, c->wpart.as<float>());
-    hipLaunchKernelGGL(wgrad_final, dim3((1728 + 3) / 4), dim3(256), 0, st, c->wpart.as<float>(), nwg, 1728, G + kW2);
+    hipLaunchKernelGGL((wgrad_kernel<8, 8>), gw, dim3(256), 0, st, a1, d2, n, Z, Y, X, ntx, nty, ntz,
+                       wp + (int64_t)kW2 * nwg);
     conv<8, 8, 2>(d2, d1, WT + kW2, a1, nullptr, n, Z, Y, X, 0, st);
     // layer 1
-    hipLaunchKernelGGL((wgrad_kernel<1, 8>), dim3(nwg), dim3(256), 0, st, u, d1, n, Z, Y, X, 0, c->wpart.as<float>());
-    hipLaunchKernelGGL(wgrad_final, dim3((216 + 3) / 4), dim3(256), 0, st, c->wpart.as<float>(), nwg, 216, G + kW1);
+    hipLaunchKernelGGL((wgrad_kernel<1, 8>), gw, dim3(256), 0, st, u, d1, n, Z, Y, X, ntx, nty, ntz,
+                       wp + (int64_t)kW1 * nwg);
+    hipLaunchKernelGGL(wgrad_final_kernel, dim3((kNW + 63) / 64), dim3(1024), 0, st, wp, nwg, G);
     if (du)
         conv<8, 1, 1>(d1, du, WT + kW1, nullptr, nullptr, n, Z, Y, X, 0, st);
     RS_HIP(hipGetLastError());

@@ -75,6 +75,26 @@ def test_loss_gradient_and_adam_match_oracle():
     assert np.max(np.abs(got - want)) <= 1e-6 * np.max(np.abs(p))
 
 
+# one-point axes, exactly one 4 x 8 x 16 block, one point past it on each
+# axis, and more blocks than work-groups (each then sums several)
+@pytest.mark.parametrize("n,dims,margin", [(2, (1, 1, 40), 0), (1, (4, 8, 16), 0), (3, (5, 9, 17), 1),
+                                           (300, (9, 9, 17), 2)])
+def test_weight_gradients_at_block_edges(n, dims, margin):
+    p = _params(13)
+    net = rsd.Cnn(n, int(np.prod(dims)))
+    net.set_params(p)
+    rng = np.random.default_rng(14)
+    u = rng.normal(size=(n,) + dims).astype(np.float32)
+    t = rng.normal(size=(n,) + dims).astype(np.float32)
+    sig = -rng.uniform(0.5, 5.0, n)
+    loss, grad, _ = net.loss_grad(_dev(u), _dev(t), _dev(sig), 0.25, margin)
+    wl, wg, _ = ocnn.loss_and_grad(p, u.astype(np.float64), t.astype(np.float64), sig, 0.25, margin)
+    # layer 2's split products carry about 2^-16 per term: 1e-5 of the sums
+    assert loss == pytest.approx(wl, rel=1e-5)
+    for a, b in ((0, 216), (216, 1944), (1944, 2160), (2160, 2162)):
+        assert _rel(grad[a:b], wg[a:b]) <= 1e-4, (a, b)
+
+
 @pytest.mark.parametrize("kind,dtype,B", [("sphere", np.float64, 8), ("sphere", np.float32, 16),
                                           ("periodic", np.float32, 8)])
 def test_precondition_matches_oracle(kind, dtype, B):
