@@ -53,6 +53,24 @@ def test_hartree_matches_oracle(kind, kw):
     assert err < 1e-12
 
 
+# every box edge (each has its own radices), with extents that end inside a
+# group of 16 lines, fill one, and differ per axis
+@pytest.mark.parametrize("n,centres,radius", [
+    (16, [[0.0, 0.0, 0.0]], 0.9), (32, [[0.0, 0.0, 0.0], [0.4, 0.9, 0.0]], 1.3),
+    (64, [[0.0, 0.0, 0.0], [2.9, 0.7, 0.0]], 1.6), (128, [[0.0, 0.0, 0.0], [0.3, 9.0, 1.0]], 1.2),
+    (256, [[0.0, 0.0, 0.0], [24.0, 0.3, 0.7]], 1.2), (512, [[0.0, 0.0, 0.0], [0.9, 0.5, 40.0]], 1.2)])
+def test_hartree_matches_oracle_at_every_box_edge(n, centres, radius):
+    c = np.array(centres)
+    og = ogrid.build_grid("union", 0.3, radius=radius, centres=c)
+    ps = rsd.Poisson(rsd.Grid("union", 0.3, radius=radius, centres=c))
+    assert ps.nbox == n
+    rho = np.random.default_rng(22).uniform(0.0, 1.0, size=og.np)
+    want = opoisson.hartree(og, rho)
+    got = ps.solve(torch.from_numpy(rho).cuda()).cpu().numpy()
+    # round-off of two transforms: about 2 log2(n^3) eps of the largest value
+    assert np.max(np.abs(got - want)) < 1e-12 * np.max(np.abs(want))
+
+
 def test_full_size_sphere_hartree_of_a_gaussian():
     """The 904k-point sphere (box 256^3): a Gaussian charge's potential
     against erf(r / (sqrt(2) s)) / r, and against the oracle at sampled
