@@ -1043,7 +1043,7 @@ rs_status cnn_precondition(rs_cnn *c, const rs_grid *g, const void *r, const dou
     const int cb = c->max_batch / B;          // blocks per chunk
     if (cb < 1) return fail(RS_EINVAL, "cnn precondition: max_batch of the network handle is below B");
     const int64_t np = g->np;
-    const int nchunks = (int)((np + kChunk - 1) / kChunk);
+    const int nchunks = chunk_count(np, B, nblk);
     if ((s = ensure(c->ss, (size_t)N * sizeof(double)))) return s;
     if ((s = ensure(c->inv_s, (size_t)N * sizeof(double)))) return s;
     if ((s = ensure(c->outs, (size_t)N * sizeof(double)))) return s;
@@ -1126,7 +1126,7 @@ extern "C" rs_status rs_cnn_crops(rs_cnn *c, const rs_grid *g, const void *r, co
     }
     hipStream_t st = (hipStream_t)stream;
     const int64_t np = g->np;
-    const int nchunks = (int)((np + kChunk - 1) / kChunk);
+    const int nchunks = chunk_count(np, B, nblk);
     if ((s = ensure(c->ss, (size_t)N * sizeof(double)))) return s;
     if ((s = ensure(c->inv_s, (size_t)N * sizeof(double)))) return s;
     if ((s = ensure(c->partial, (size_t)nchunks * N * sizeof(double)))) return s;
@@ -1175,7 +1175,7 @@ rs_status shifted_cg(const rs_grid *g, const T *b, const double *sigma, T *x, in
     const int N = nblk * B;
     const int64_t np = g->np, total = np * N;
     const size_t bytes = (size_t)total * sizeof(T);
-    const int nchunks = (int)((np + kChunk - 1) / kChunk);
+    const int nchunks = chunk_count(np, B, nblk);
     rs::DevBuf r, p, q, partial, small, flags;
     rs_status s = r.alloc(bytes);
     if (!s) s = p.alloc(bytes);

