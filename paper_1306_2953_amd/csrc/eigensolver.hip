@@ -228,74 +228,101 @@ combine_kernel(Hist<T> H, const double *__restrict__ eps, const double *__restri
 // ----------------------------------------------------- per-state solvers
 // Lowest eigenpair of the symmetric generalised problem A c = mu B c
 // (n <= 4): scale by diag(B)^-1/2, Cholesky of B, Jacobi on L^-1 A L^-T.
-// Returns false when B is not positive definite.
-__device__ bool lowest_geneig(int n, const double *A_in, const double *B_in, double *c) {
-    double A[16], Bm[16], D[4], L[16], C[16], V[16];
+// Returns false when B is not positive definite.  n is a template parameter
+// and every loop over indices unrolls, so the matrices live in registers;
+// with n at run time they lay in scratch memory and a call took 81-111 us,
+// now 5-8 (a serial chain of FP64 divisions and square roots).
+template <int n>
+__device__ __forceinline__ bool lowest_geneig(const double (&A_in)[n * n], const double (&B_in)[n * n],
+                                              double (&c)[n]) {
+    double A[n * n], Bm[n * n], D[n], L[n * n], C[n * n], V[n * n];
+#pragma unroll
     for (int i = 0; i < n; ++i) {
         if (!(B_in[i * n + i] > 0.0)) return false;
         D[i] = 1.0 / sqrt(B_in[i * n + i]);
     }
+#pragma unroll
     for (int i = 0; i < n; ++i)
+#pragma unroll
         for (int j = 0; j < n; ++j) {
             A[i * n + j] = A_in[i * n + j] * D[i] * D[j];
             Bm[i * n + j] = B_in[i * n + j] * D[i] * D[j];
         }
-    for (int i = 0; i < 16; ++i) L[i] = 0.0;
+#pragma unroll
     for (int j = 0; j < n; ++j) {
         double d = Bm[j * n + j];
+#pragma unroll
         for (int k = 0; k < j; ++k) d -= L[j * n + k] * L[j * n + k];
         if (!(d > 0.0)) return false;
         L[j * n + j] = sqrt(d);
+#pragma unroll
         for (int i = j + 1; i < n; ++i) {
             double s = Bm[i * n + j];
+#pragma unroll
             for (int k = 0; k < j; ++k) s -= L[i * n + k] * L[j * n + k];
             L[i * n + j] = s / L[j * n + j];
         }
     }
     // C = L^-1 A L^-T: solve L Y = A, then L C^T = Y^T
-    double Y[16];
+    double Y[n * n];
+#pragma unroll
     for (int col = 0; col < n; ++col)
+#pragma unroll
         for (int i = 0; i < n; ++i) {
             double s = A[i * n + col];
+#pragma unroll
             for (int k = 0; k < i; ++k) s -= L[i * n + k] * Y[k * n + col];
             Y[i * n + col] = s / L[i * n + i];
         }
+#pragma unroll
     for (int row = 0; row < n; ++row)
+#pragma unroll
         for (int i = 0; i < n; ++i) {
             double s = Y[row * n + i];
+#pragma unroll
             for (int k = 0; k < i; ++k) s -= L[i * n + k] * C[row * n + k];
             C[row * n + i] = s / L[i * n + i];
         }
+#pragma unroll
     for (int i = 0; i < n; ++i)
+#pragma unroll
         for (int j = 0; j < n; ++j) {
             V[i * n + j] = i == j ? 1.0 : 0.0;
             if (j > i) C[i * n + j] = C[j * n + i] = 0.5 * (C[i * n + j] + C[j * n + i]);
         }
+#pragma unroll 1
     for (int sweep = 0; sweep < 50; ++sweep) {
         double off = 0.0, tot = 0.0;
+#pragma unroll
         for (int i = 0; i < n; ++i)
+#pragma unroll
             for (int j = 0; j < n; ++j) {
                 tot += C[i * n + j] * C[i * n + j];
                 if (i != j) off += C[i * n + j] * C[i * n + j];
             }
         if (!(off > 1e-32 * tot)) break;
+#pragma unroll
         for (int p = 0; p < n; ++p)
+#pragma unroll
             for (int q = p + 1; q < n; ++q) {
                 const double apq = C[p * n + q];
                 if (apq == 0.0) continue;
                 const double th = (C[q * n + q] - C[p * n + p]) / (2.0 * apq);
                 const double t = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
                 const double cs = 1.0 / sqrt(t * t + 1.0), sn = t * cs;
+#pragma unroll
                 for (int k = 0; k < n; ++k) {
                     const double kp = C[k * n + p], kq = C[k * n + q];
                     C[k * n + p] = cs * kp - sn * kq;
                     C[k * n + q] = sn * kp + cs * kq;
                 }
+#pragma unroll
                 for (int k = 0; k < n; ++k) {
                     const double pk = C[p * n + k], qk = C[q * n + k];
                     C[p * n + k] = cs * pk - sn * qk;
                     C[q * n + k] = sn * pk + cs * qk;
                 }
+#pragma unroll
                 for (int k = 0; k < n; ++k) {
                     const double kp = V[k * n + p], kq = V[k * n + q];
                     V[k * n + p] = cs * kp - sn * kq;
@@ -303,21 +330,32 @@ __device__ bool lowest_geneig(int n, const double *A_in, const double *B_in, dou
                 }
             }
     }
-    int lo = 0;
-    for (int i = 1; i < n; ++i)
-        if (C[i * n + i] < C[lo * n + lo]) lo = i;
+    // the lowest pair, taken by selects (an index would spill V)
+    double mu = C[0], y[n];
+#pragma unroll
+    for (int i = 0; i < n; ++i) y[i] = V[i * n];
+#pragma unroll
+    for (int j = 1; j < n; ++j) {
+        const bool lower = C[j * n + j] < mu;
+        mu = lower ? C[j * n + j] : mu;
+#pragma unroll
+        for (int i = 0; i < n; ++i) y[i] = lower ? V[i * n + j] : y[i];
+    }
     // c = D L^-T y
-    double y[4];
-    for (int i = 0; i < n; ++i) y[i] = V[i * n + lo];
+#pragma unroll
     for (int i = n - 1; i >= 0; --i) {
         double s = y[i];
+#pragma unroll
         for (int k = i + 1; k < n; ++k) s -= L[k * n + i] * c[k];
         c[i] = s / L[i * n + i];
     }
-    for (int i = 0; i < n; ++i) c[i] *= D[i];
-    for (int i = 0; i < n; ++i)
-        if (!isfinite(c[i])) return false;
-    return true;
+    bool finite = true;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        c[i] *= D[i];
+        finite = finite && isfinite(c[i]);
+    }
+    return finite;
 }
 
 // Trial step lambda (state frozen -> 0).  dots: [<x|Hx>, <x|x>] and
@@ -336,7 +374,7 @@ __global__ void lambda_kernel(const double *__restrict__ d2, const double *__res
         const double b12 = d5[3 * N + c] * s;
         const double A[4] = {a11, a12, a12, a22}, Bm[4] = {b11, b12, b12, 1.0};
         double v[2];
-        if (lowest_geneig(2, A, Bm, v) && v[0] != 0.0) l = v[1] / v[0] * s;
+        if (lowest_geneig<2>(A, Bm, v) && v[0] != 0.0) l = v[1] / v[0] * s;
     }
     lam[c] = l;
 }
@@ -379,7 +417,7 @@ __global__ void mix_kernel(const double *__restrict__ d2, const double *__restri
         {
             const double A[4] = {a11, a12, a12, a22}, Bm[4] = {b11, b12, b12, 1.0};
             double v[2];
-            if (lowest_geneig(2, A, Bm, v) && v[0] != 0.0) l = v[1] / v[0] * s;
+            if (lowest_geneig<2>(A, Bm, v) && v[0] != 0.0) l = v[1] / v[0] * s;
             ma = l;
         }
         if (bee > 0.0 && isfinite(bee)) {
@@ -392,7 +430,7 @@ __global__ void mix_kernel(const double *__restrict__ d2, const double *__restri
             const double A[9] = {a11, a12, a13, a12, a22, a23, a13, a23, a33};
             const double Bm[9] = {b11, b12, b13, b12, 1.0, b23, b13, b23, 1.0};
             double v[3];
-            if (lowest_geneig(3, A, Bm, v) && v[0] != 0.0) {
+            if (lowest_geneig<3>(A, Bm, v) && v[0] != 0.0) {
                 ma = v[1] / v[0] * s;
                 mb = v[2] / v[0] * t;
                 l = 1.0;
@@ -432,24 +470,29 @@ __global__ void eps_kernel(const double *__restrict__ d2, int N, double *__restr
 }
 
 // DIIS coefficients per state (c_0 = 1); frozen or degenerate -> e_0.
-__global__ void diis_kernel(const double *__restrict__ mats, int n, const double *__restrict__ lam, int N,
+template <int n>
+__global__ void diis_kernel(const double *__restrict__ mats, const double *__restrict__ lam, int N,
                             double *__restrict__ coef) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= N) return;
     double out[kMaxHist] = {1.0, 0.0, 0.0, 0.0};
     if (lam[c] != 0.0) {
-        double A[16], Bm[16], v[4];
-        const int nt = n * (n + 1) / 2;
+        double A[n * n], Bm[n * n], v[n];
+        constexpr int nt = n * (n + 1) / 2;
         int t = 0;
+#pragma unroll
         for (int p = 0; p < n; ++p)
+#pragma unroll
             for (int q = p; q < n; ++q) {
                 A[p * n + q] = A[q * n + p] = mats[(int64_t)t * N + c];
                 Bm[p * n + q] = Bm[q * n + p] = mats[(int64_t)(t + nt) * N + c];
                 ++t;
             }
-        if (lowest_geneig(n, A, Bm, v) && v[0] != 0.0)
+        if (lowest_geneig<n>(A, Bm, v) && v[0] != 0.0)
+#pragma unroll
             for (int i = 0; i < n; ++i) out[i] = v[i] / v[0];
     }
+#pragma unroll
     for (int i = 0; i < kMaxHist; ++i) coef[c * kMaxHist + i] = out[i];
 }
 
@@ -776,8 +819,8 @@ rs_status step_impl(rs_solver *S, T *psi, hipStream_t st) {
             if ((e = colreduce<12>(op, np, B, nblk, dv, partial, S->mats.as<double>(), st, bs.map, bs.n)))
                 return e;
         }
-        hipLaunchKernelGGL(diis_kernel, dim3(gs), dim3(64), 0, st, S->mats.as<double>(), n, S->lam.as<double>(), N,
-                           S->coef.as<double>());
+        hipLaunchKernelGGL(n == 2 ? diis_kernel<2> : diis_kernel<3>, dim3(gs), dim3(64), 0, st, S->mats.as<double>(),
+                           S->lam.as<double>(), N, S->coef.as<double>());
         // psi_bar, H psi_bar into slot n; R_bar into R.  The last iteration
         // needs no H psi_bar (nothing follows that would use it)
         T *xb = S->hx[n].as<T>(), *hb = n < m ? S->hh[n].as<T>() : nullptr;
