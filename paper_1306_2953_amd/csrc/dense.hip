@@ -1096,20 +1096,262 @@ trinv_kernel(const double *__restrict__ U, double *__restrict__ T, int N, const 
 }
 
 // ------------------------------------------------------ Jacobi eigensolver
-// Cyclic parallel Jacobi on a symmetric A (N <= 256, FP64, one work-group).
-// Each round rotates N/2 disjoint pairs (round-robin ordering) as
-// A <- J^T A J, V <- V J; sweeps repeat until the off-diagonal norm is below
-// tol * ||A||_F or max_sweeps is reached.  A lives in LDS when it fits
-// (LDSA), else in global memory.  Eigenvalues ascending; each eigenvector's
-// largest-magnitude component is made positive.
-// Cyclic Jacobi in the parallel (round-robin) ordering: each round
-// annihilates M/2 disjoint pivots (p, q) at once, so A <- J^T A J splits
-// into independent 2x2 blocks (pair k) x (pair l).  One work-group; A lives
-// in LDS with an odd row stride when it fits, else in place in global
-// memory.  A must be symmetric; only blocks k <= l are computed and the
-// transposed block is mirrored, keeping A exactly symmetric.  The rotations
-// (c, s) are recorded per round for the eigenvector kernel; the final
-// diagonal goes to diag.
+// Cyclic Jacobi on a symmetric A (N <= 256, FP64, one work-group) in the
+// parallel round-robin ordering: each round annihilates M/2 disjoint pivots
+// at once (M = N rounded up to even; an odd N gets a dummy of zeros), so
+// A <- J^T A J splits into independent 2x2 blocks (pair k) x (pair l), k <= l;
+// sweeps of M - 1 rounds repeat until the off-diagonal norm is below
+// tol * ||A||_F or max_sweeps is reached.  The rotations (c, s) are recorded
+// per round for the eigenvector kernel; the final diagonal goes to diag.
+// Eigenvalues ascending; each eigenvector's largest-magnitude component is
+// made positive.
+//
+// N <= 128, jacobi_slot_kernel: the players move and the blocks stay.  Pair k
+// is always slots k and M - 1 - k, and after a round the player in slot i
+// moves to slot i - 1 (1 to M - 1; 0 stays), so every block reads its four
+// values at its own place and writes them to four places that never change:
+// no index is computed inside a round.  The blocks lie in two LDS copies (one
+// read, one written), component by component, so that lanes read 512
+// contiguous bytes.  Wave 0 owns the angles: it forms the next round's pivots
+// from this round's values (the new pair's two players come from two old
+// pairs: their diagonals and the one block that joins them) while the other
+// waves update, so the divisions and square roots are off the others' path
+// and a round has one barrier.  Bound by LDS traffic: 2080 blocks of 32 bytes
+// in and out and two rotations each, about 1500 cycles a round at N = 128.
+// Measured at N = 128 with players that stay (indices looked up and formed per
+// round, two barriers): 2.2 us a round; now 0.73 us.
+//
+// Position of slots (i, j) in the block triangle: block (pair, pair) in row
+// order with the smaller pair first, component 2 (row is the pair's second
+// slot) + (column is), 01 for both off-diagonal places of a diagonal block.
+constexpr int kSlotMaxN = 128, kSlotNB = 64 * 65 / 2;   // largest N, its blocks (the components' stride)
+__device__ __forceinline__ int slot_place(int i, int j, int M) {
+    const int h = M / 2;
+    int pi = min(i, M - 1 - i), pj = min(j, M - 1 - j), si = i >= h, sj = j >= h;
+    if (pi > pj || (pi == pj && si > sj)) {
+        const int t = pi, u = si;
+        pi = pj;
+        si = sj;
+        pj = t;
+        sj = u;
+    }
+    return (2 * si + sj) * kSlotNB + pi * h - pi * (pi - 1) / 2 + (pj - pi);
+}
+__device__ __forceinline__ int slot_next(int i, int M) { return i == 0 ? 0 : i == 1 ? M - 1 : i - 1; }
+__device__ __forceinline__ int slot_prev(int i, int M) { return i == 0 ? 0 : i == M - 1 ? 1 : i + 1; }
+
+// Rotation that annihilates apq: columns p' = c p - s q, q' = s p + c q.
+__device__ __forceinline__ double2 jacobi_rotation(double app, double apq, double aqq) {
+    double c = 1.0, s = 0.0;
+    if (apq != 0.0) {
+        const double th = (aqq - app) / (2.0 * apq);
+        const double t = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
+        c = 1.0 / sqrt(t * t + 1.0);
+        s = t * c;
+    }
+    return make_double2(c, s);
+}
+
+constexpr int kSlotBlocks = 3;   // blocks per lane of the 15 updating waves: 3 * 960 >= 64 * 65 / 2
+__global__ void __launch_bounds__(1024)
+jacobi_slot_kernel(const double *__restrict__ Ag, int N, int max_sweeps, double tol, int *__restrict__ sweeps_out,
+                   double2 *__restrict__ rot, double *__restrict__ diag) {
+    extern __shared__ double ldsA[];            // two copies of [4][kSlotNB]
+    __shared__ double2 cs[2][kSlotMaxN / 2];
+    __shared__ double red[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+    const int M = N + (N & 1), h = M / 2, nb = h * (h + 1) / 2, nu = blockDim.x - 64;
+    double *cur = ldsA;
+    double fro = 0.0;
+    for (int i = wave; i < M; i += nw)
+        for (int j = lane; j < M; j += 64) {
+            const double a = i < N && j < N ? Ag[i * N + j] : 0.0;
+            fro += a * a;
+            if (i <= j) {
+                cur[slot_place(i, j, M)] = a;
+                // the unused component of a diagonal block stays zero
+                if (i + j == M - 1)
+                    cur[2 * kSlotNB + i * h - i * (i - 1) / 2] = cur[6 * kSlotNB + i * h - i * (i - 1) / 2] = 0.0;
+            }
+        }
+    auto block_sum = [&](double v) {
+        v = wave_sum(v);
+        if (lane == 0) red[wave] = v;
+        __syncthreads();
+        double t = 0.0;
+        for (int w2 = 0; w2 < nw; ++w2) t += red[w2];
+        __syncthreads();
+        return t;
+    };
+    fro = sqrt(block_sum(fro));
+    // this lane's blocks (waves 1..) and where their values go
+    // (places two to a register: they are below 4 * 2080)
+    int kk[kSlotBlocks], ll[kSlotBlocks];
+    uint32_t dst[kSlotBlocks][2];
+#pragma unroll
+    for (int b = 0; b < kSlotBlocks; ++b) {
+        const int e = tid - 64 + b * nu;
+        int k = 0, row = 0;
+        if (e < nb)
+            while (row + (h - k) <= e) row += h - k++;
+        kk[b] = k;
+        ll[b] = tid >= 64 && e < nb ? k + e - row : -1;   // -1: no block
+        const int r0 = slot_next(kk[b], M), r1 = slot_next(M - 1 - kk[b], M);
+        const int l = max(ll[b], 0), c0 = slot_next(l, M), c1 = slot_next(M - 1 - l, M);
+        dst[b][0] = (uint32_t)slot_place(r0, c0, M) | (uint32_t)slot_place(r0, c1, M) << 16;
+        dst[b][1] = (uint32_t)slot_place(r1, c0, M) | (uint32_t)slot_place(r1, c1, M) << 16;
+    }
+    // wave 0: the players of new pair `lane` come from slots u and v, of
+    // pairs pu and pv
+    const bool angle = wave == 0 && lane < h;
+    const int u = angle ? slot_prev(lane, M) : 0, v = angle ? slot_prev(M - 1 - lane, M) : 0;
+    const int pu = min(u, M - 1 - u), pv = min(v, M - 1 - v);
+    const bool su = u >= h, sv = v >= h;
+    const int eu = pu * h - pu * (pu - 1) / 2, ev = pv * h - pv * (pv - 1) / 2;
+    const int uv00 = slot_place(pu, pv, M), uv01 = slot_place(pu, M - 1 - pv, M),
+              uv10 = slot_place(M - 1 - pu, pv, M), uv11 = slot_place(M - 1 - pu, M - 1 - pv, M);
+    const int64_t nrot = (int64_t)max_sweeps * (M - 1);
+    int64_t round = 0;
+    if (angle) {
+        const int e = lane * h - lane * (lane - 1) / 2;
+        const double2 r = jacobi_rotation(cur[e], cur[kSlotNB + e], cur[3 * kSlotNB + e]);
+        cs[0][lane] = r;
+        if (round < nrot) rot[lane] = r;
+    }
+    int side = 0, sweep = 0;
+    for (; sweep < max_sweeps; ++sweep) {
+        double off = 0.0;
+#pragma unroll
+        for (int b = 0; b < kSlotBlocks; ++b) {
+            if (ll[b] < 0) continue;
+            const int e = tid - 64 + b * nu;
+            const double x01 = cur[kSlotNB + e];
+            off += 2.0 * (x01 * x01);
+            if (kk[b] != ll[b]) {
+                const double x00 = cur[e], x10 = cur[2 * kSlotNB + e], x11 = cur[3 * kSlotNB + e];
+                off += 2.0 * (x00 * x00 + x10 * x10 + x11 * x11);
+            }
+        }
+        if (!(sqrt(block_sum(off)) > tol * fro)) break;
+#pragma unroll 1
+        for (int r = 0; r < M - 1; ++r) {
+            ++round;
+            double *nxt = ldsA + (side ^ 1) * 4 * kSlotNB;
+            if (wave == 0) {
+                if (angle) {
+                    // the pair's 2x2 problem after this round's rotations
+                    const double2 ru = cs[side][pu], rv = cs[side][pv];
+                    double d[2], z = 0.0;
+#pragma unroll
+                    for (int w2 = 0; w2 < 2; ++w2) {
+                        const int e = w2 ? ev : eu;
+                        const bool second = w2 ? sv : su;
+                        const double c = w2 ? rv.x : ru.x, s = w2 ? rv.y : ru.y;
+                        const double x00 = cur[e], x01 = cur[kSlotNB + e], x11 = cur[3 * kSlotNB + e];
+                        const double y00 = c * x00 - s * x01, y01 = s * x00 + c * x01;
+                        const double y10 = c * x01 - s * x11, y11 = s * x01 + c * x11;
+                        d[w2] = second ? s * y01 + c * y11 : c * y00 - s * y10;
+                    }
+                    if (pu != pv) {
+                        const double x00 = cur[uv00], x01 = cur[uv01], x10 = cur[uv10], x11 = cur[uv11];
+                        const double c0 = sv ? rv.y : rv.x, c1 = sv ? rv.x : -rv.y;
+                        const double y0 = c0 * x00 + c1 * x01, y1 = c0 * x10 + c1 * x11;
+                        z = su ? ru.y * y0 + ru.x * y1 : ru.x * y0 - ru.y * y1;
+                    }
+                    const double2 n = jacobi_rotation(d[0], z, d[1]);
+                    cs[side ^ 1][lane] = n;
+                    if (round < nrot) rot[round * h + lane] = n;
+                }
+            } else {
+                double x[kSlotBlocks][4];
+                double2 rk[kSlotBlocks], rl[kSlotBlocks];
+#pragma unroll
+                for (int b = 0; b < kSlotBlocks; ++b) {
+                    if (ll[b] < 0) continue;
+                    const int e = tid - 64 + b * nu;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) x[b][q] = cur[q * kSlotNB + e];
+                    rk[b] = cs[side][kk[b]];
+                    rl[b] = cs[side][ll[b]];
+                }
+#pragma unroll
+                for (int b = 0; b < kSlotBlocks; ++b) {
+                    if (ll[b] < 0) continue;
+                    const bool dg = kk[b] == ll[b];
+                    const double ck = rk[b].x, sk = rk[b].y, cl = rl[b].x, sl = rl[b].y;
+                    const double x00 = x[b][0], x01 = x[b][1], x10 = dg ? x01 : x[b][2], x11 = x[b][3];
+                    // columns (A J), then rows (J^T A J)
+                    const double y00 = cl * x00 - sl * x01, y01 = sl * x00 + cl * x01;
+                    const double y10 = cl * x10 - sl * x11, y11 = sl * x10 + cl * x11;
+                    nxt[dst[b][0] & 0xFFFFu] = ck * y00 - sk * y10;
+                    // the pivot is annihilated exactly
+                    nxt[dst[b][0] >> 16] = dg ? 0.0 : ck * y01 - sk * y11;
+                    if (!dg) nxt[dst[b][1] & 0xFFFFu] = sk * y00 + ck * y10;
+                    nxt[dst[b][1] >> 16] = sk * y01 + ck * y11;
+                }
+            }
+            __syncthreads();
+            side ^= 1;
+            cur = nxt;
+        }
+    }
+    // M - 1 rounds bring every player back: slot i holds player i
+    for (int i = tid; i < N; i += blockDim.x) diag[i] = cur[slot_place(i, i, M)];
+    if (tid == 0) *sweeps_out = sweep;
+}
+
+// Eigenvectors of jacobi_slot_kernel: V = J_1 J_2 ... J_R; the rows of V are
+// independent, so a wave owns one: lane k holds the values of slots k and
+// M - 1 - k in registers, rotates them, and the players move one slot on by
+// a lane shift (lane 0's first slot stays; the last lane's first slot takes
+// its second; lane 0's second takes lane 1's first).  The rotations, 1 KB a
+// round at N = 128, are loaded kVecAhead rounds ahead.  Rows in LDS with
+// indices formed per round took 330 us for 9 sweeps of N = 128; now 79 us.
+constexpr int kVecAhead = 16;
+template <int CTRL> __device__ __forceinline__ double wave_shift(double v) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)u, CTRL, 0xF, 0xF, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+constexpr int kShiftDown = 0x130, kShiftUp = 0x138;   // wave_shl:1 (lane i takes i + 1), wave_shr:1 (i - 1)
+__global__ void __launch_bounds__(64)
+jacobi_slot_vec_kernel(const double2 *__restrict__ rot, const int *__restrict__ sweeps, int N,
+                       double *__restrict__ Vw) {
+    const int lane = threadIdx.x, i = blockIdx.x;
+    const int M = N + (N & 1), h = M / 2;
+    const int R = *sweeps * (M - 1);
+    const int k = min(lane, h - 1);
+    double a = lane == i ? 1.0 : 0.0, b = M - 1 - lane == i && lane < h ? 1.0 : 0.0;
+    const double2 *p = rot + k;
+    double2 ahead[kVecAhead];
+#pragma unroll
+    for (int t = 0; t < kVecAhead; ++t) ahead[t] = t < R ? p[(int64_t)t * h] : make_double2(1.0, 0.0);
+    for (int r0 = 0; r0 < R; r0 += kVecAhead)
+#pragma unroll
+        for (int t = 0; t < kVecAhead; ++t) {
+            if (r0 + t >= R) break;
+            const double c = ahead[t].x, s = ahead[t].y;
+            if (r0 + t + kVecAhead < R) ahead[t] = p[(int64_t)(r0 + t + kVecAhead) * h];
+            const double na = c * a - s * b, nb = s * a + c * b;
+            if (h == 1) {
+                a = na;
+                b = nb;
+                continue;
+            }
+            const double da = wave_shift<kShiftDown>(na), ub = wave_shift<kShiftUp>(nb);
+            a = lane == 0 ? na : lane == h - 1 ? nb : da;
+            b = lane == 0 ? da : ub;
+        }
+    if (lane >= h) return;
+    Vw[(int64_t)i * N + lane] = a;
+    if (M - 1 - lane < N) Vw[(int64_t)i * N + M - 1 - lane] = b;
+}
+
+// N > 128: the players stay.  A lives in LDS with an odd row stride when it
+// fits (LDSA), else in place in global memory; A must be symmetric, only
+// blocks k <= l are computed and the transposed block is mirrored, keeping A
+// exactly symmetric.
 template <bool LDSA>
 __global__ void __launch_bounds__(1024)
 jacobi_rot_kernel(double *__restrict__ Ag, int N, int max_sweeps, double tol, int *__restrict__ sweeps_out,
@@ -1128,9 +1370,6 @@ jacobi_rot_kernel(double *__restrict__ Ag, int N, int max_sweeps, double tol, in
             for (int j = lane; j < N; j += 64) A[i * ld + j] = Ag[i * N + j];
     const int M = N + (N & 1);        // even number of players (a dummy when N is odd)
     const int h = M / 2;
-    // N <= 128: rounds keep only the upper triangle up to date (each element
-    // written once, at (min, max) of its indices); larger N: both
-    const bool upper = h <= 64 && nw == 16;
     __syncthreads();
     // Frobenius norms (all entries, then off-diagonal) in a fixed order
     auto block_sum = [&](bool offdiag) {
@@ -1138,8 +1377,7 @@ jacobi_rot_kernel(double *__restrict__ Ag, int N, int max_sweeps, double tol, in
         for (int i = wave; i < N; i += nw)
             for (int j = lane; j < N; j += 64) {
                 const double a = A[i * ld + j];
-                if (upper && offdiag) loc += j > i ? 2.0 * (a * a) : 0.0;
-                else if (!offdiag || i != j) loc += a * a;
+                if (!offdiag || i != j) loc += a * a;
             }
         loc = wave_sum(loc);
         if (lane == 0) red[wave] = loc;
@@ -1150,22 +1388,6 @@ jacobi_rot_kernel(double *__restrict__ Ag, int N, int max_sweeps, double tol, in
         return t;
     };
     const double fro = sqrt(block_sum(false));
-    // N <= 128: rows a = P and h - 1 - P of the upper triangle of 2x2 blocks
-    // hold h + 1 blocks together, so wave w takes the row pairs P = w and
-    // w + 16 (one block per lane each, the 65th on lanes 0 and 1): at most
-    // three blocks (k, l) per lane, the same in every round
-    int kl[3][2];
-    bool on[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        const int P = j < 2 ? wave + 16 * j : wave + 16 * lane;
-        const int c = j < 2 ? lane : 64;
-        const int a = P, b = h - 1 - P;
-        const int na = h - a, nt = a < b ? h + 1 : na;
-        on[j] = upper && a <= b && c < nt && (j < 2 || lane < 2);
-        kl[j][0] = c < na ? a : b;
-        kl[j][1] = c < na ? a + c : b + (c - na);
-    }
     int sweep = 0;
     for (; sweep < max_sweeps; ++sweep) {
         const double off = sqrt(block_sum(true));
@@ -1182,70 +1404,13 @@ jacobi_rot_kernel(double *__restrict__ Ag, int N, int max_sweeps, double tol, in
                 };
                 int p = pos(k), q = pos(M - 1 - k);
                 if (p > q) { const int t = p; p = q; q = t; }
-                double c = 1.0, s = 0.0;
-                if (q < N) {
-                    const double apq = A[p * ld + q];
-                    if (apq != 0.0) {
-                        const double app = A[p * ld + p], aqq = A[q * ld + q];
-                        const double th = (aqq - app) / (2.0 * apq);
-                        const double t = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-                        c = 1.0 / sqrt(t * t + 1.0);
-                        s = t * c;
-                    }
-                }
+                const double2 cr =
+                    q < N ? jacobi_rotation(A[p * ld + p], A[p * ld + q], A[q * ld + q]) : make_double2(1.0, 0.0);
                 pq[k] = make_int2(p, q);
-                csn[k] = make_double2(c, s);
-                rot[((int64_t)sweep * (M - 1) + r) * h + k] = make_double2(c, s);
+                csn[k] = cr;
+                rot[((int64_t)sweep * (M - 1) + r) * h + k] = cr;
             }
             __syncthreads();
-            if (upper) {
-                // a round reads and writes each element of the upper triangle
-                // once (element (a, b) at (min, max)), and only the blocks'
-                // own elements, so all blocks are loaded before any is
-                // stored (the loads of a round then overlap in LDS)
-                auto cix = [&](int a, int b) { return a < b ? a * ld + b : b * ld + a; };
-                double x[3][4];
-                int4 ix[3];
-#pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    if (!on[j]) continue;
-                    const int2 u = pq[kl[j][0]], v = pq[kl[j][1]];
-                    const int pk = u.x, qk = u.y, pl = v.x, ql = v.y;
-                    ix[j] = make_int4(pk, qk, pl, ql);
-                    x[j][0] = A[cix(pk, pl)];
-                    x[j][1] = ql < N ? A[cix(pk, ql)] : 0.0;
-                    x[j][2] = qk < N ? A[cix(qk, pl)] : 0.0;
-                    x[j][3] = qk < N && ql < N ? A[cix(qk, ql)] : 0.0;
-                }
-#pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    if (!on[j]) continue;
-                    const int k = kl[j][0], l = kl[j][1];
-                    const int pk = ix[j].x, qk = ix[j].y, pl = ix[j].z, ql = ix[j].w;
-                    const bool vk = qk < N, vl = ql < N;
-                    const double2 rk = csn[k], rl = csn[l];
-                    const double ck = rk.x, sk = rk.y, cl = rl.x, sl = rl.y;
-                    const double x00 = x[j][0], x01 = x[j][1], x10 = x[j][2], x11 = x[j][3];
-                    const double y00 = cl * x00 - sl * x01, y01 = sl * x00 + cl * x01;
-                    const double y10 = cl * x10 - sl * x11, y11 = sl * x10 + cl * x11;
-                    const double z00 = ck * y00 - sk * y10, z01 = ck * y01 - sk * y11;
-                    const double z10 = sk * y00 + ck * y10, z11 = sk * y01 + ck * y11;
-                    if (l == k) {
-                        A[pk * ld + pk] = z00;
-                        if (vk) {
-                            A[cix(pk, qk)] = 0.0;
-                            A[qk * ld + qk] = z11;
-                        }
-                        continue;
-                    }
-                    A[cix(pk, pl)] = z00;
-                    if (vl) A[cix(pk, ql)] = z01;
-                    if (vk) A[cix(qk, pl)] = z10;
-                    if (vk && vl) A[cix(qk, ql)] = z11;
-                }
-                __syncthreads();
-                continue;
-            }
             for (int k = wave; k < h; k += nw) {
                 const int pk = pq[k].x, qk = pq[k].y;
                 const bool vk = qk < N;
@@ -1296,10 +1461,10 @@ jacobi_rot_kernel(double *__restrict__ Ag, int N, int max_sweeps, double tol, in
     if (tid == 0) *sweeps_out = sweep;
 }
 
-// Eigenvectors from the recorded rotations: V = J_1 J_2 ... J_R, and the
-// rows of V are independent (v <- v J per round), so one wave owns one row
-// in LDS and applies every round in order; rotations are staged through LDS
-// in groups of 16 rounds.
+// Eigenvectors of jacobi_rot_kernel: V = J_1 J_2 ... J_R, and the rows of V
+// are independent (v <- v J per round), so one wave owns one row in LDS and
+// applies every round in order; rotations are staged through LDS in groups of
+// 16 rounds.
 constexpr int kRotStage = 16;
 __global__ void __launch_bounds__(256)
 jacobi_vec_kernel(const double2 *__restrict__ rot, const int *__restrict__ sweeps, int N, double *__restrict__ Vw) {
@@ -1342,11 +1507,11 @@ jacobi_vec_kernel(const double2 *__restrict__ rot, const int *__restrict__ sweep
 // Sort ascending (rank by value, ties by index) and normalise each
 // eigenvector's sign so that its largest-magnitude entry is positive
 // (ties: the lowest index); one wave per eigenvector.
-__global__ void __launch_bounds__(1024)
+__global__ void __launch_bounds__(256)
 jacobi_sort_kernel(const double *__restrict__ diag, const double *__restrict__ Vw, int N, double *__restrict__ V,
                    double *__restrict__ evals) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    for (int j = wave; j < N; j += nw) {
+    const int lane = threadIdx.x & 63, j = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (j < N) {
         const double d = diag[j];
         int rank = 0;
         double big = -1.0;
@@ -1652,26 +1817,38 @@ rs_status trinv(const double *U, double *T, int N, const int *info_dev, hipStrea
 
 rs_status eigh(DenseWork &w, double *A, double *V, double *evals, int N, hipStream_t st, int max_sweeps) {
     max_sweeps = std::max(0, std::min(max_sweeps, kMaxSweeps));
-    const size_t lds = (size_t)N * (N + 1) * sizeof(double);
     double *diag = w.diag.as<double>();
     double2 *rot = w.rot.as<double2>();
-    if (lds <= kJacobiLds) {
-        if (!w.jacobi_lds_set) {
-            RS_HIP(hipFuncSetAttribute((const void *)jacobi_rot_kernel<true>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kJacobiLds));
-            w.jacobi_lds_set = true;
-        }
-        hipLaunchKernelGGL(jacobi_rot_kernel<true>, dim3(1), dim3(1024), lds, st, A, N, max_sweeps, 1e-15,
-                           w.sweeps.as<int>(), rot, diag);
-    } else {
-        hipLaunchKernelGGL(jacobi_rot_kernel<false>, dim3(1), dim3(1024), 0, st, A, N, max_sweeps, 1e-15,
-                           w.sweeps.as<int>(), rot, diag);
+    const size_t lds = (size_t)N * (N + 1) * sizeof(double);
+    if (lds <= kJacobiLds && !w.jacobi_lds_set) {
+        for (const void *f : {(const void *)jacobi_slot_kernel, (const void *)jacobi_rot_kernel<true>})
+            RS_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kJacobiLds));
+        w.jacobi_lds_set = true;
     }
-    RS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(jacobi_vec_kernel, dim3((N + 3) / 4), dim3(256), 0, st, rot, w.sweeps.as<int>(), N,
-                       w.mwork.as<double>());
-    RS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(jacobi_sort_kernel, dim3(1), dim3(1024), 0, st, diag, w.mwork.as<double>(), N, V, evals);
+    if (N <= kSlotMaxN) {
+        // two copies of the block triangle fit the LDS up to N = 128, and a
+        // pair per lane of the angle wave; one wave per 64 blocks beside it
+        const int h = (N + 1) / 2, nb = h * (h + 1) / 2;
+        const int nt = 64 + std::min(960, (nb + 63) / 64 * 64);
+        hipLaunchKernelGGL(jacobi_slot_kernel, dim3(1), dim3(nt), kSlotNB * 8 * sizeof(double), st, A, N,
+                           max_sweeps, 1e-15, w.sweeps.as<int>(), rot, diag);
+        RS_HIP(hipGetLastError());
+        hipLaunchKernelGGL(jacobi_slot_vec_kernel, dim3(N), dim3(64), 0, st, rot, w.sweeps.as<int>(), N,
+                           w.mwork.as<double>());
+        RS_HIP(hipGetLastError());
+    } else {
+        if (lds <= kJacobiLds)
+            hipLaunchKernelGGL(jacobi_rot_kernel<true>, dim3(1), dim3(1024), lds, st, A, N, max_sweeps, 1e-15,
+                               w.sweeps.as<int>(), rot, diag);
+        else
+            hipLaunchKernelGGL(jacobi_rot_kernel<false>, dim3(1), dim3(1024), 0, st, A, N, max_sweeps, 1e-15,
+                               w.sweeps.as<int>(), rot, diag);
+        RS_HIP(hipGetLastError());
+        hipLaunchKernelGGL(jacobi_vec_kernel, dim3((N + 3) / 4), dim3(256), 0, st, rot, w.sweeps.as<int>(), N,
+                           w.mwork.as<double>());
+        RS_HIP(hipGetLastError());
+    }
+    hipLaunchKernelGGL(jacobi_sort_kernel, dim3((N + 3) / 4), dim3(256), 0, st, diag, w.mwork.as<double>(), N, V, evals);
     RS_HIP(hipGetLastError());
     return RS_OK;
 }

@@ -126,6 +126,27 @@ def test_eigh_jacobi(small, N):
     assert np.max(np.abs(V - X)) < 1e-13 * N * nrm / gap
 
 
+# one to five players (pairs whose two players come from the same pair, a
+# dummy player), one wave of blocks and one past it, the largest size of the
+# moving-player kernel and the sizes beyond it; a matrix with equal
+# eigenvalues and one that is diagonal already
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 5, 22, 23, 88, 127, 128, 129, 131, 132])
+def test_eigh_sizes(small, N):
+    w, og, H, g, ctx = small
+    rng = np.random.default_rng(N)
+    q, _ = np.linalg.qr(rng.normal(size=(N, N)))
+    sym = rng.normal(size=(N, N))
+    twice = (q * np.repeat(np.arange(1.0, N // 2 + 2), 2)[:N]) @ q.T
+    for A in (0.5 * (sym + sym.T), 0.5 * (twice + twice.T), np.diag(rng.normal(size=N))):
+        ev, V = ctx.eigh(_dev(A))
+        ev, V = ev.cpu().numpy(), V.cpu().numpy()
+        nrm = np.linalg.norm(A, 2)
+        assert np.max(np.abs(ev - np.linalg.eigvalsh(A))) < 1e-13 * N * nrm
+        assert np.allclose(V.T @ V, np.eye(N), atol=1e-13 * N)
+        assert np.max(np.abs(A @ V - V * ev)) < 1e-13 * N * nrm
+        assert np.all(V[np.argmax(np.abs(V), axis=0), np.arange(N)] > 0)
+
+
 @pytest.mark.parametrize("dtype,nblk,B", [(np.float64, 3, 32), (np.float64, 5, 8), (np.float32, 4, 32),
                                           (np.float32, 2, 8), (np.float64, 5, 32), (np.float64, 3, 16),
                                           (np.float32, 5, 32), (np.float32, 3, 16), (np.float64, 4, 32),
