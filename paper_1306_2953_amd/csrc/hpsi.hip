@@ -354,6 +354,96 @@ hpsi_brick_kernel(const BrickRec *__restrict__ bricks, const int32_t *__restrict
 }
 
 // ---------------------------------------------------------------------------
+// One thread per (state, point), for problems too small to fill the chip with
+// bricks or columns, or with too few states for 64 lanes: a wave takes 64 / B
+// neighbouring slots of one brick, so blocks narrower than 64 states leave no
+// lane idle, all 25 loads of an output are in flight at once, and one launch
+// covers interior and surface bricks.  Same sums in the same order as the
+// per-brick kernel (bitwise equal).  It reads every value 25 times from L1
+// and L2 and is bound by that (about 90 G outputs/s in FP64, 100 in FP32),
+// where the other kernels reach 150-200 and 250-400 once they fill the chip:
+// see point_kernel for where the line lies.
+template <typename T, int B, int R>
+__global__ void __launch_bounds__(256)
+hpsi_point_kernel(const BrickRec *__restrict__ bricks, const int32_t *__restrict__ exec, int nbricks, int nwg,
+                  int nwg_pad, const T *__restrict__ psi, T *__restrict__ hpsi, const T *__restrict__ vloc, T vconst,
+                  int64_t np, T pre, T w0, T w1, T w2, T w3, const int32_t *__restrict__ brick_nl,
+                  const int32_t *__restrict__ pt_ptr, const int32_t *__restrict__ ent_atom,
+                  const T *__restrict__ ent_gamma, const T *__restrict__ dp, int nat) {
+    constexpr uint32_t ROW = B * sizeof(T);
+    const int wg = xcd_remap(blockIdx.x, nwg_pad);
+    if (wg >= nwg) return;
+    // 64 / B slots of one brick per wave
+    const uint32_t t = (uint32_t)wg * 256u + threadIdx.x;
+    const int q = (int)(t / B) % 64, s = (int)(t % B);
+    const int bi = __builtin_amdgcn_readfirstlane((int)(t / (64u * B)));
+    if (bi >= nbricks) return;
+    const int b = exec[bi];
+    const BrickRec br = bricks[b];
+    if (!((br.mask >> q) & 1ull)) return;
+    const int64_t bel = np * B;
+    const uint32_t bytes = (uint32_t)(bel * sizeof(T));
+    const rsrc_t rp = make_rsrc(psi + blockIdx.y * bel, bytes), rh = make_rsrc(hpsi + blockIdx.y * bel, bytes);
+    const uint32_t so = (uint32_t)(s * sizeof(T));
+    const int p = br.start + __popcll(br.mask & ((1ull << q) - 1ull));
+    const int c[3] = {q & 3, (q >> 2) & 3, q >> 4};
+    T v[3][9];
+    const T own = bload<T>(rp, (uint32_t)p * ROW + so);
+    if (br.flags & kBrickFast) {
+        // seven full bricks: slot and point differ by a constant
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int lo = bricks[br.nbr[2 * a]].start, hi = bricks[br.nbr[2 * a + 1]].start;
+#pragma unroll
+            for (int m = -R; m <= R; ++m) {
+                const int st = m << (2 * a), x = c[a] + m;
+                const int base = m < 0 ? (x < 0 ? lo + (4 << (2 * a)) : br.start)
+                                       : (x > 3 ? hi - (4 << (2 * a)) : br.start);
+                v[a][4 + m] = m == 0 ? own : bload<T>(rp, (uint32_t)(base + q + st) * ROW + so);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int jl = br.nbr[2 * a], jh = br.nbr[2 * a + 1];
+            const uint64_t ml = jl >= 0 ? bricks[jl].mask : 0ull, mh = jh >= 0 ? bricks[jh].mask : 0ull;
+            const int sl = jl >= 0 ? bricks[jl].start : 0, sh = jh >= 0 ? bricks[jh].start : 0;
+#pragma unroll
+            for (int m = -R; m <= R; ++m) {
+                const int x = c[a] + m;
+                const bool out = m < 0 ? x < 0 : x > 3;
+                const uint64_t mask = out ? (m < 0 ? ml : mh) : br.mask;
+                const int start = out ? (m < 0 ? sl : sh) : br.start;
+                const int qq = q + (m << (2 * a)) + (out ? (m < 0 ? 4 : -4) << (2 * a) : 0);
+                v[a][4 + m] = m == 0 ? own : bload<T>(rp, slot_off(mask, start, qq, ROW) + so);
+            }
+        }
+    }
+    if constexpr (R == 1)
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int k = 0; k < 9; ++k)
+                if (k < 3 || k > 5) v[a][k] = T(0);
+    T lap[1], acc = T(0);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        line_lap<T, 9, R>(v[a], lap, w0, w1, w2, w3);
+        acc = a == 0 ? lap[0] : acc + lap[0];
+    }
+    acc = pre * acc + (vloc == nullptr ? vconst : vloc[p]) * own;
+    if (brick_nl != nullptr && brick_nl[b]) {
+        const T *dpl = dp + (int64_t)blockIdx.y * nat * 4 * B + s;
+        for (int e = pt_ptr[p], e1 = pt_ptr[p + 1]; e < e1; ++e) {
+            const T *g = ent_gamma + 4 * (int64_t)e;
+            const T *d = dpl + ent_atom[e] * 4 * B;
+            acc += g[0] * d[0] + g[1] * d[B] + g[2] * d[2 * B] + g[3] * d[3 * B];
+        }
+    }
+    bstore<T>(acc, rh, (uint32_t)p * ROW + so);
+}
+
+// ---------------------------------------------------------------------------
 // z-marching kernel (the 25-point stencil of Sec. 5.1 plus the local
 // potential; the projector term is added by nl_add_kernel).  A work-group
 // owns one chunk: a column of 2 x 2 bricks (8 x 8 points in x-y) over nz
@@ -769,6 +859,24 @@ rs_status launch_nl_add(const rs_grid *g, const rs_nl *nl, T *hpsi, int nblk, in
     return RS_OK;
 }
 
+// Where hpsi_point_kernel is the fastest.  Measured, us per call without
+// projectors, other kernels -> point kernel:
+//  - few outputs: both others have two launches and a long chain of dependent
+//    phases, 19-36 us before the work counts.  FP64, 32^3 box: 8 states 31 ->
+//    12, 32 states 36 -> 17; 2.1M outputs 36 -> 32 (32^3), 35 -> 34 (65k
+//    points), 3.5M 37 -> 44.  FP32: 0.9M outputs 19-22 -> 15-16, 1.8M 21-24
+//    -> 20-27, 2.1M 21 -> 25.
+//  - few columns where the per-brick kernel would run (FP32, or FP64 with
+//    blocks the z-marching kernel does not take): its 64 lanes are columns.
+//    262k points, FP64 8 columns 118 -> 28, 64 columns 146 -> 200; FP32 8
+//    columns 47 -> 23, 16 columns 46-55 -> 44-46, 32 columns 47-55 -> 84.
+template <typename T> bool point_kernel(const rs_grid *g, int nblk, int B) {
+    const int64_t cols = (int64_t)nblk * B, outputs = g->np * cols;
+    if (g->nbricks * 64 * B >= (1ll << 31)) return false;   // 32-bit thread numbers
+    if (sizeof(T) == 8) return outputs <= (2 << 20) || (B % kMarchSG != 0 && cols <= 32);
+    return outputs <= (5 << 18) || cols <= 16;
+}
+
 // Applies out = pre * L psi + V psi (+ V_nl psi when nl is given), L the
 // star stencil with first-difference weights w0..w3 (see line_lap); V is
 // vloc, or the constant vconst when vloc is null.  R = 1: nearest
@@ -794,6 +902,23 @@ rs_status launch_stencil(const rs_grid *g, const rs_nl *nl, const T *vloc, T vco
     const int nat = with_nl ? nl->nat : 0;
     const int npj = with_nl ? nl->npj : 0;
     const T w0 = (T)w[0], w1 = (T)w[1], w2 = (T)w[2], w3 = (T)w[3];
+    if (point_kernel<T>(g, nblk, B)) {
+        const bool fuse = with_nl && npj == 4;
+        const int nwg = (int)((g->nbricks * 64 * B + 255) / 256), nwg_pad = (nwg + 7) & ~7;
+        const dim3 grid(nwg_pad, nblk);
+#define RS_POINT(BB)                                                                                        \
+    case BB:                                                                                                \
+        hipLaunchKernelGGL((hpsi_point_kernel<T, BB, R>), grid, dim3(256), 0, st, g->bricks.as<BrickRec>(), \
+                           g->exec.as<int32_t>(), (int)g->nbricks, nwg, nwg_pad, psi, hpsi, vloc, vconst,   \
+                           g->np, pre, w0, w1, w2, w3, fuse ? bnl : nullptr, ptp, eat, egm, dp, nat);       \
+        break;
+        switch (B) {
+            RS_POINT(1) RS_POINT(2) RS_POINT(4) RS_POINT(8) RS_POINT(16) RS_POINT(32) RS_POINT(64)
+        }
+#undef RS_POINT
+        RS_HIP(hipGetLastError());
+        return with_nl && !fuse ? launch_nl_add<T>(g, nl, hpsi, nblk, B, st) : RS_OK;
+    }
     // z-marching kernel (FP64): the full stencil when the block splits into
     // state groups of 16 columns (B = 16, 32, 64)
     if constexpr (R == 4 && sizeof(T) == 8) {

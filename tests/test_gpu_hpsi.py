@@ -105,6 +105,37 @@ def test_hpsi_fp64_march_lattice_edges(kind, n, nat):
         assert _relerr(got, want) < 1e-12, (kind, n, B)
 
 
+# Few outputs run one thread per (state, point), many the z-marching (FP64,
+# blocks of 16 and more) or the per-brick kernel: a call of many blocks
+# against the same blocks one at a time.  Periodic edges of 1, 3 and 5 bricks,
+# partial bricks on every face, a sphere, with and without projectors (16 per
+# atom take the separate add), and sizes one block either side of the line.
+@pytest.mark.parametrize("kind,n,nat,lmax", [("periodic", 4, 0, 1), ("periodic", 12, 0, 1), ("periodic", 20, 2, 3),
+                                             ("box", 13, 0, 1), ("sphere", 2.2, 3, 1)])
+@pytest.mark.parametrize("dtype,B", [(np.float64, 8), (np.float64, 16), (np.float64, 64), (np.float32, 1),
+                                     (np.float32, 32)])
+def test_hpsi_routes_agree(kind, n, nat, lmax, dtype, B):
+    g = rsd.Grid("sphere", 0.2, radius=n) if kind == "sphere" else rsd.Grid(kind, 0.25, n=n)
+    line = ((2 << 20) if dtype == np.float64 else (5 << 18)) // (g.np * B) + 1   # blocks past the line
+    many = max(line, 64 // B + 1)
+    if nat and many * B > 4096:
+        many = 4096 // B          # the projector sets' limit (below the line)
+    rng = np.random.default_rng(3)
+    npj = (lmax + 1) ** 2
+    nl = rsd.NonLocal(g, rng.uniform(0.2, 1.2, (nat, 3)), rng.uniform(0.5, 2.0, (nat, npj)), 1.0, 0.5,
+                      max_states=many * B, lmax=lmax) if nat else None
+    tdt = torch.float64 if dtype == np.float64 else torch.float32
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    psi = torch.rand((many, g.np, B), generator=gen, device=DEV, dtype=tdt) - 0.5
+    v = torch.rand(g.np, generator=gen, device=DEV, dtype=tdt)
+    got = rsd.hpsi_block(g, nl, v, psi, torch.empty_like(psi))
+    # FP64: sums of 26 terms in another order; FP32 the same order throughout
+    tol = 1e-13 if dtype == np.float64 else 1e-6
+    for k in (0, many // 2, many - 1):
+        one = rsd.hpsi_block(g, nl, v, psi[k:k + 1].clone(), torch.empty_like(psi[k:k + 1]))
+        assert float((got[k] - one[0]).abs().max()) <= tol * float(one.abs().max()), (many, k)
+
+
 def test_overlapping_spheres_no_race():
     w = synthetic.make_workload("sphere_r12_h0.2", radius=2.4, nat=8, atom_radius=0.8, rc=1.5)
     og, H, g, nl = _system(w)
