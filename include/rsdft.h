@@ -358,8 +358,8 @@ typedef struct {
  * zero states: they stay zero, get identity pivots in the orthonormalisation
  * and are left out of the Rayleigh-Ritz problem, the stopping rule and the
  * outputs.  opts NULL: m = 3, alpha = 0.52,
- * tol = 1e-6, block_stop = 1, record = 0, rr_sweeps = 0.  Allocates all workspaces (about 2(m+1)+3
- * field arrays of np * nstates elements). */
+ * tol = 1e-6, block_stop = 1, record = 0, rr_sweeps = 0.  Allocates all workspaces (four field
+ * arrays of np * nstates elements, six for m = 3). */
 rs_status rs_eigensolve_create(const rs_grid *g, const rs_nl *nl, const void *vloc,
                                int32_t nstates, int32_t B, int32_t dtype,
                                const rs_solver_opts *opts, rs_solver **out);

@@ -671,10 +671,13 @@ crop_kernel(const T *__restrict__ r, const T *__restrict__ xs, const int32_t *__
     t[gid] = tv;
 }
 
-template <typename T> struct OpSumSq {
+template <typename F> struct OpSumSq {
+    typedef F T;
+    static constexpr int NF = 1;
     const T *x;
-    __device__ void operator()(int64_t i, int, double *a) const {
-        const double v = x[i];
+    __device__ void load(int64_t i, T *v) const { v[0] = x[i]; }
+    __device__ void operator()(const T *f, int64_t, int, double *a) const {
+        const double v = f[0];
         a[0] += v * v;
     }
 };
@@ -699,22 +702,36 @@ __global__ void invs_kernel(const double *__restrict__ ss, int64_t np, int N, do
 }
 
 // ------------------------------------------------- conjugate gradients
-template <typename T> struct OpPAp {      // <p|(T - sigma) p> with q = T p
+template <typename F> struct OpPAp {      // <p|(T - sigma) p> with q = T p
+    typedef F T;
+    static constexpr int NF = 2;
     const T *p, *q;
     const double *sig;
-    __device__ void operator()(int64_t i, int c, double *a) const {
-        const double pv = p[i];
-        a[0] += pv * ((double)q[i] - sig[c] * pv);
+    __device__ void load(int64_t i, T *v) const {
+        v[0] = p[i];
+        v[1] = q[i];
+    }
+    __device__ void operator()(const T *f, int64_t, int c, double *a) const {
+        const double pv = f[0];
+        a[0] += pv * ((double)f[1] - sig[c] * pv);
     }
 };
-template <typename T> struct OpCgUpdate { // x += al p, r -= al (q - sigma p), <r|r>
+template <typename F> struct OpCgUpdate { // x += al p, r -= al (q - sigma p), <r|r>
+    typedef F T;
+    static constexpr int NF = 4;
     T *x, *r;
     const T *p, *q;
     const double *sig, *al;
-    __device__ void operator()(int64_t i, int c, double *a) const {
-        const double pv = p[i], l = al[c];
-        x[i] = (T)((double)x[i] + l * pv);
-        const double rv = (double)r[i] - l * ((double)q[i] - sig[c] * pv);
+    __device__ void load(int64_t i, T *v) const {
+        v[0] = x[i];
+        v[1] = r[i];
+        v[2] = p[i];
+        v[3] = q[i];
+    }
+    __device__ void operator()(const T *f, int64_t i, int c, double *a) const {
+        const double pv = f[2], l = al[c];
+        x[i] = (T)((double)f[0] + l * pv);
+        const double rv = (double)f[1] - l * ((double)f[3] - sig[c] * pv);
         r[i] = (T)rv;
         a[0] += rv * rv;
     }

@@ -5,19 +5,29 @@
 //   1. H psi for all blocks; Rayleigh-Ritz (subspace matrix, Jacobi, rotate).
 //   2. Per state: eps0 = <psi|H psi>/<psi|psi>, R0 = H psi - eps0 psi,
 //      residual norm.  A block whose states are all below tol is frozen.
-//   3. d = K R0 (filter), H d; the trial step lambda minimises the Rayleigh
-//      quotient of psi + lambda d (2x2 generalised problem per state);
-//      psi1 = psi + lambda d, H psi1 = H psi + lambda H d.  With a learned
-//      preconditioner its direction d_n = K_n R0 joins the filter's: the
-//      Rayleigh quotient is minimised over span{psi, d_f, d_n} (3x3 problem
-//      per state), giving K = a K_f + b K_n for the state's step (lambda 1);
-//      a singular 3x3 problem leaves the state on the filter (b = 0).
+//   3. d1 = K R0 (filter), H d1; the trial step lambda minimises the Rayleigh
+//      quotient of psi + lambda d1 (2x2 generalised problem per state); psi1 =
+//      psi + lambda d1.  With a learned preconditioner its direction d_n =
+//      K_n R0 joins the filter's: the Rayleigh quotient is minimised over
+//      span{psi, d_f, d_n} (3x3 problem per state), giving K = a K_f + b K_n
+//      for the state's step (lambda 1); a singular 3x3 problem leaves the
+//      state on the filter (b = 0).
 //   4. m - 1 DIIS iterations: residuals R_i = H psi_i - eps_i psi_i of the
 //      history; minimise |sum c R| / |sum c psi| over the history written in
 //      the basis {psi_L, psi_i - psi_L} (generalised eigenproblem per state,
-//      lowest eigenvector, c_0 = 1); psi_bar, H psi_bar, R_bar; d = K R_bar;
-//      psi_{j+1} = psi_bar + lambda d, H psi_{j+1} = H psi_bar + lambda H d.
+//      lowest eigenvector, c_0 = 1); psi_bar, R_bar; d = K R_bar; psi_{j+1} =
+//      psi_bar + lambda d.
 //   5. Orthonormalise (Cholesky, eq. 8).
+// The iterates are never formed: all of them are psi plus multiples of d1 and
+// d2, and their residuals are R0 plus multiples of psi and of d_i and H d_i,
+// so the DIIS matrices follow per state from the inner products of {psi, R0,
+// d1, g1, d2, g2}, g = H d - eps0 d.  Residuals enter as R0 and g (small as
+// the residuals themselves), not as H psi, so the products lose no digits to
+// cancellation.  One pass over {psi, R0, d1, H d1} gives lambda and the first
+// DIIS coefficients, one over those and {d2, H d2} the second, each followed
+// by one pass that writes R_bar; the last psi_bar + lambda K R_bar is formed
+// by the filter itself.  Storing the iterates and their H took 45 field reads
+// and writes a step beside H psi and the dense stage, this takes 30.
 // Per-state inner products are sums over points with FP64 accumulation and
 // a fixed-order reduction over point chunks; the small per-state problems
 // are solved in FP64, one thread per state.
@@ -27,6 +37,7 @@
 #include "colreduce.hpp"
 #include "dense.hpp"
 #include "internal.hpp"
+#include "rotation.hpp"
 
 rs_status subspace_diag_capped(rs_ctx *c, void *psi, void *hpsi, double *eig, int nblk, int B, int dtype,
                                int prec, int max_sweeps, int nreal, hipStream_t st);
@@ -38,7 +49,7 @@ namespace rs {
 rs_status hpsi_apply(const rs_grid *g, const rs_nl *nl, const void *vloc, const void *psi, void *hpsi,
                      int nblk, int B, int dtype, hipStream_t st);
 rs_status filter_apply(const rs_grid *g, double alpha, const void *r, void *out, int nblk, int B, int dtype,
-                       hipStream_t st);
+                       hipStream_t st, const FilterUpdate *upd = nullptr);
 rs_status kinetic_apply(const rs_grid *g, const void *psi, void *out, int nblk, int B, int dtype,
                         hipStream_t st);
 rs_status cnn_precondition(rs_cnn *c, const rs_grid *g, const void *r, const double *sigma, void *out, int nblk,
@@ -48,89 +59,56 @@ rs_status cnn_precondition(rs_cnn *c, const rs_grid *g, const void *r, const dou
 namespace {
 using namespace rsred;
 
-constexpr int kMaxHist = 4;   // iterates kept (m <= 3)
+constexpr int kMaxIter = 3;   // largest m
 constexpr int kMaxSweeps = 30;  // Jacobi sweeps that reach FP64 accuracy from any start
 
-template <typename T> struct OpDots2 {   // <x|x>, <x|y>
+template <typename F> struct OpDots2 {   // <x|x>, <x|y>
+    typedef F T;
+    static constexpr int NF = 2;
     const T *x, *y;
-    __device__ void operator()(int64_t i, int, double *a) const {
-        const double u = x[i], v = y[i];
+    __device__ void load(int64_t i, T *v) const {
+        v[0] = x[i];
+        v[1] = y[i];
+    }
+    __device__ void operator()(const T *w, int64_t, int, double *a) const {
+        const double u = w[0], v = w[1];
         a[0] += u * u;
         a[1] += u * v;
     }
 };
-// y = x + lambda d, hy = hx + lambda hd (per-state lambda; in place when
-// y == x), and the dots <y|y>, <y|hy> of the new iterate for its Rayleigh
-// quotient.
-template <typename T> struct OpAxpy2Dots {
-    const T *x, *hx, *d, *hd;
-    T *y, *hy;
-    const double *lam;
-    __device__ void operator()(int64_t i, int c, double *a) const {
-        const double l = lam[c];
-        const T yv = (T)((double)x[i] + l * (double)d[i]);
-        const T hv = (T)((double)hx[i] + l * (double)hd[i]);
-        y[i] = yv;
-        hy[i] = hv;
-        a[0] += (double)yv * (double)yv;
-        a[1] += (double)yv * (double)hv;
-    }
-};
-// The first DIIS pass over iterates 0 and 1 with iterate 1 formed on the
-// fly: y = x + lambda d, hy = hx + lambda hd (stored, rounded to T, for the
-// later passes), and the DIIS matrices of {x, y} as OpDiis<T, 2> forms them
-// from the stored values.  eps[N + c] (iterate 1's Rayleigh quotient) comes
-// from the trial-step dots, so no separate pass writes iterate 1.
-template <typename T> struct OpDiis2New {
-    const T *x, *hx, *d, *hd;
-    T *y, *hy;
-    const double *lam, *eps;
-    int N;
-    __device__ void operator()(int64_t i, int c, double *a) const {
-        const double l = lam[c];
-        const double u = x[i], hu = hx[i];
-        const T yv = (T)(u + l * (double)d[i]);
-        const T hv = (T)(hu + l * (double)hd[i]);
-        y[i] = yv;
-        hy[i] = hv;
-        const double xl = yv, rl = (double)hv - eps[N + c] * xl;
-        const double e1 = u - xl, r1 = (hu - eps[c] * u) - rl;
-        a[0] += rl * rl;
-        a[1] += rl * r1;
-        a[2] += r1 * r1;
-        a[3] += xl * xl;
-        a[4] += xl * e1;
-        a[5] += e1 * e1;
-    }
-};
-template <typename T> struct OpResid {   // R = h - eps x, <R|R>
+template <typename F> struct OpResid {   // R = h - eps x, <R|R>
+    typedef F T;
+    static constexpr int NF = 2;
     const T *x, *h;
     T *R;
     const double *eps;
-    __device__ void operator()(int64_t i, int c, double *a) const {
-        const T r = (T)((double)h[i] - eps[c] * (double)x[i]);
+    __device__ void load(int64_t i, T *v) const {
+        v[0] = x[i];
+        v[1] = h[i];
+    }
+    __device__ void operator()(const T *w, int64_t i, int c, double *a) const {
+        const T r = (T)((double)w[1] - eps[c] * (double)w[0]);
         R[i] = r;
         a[0] += (double)r * (double)r;
-    }
-};
-template <typename T> struct OpLam {     // <x|Hd>, <d|Hx>, <d|Hd>, <x|d>, <d|d>
-    const T *x, *hx, *d, *hd;
-    __device__ void operator()(int64_t i, int, double *a) const {
-        const double u = x[i], hu = hx[i], v = d[i], hv = hd[i];
-        a[0] += u * hv;
-        a[1] += v * hu;
-        a[2] += v * hv;
-        a[3] += u * v;
-        a[4] += v * v;
     }
 };
 // The trial subspace {x, d, e} (filter and network directions): <x|Hd>,
 // <d|Hx>, <d|Hd>, <x|d>, <d|d>, the same five for e, then <d|He>, <e|Hd>,
 // <d|e>.
-template <typename T> struct OpLam3 {
+template <typename F> struct OpLam3 {
+    typedef F T;
+    static constexpr int NF = 6;
     const T *x, *hx, *d, *hd, *e, *he;
-    __device__ void operator()(int64_t i, int, double *a) const {
-        const double u = x[i], hu = hx[i], v = d[i], hv = hd[i], w = e[i], hw = he[i];
+    __device__ void load(int64_t i, T *v) const {
+        v[0] = x[i];
+        v[1] = hx[i];
+        v[2] = d[i];
+        v[3] = hd[i];
+        v[4] = e[i];
+        v[5] = he[i];
+    }
+    __device__ void operator()(const T *f, int64_t, int, double *a) const {
+        const double u = f[0], hu = f[1], v = f[2], hv = f[3], w = f[4], hw = f[5];
         a[0] += u * hv;
         a[1] += v * hu;
         a[2] += v * hv;
@@ -146,83 +124,121 @@ template <typename T> struct OpLam3 {
         a[12] += v * w;
     }
 };
-// DIIS matrices over n = L + 1 iterates in the basis {x_L, x_i - x_L}:
-// A_ab = <r_a|r_b>, B_ab = <e_a|e_b> (upper triangles, 2 * n(n+1)/2 values)
-template <typename T, int NIT> struct OpDiis {
-    const T *x[NIT], *h[NIT];
-    const double *eps;   // [NIT][N]
-    int N;
-    __device__ void operator()(int64_t i, int c, double *a) const {
-        double e[NIT], r[NIT];
-        const double xl = x[NIT - 1][i];
-        const double rl = (double)h[NIT - 1][i] - eps[(NIT - 1) * N + c] * xl;
-        e[0] = xl;
-        r[0] = rl;
-#pragma unroll
-        for (int k = 0; k < NIT - 1; ++k) {
-            const double xk = x[k][i];
-            e[k + 1] = xk - xl;
-            r[k + 1] = ((double)h[k][i] - eps[k * N + c] * xk) - rl;
-        }
-        int t = 0;
-#pragma unroll
-        for (int p = 0; p < NIT; ++p)
-#pragma unroll
-            for (int q = p; q < NIT; ++q) {
-                a[t] += r[p] * r[q];
-                a[t + NIT * (NIT + 1) / 2] += e[p] * e[q];
-                ++t;
-            }
+// Inner products of {x, R, d, g}, g = hd - eps0 d, without <x|x> and <R|R>:
+// <x|R>, <x|d>, <x|g>, <R|d>, <R|g>, <d|d>, <d|g>, <g|g>.
+template <typename F> struct OpGram1 {
+    typedef F T;
+    static constexpr int NF = 4;
+    const T *x, *R, *d, *hd;
+    const double *eps;
+    __device__ void load(int64_t i, T *v) const {
+        v[0] = x[i];
+        v[1] = R[i];
+        v[2] = d[i];
+        v[3] = hd[i];
+    }
+    __device__ void operator()(const T *f, int64_t, int c, double *a) const {
+        const double u = f[0], r = f[1], v = f[2], g = (double)f[3] - eps[c] * v;
+        a[0] += u * r;
+        a[1] += u * v;
+        a[2] += u * g;
+        a[3] += r * v;
+        a[4] += r * g;
+        a[5] += v * v;
+        a[6] += v * g;
+        a[7] += g * g;
+    }
+};
+// The products that {e, f}, f = he - eps0 e, add: e and f with x, R, d, g,
+// then <e|e>, <e|f>, <f|f>.
+template <typename F> struct OpGram2 {
+    typedef F T;
+    static constexpr int NF = 6;
+    const T *x, *R, *d, *hd, *e, *he;
+    const double *eps;
+    __device__ void load(int64_t i, T *v) const {
+        v[0] = x[i];
+        v[1] = R[i];
+        v[2] = d[i];
+        v[3] = hd[i];
+        v[4] = e[i];
+        v[5] = he[i];
+    }
+    __device__ void operator()(const T *z, int64_t, int c, double *a) const {
+        const double w = z[4], f = (double)z[5] - eps[c] * w;
+        const double u = z[0], r = z[1], v = z[2], g = (double)z[3] - eps[c] * v;
+        a[0] += u * w;
+        a[1] += u * f;
+        a[2] += r * w;
+        a[3] += r * f;
+        a[4] += v * w;
+        a[5] += v * f;
+        a[6] += g * w;
+        a[7] += g * f;
+        a[8] += w * w;
+        a[9] += w * f;
+        a[10] += f * f;
     }
 };
 
 // --------------------------------------------------------- map kernels
-// y = x + lambda d (the newest iterate, written straight into psi)
-template <typename T>
-__global__ void __launch_bounds__(256)
-axpy1_kernel(const T *__restrict__ x, const T *__restrict__ d, T *y, const double *__restrict__ lam, int64_t np,
-             int B, const int *__restrict__ bmap) {
-    // blockIdx.y: the block (or its entry in the block map); B is a power of two
+// blockIdx.y: the block (or its entry in the block map); a thread takes
+// kMapPts values of one state (256 and its multiples are multiples of B), so
+// the state's factors are read once.
+constexpr int kMapPts = 4;
+template <typename F>
+__device__ __forceinline__ void map_block(int64_t np, int B, const int *bmap, F f) {
     const int blk = bmap ? bmap[blockIdx.y] : (int)blockIdx.y;
-    const int64_t il = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (il >= np * B) return;
-    const int64_t i = (int64_t)blk * np * B + il;
-    const int c = blk * B + (int)(il & (B - 1));
-    y[i] = (T)((double)x[i] + lam[c] * (double)d[i]);
+    const int64_t n = np * B, i0 = (int64_t)blockIdx.x * (256 * kMapPts) + threadIdx.x;
+    f(blk * B + (int)(i0 & (B - 1)), [&](auto g) {
+#pragma unroll
+        for (int k = 0; k < kMapPts; ++k)
+            if (i0 + 256 * k < n) g(blk * n + i0 + 256 * k);
+    });
+}
+dim3 map_grid(int64_t np, int B, int nblk) {
+    return dim3((unsigned)((np * B + 256 * kMapPts - 1) / (256 * kMapPts)), nblk);
 }
 
-// psi_bar = sum_a c_a e_a, H psi_bar = sum_a c_a he_a (skipped when hb is
-// null), R_bar = sum_a c_a r_a
-template <typename T> struct Hist {
-    const T *x[kMaxHist], *h[kMaxHist];
-};
-
-template <typename T, int NIT>
+// rb = R + a0 x + a1 d + a2 hd (+ a3 e + a4 he when e is given): the mixed
+// residual R_bar; lin [5][N] per state.
+template <typename T>
 __global__ void __launch_bounds__(256)
-combine_kernel(Hist<T> H, const double *__restrict__ eps, const double *__restrict__ coef, T *__restrict__ xb,
-               T *__restrict__ hb, T *__restrict__ rb, int64_t np, int B, int N, const int *__restrict__ bmap) {
-    const T *const *xs = H.x;
-    const T *const *hs = H.h;
-    // blockIdx.y: the block (or its entry in the block map); B is a power of two
-    const int blk = bmap ? bmap[blockIdx.y] : (int)blockIdx.y;
-    const int64_t il = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (il >= np * B) return;
-    const int64_t i = (int64_t)blk * np * B + il;
-    const int c = blk * B + (int)(il & (B - 1));
-    const double xl = xs[NIT - 1][i], hl = hs[NIT - 1][i];
-    const double rl = hl - eps[(NIT - 1) * N + c] * xl;
-    double sx = coef[c * kMaxHist] * xl, sh = coef[c * kMaxHist] * hl, sr = coef[c * kMaxHist] * rl;
-#pragma unroll
-    for (int k = 0; k < NIT - 1; ++k) {
-        const double ck = coef[c * kMaxHist + k + 1];
-        const double xk = xs[k][i], hk = hs[k][i];
-        sx += ck * (xk - xl);
-        sh += ck * (hk - hl);
-        sr += ck * ((hk - eps[k * N + c] * xk) - rl);
-    }
-    xb[i] = (T)sx;
-    if (hb != nullptr) hb[i] = (T)sh;
-    rb[i] = (T)sr;
+residual_mix_kernel(const T *__restrict__ x, const T *__restrict__ R, const T *__restrict__ d,
+                    const T *__restrict__ hd, const T *__restrict__ e, const T *__restrict__ he,
+                    const double *__restrict__ lin, T *__restrict__ rb, int64_t np, int B, int N,
+                    const int *__restrict__ bmap) {
+    map_block(np, B, bmap, [&](int c, auto each) {
+        const double a0 = lin[c], a1 = lin[N + c], a2 = lin[2 * N + c];
+        if (e) {
+            const double a3 = lin[3 * N + c], a4 = lin[4 * N + c];
+            each([&](int64_t i) {
+                rb[i] = (T)((double)R[i] + a0 * (double)x[i] + a1 * (double)d[i] + a2 * (double)hd[i] +
+                            a3 * (double)e[i] + a4 * (double)he[i]);
+            });
+        } else {
+            each([&](int64_t i) {
+                rb[i] = (T)((double)R[i] + a0 * (double)x[i] + a1 * (double)d[i] + a2 * (double)hd[i]);
+            });
+        }
+    });
+}
+
+// x += a0 d1 + a1 d2 + a2 dl (d1, d2 where given): the newest iterate, where
+// the filter does not form it itself; upd [3][N] per state.
+template <typename T>
+__global__ void __launch_bounds__(256)
+update_kernel(T *__restrict__ x, const T *__restrict__ d1, const T *__restrict__ d2, const T *__restrict__ dl,
+              const double *__restrict__ upd, int64_t np, int B, int N, const int *__restrict__ bmap) {
+    map_block(np, B, bmap, [&](int c, auto each) {
+        const double a0 = upd[c], a1 = upd[N + c], a2 = upd[2 * N + c];
+        each([&](int64_t i) {
+            double v = (double)x[i] + a2 * (double)dl[i];
+            if (d1) v += a0 * (double)d1[i];
+            if (d2) v += a1 * (double)d2[i];
+            x[i] = (T)v;
+        });
+    });
 }
 
 // ----------------------------------------------------- per-state solvers
@@ -305,11 +321,8 @@ __device__ __forceinline__ bool lowest_geneig(const double (&A_in)[n * n], const
         for (int p = 0; p < n; ++p)
 #pragma unroll
             for (int q = p + 1; q < n; ++q) {
-                const double apq = C[p * n + q];
-                if (apq == 0.0) continue;
-                const double th = (C[q * n + q] - C[p * n + p]) / (2.0 * apq);
-                const double t = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-                const double cs = 1.0 / sqrt(t * t + 1.0), sn = t * cs;
+                const double2 r = rs::jacobi_rotation(C[p * n + p], C[p * n + q], C[q * n + q]);
+                const double cs = r.x, sn = r.y;
 #pragma unroll
                 for (int k = 0; k < n; ++k) {
                     const double kp = C[k * n + p], kq = C[k * n + q];
@@ -358,42 +371,153 @@ __device__ __forceinline__ bool lowest_geneig(const double (&A_in)[n * n], const
     return finite;
 }
 
-// Trial step lambda (state frozen -> 0).  dots: [<x|Hx>, <x|x>] and
-// [<x|Hd>, <d|Hx>, <d|Hd>, <x|d>, <d|d>].
-__global__ void lambda_kernel(const double *__restrict__ d2, const double *__restrict__ d5,
-                              const int *__restrict__ active, int N, double *__restrict__ lam) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= N) return;
-    double l = 0.0;
-    const double b22 = d5[4 * N + c];
-    if (active[c] && b22 > 0.0) {
-        const double s = 1.0 / sqrt(b22);
-        const double a11 = d2[1 * N + c], b11 = d2[0 * N + c];
-        const double a12 = 0.5 * (d5[0 * N + c] + d5[1 * N + c]) * s;
-        const double a22 = d5[2 * N + c] * s * s;
-        const double b12 = d5[3 * N + c] * s;
-        const double A[4] = {a11, a12, a12, a22}, Bm[4] = {b11, b12, b12, 1.0};
-        double v[2];
-        if (lowest_geneig<2>(A, Bm, v) && v[0] != 0.0) l = v[1] / v[0] * s;
+// Rayleigh quotient of the Rayleigh-Ritz state from <x|x>, <x|Hx> (0 for zero
+// padding states); the sums are kept.
+struct Eps0 {
+    double *d2, *eps;
+    int N;
+    __device__ void operator()(int c, const double *s) const {
+        d2[c] = s[0];
+        d2[N + c] = s[1];
+        eps[c] = s[0] > 0.0 ? s[1] / s[0] : 0.0;
     }
-    lam[c] = l;
+};
+
+// p^T G q for the symmetric G (n x n).
+template <int n> __device__ __forceinline__ double quad(const double (&G)[n][n], const double (&p)[n], const double (&q)[n]) {
+    double t = 0.0;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        double u = 0.0;
+#pragma unroll
+        for (int j = 0; j < n; ++j) u += G[i][j] * q[j];
+        t += p[i] * u;
+    }
+    return t;
+}
+// DIIS coefficients over n iterates from the residuals rho and the differences
+// e as combinations of the k vectors of G (c_0 = 1; degenerate: e_0).
+template <int n, int k>
+__device__ __forceinline__ void diis(const double (&G)[k][k], const double (&rho)[n][k], const double (&e)[n][k],
+                                     double (&c)[n]) {
+    double A[n * n], Bm[n * n], v[n];
+#pragma unroll
+    for (int p = 0; p < n; ++p)
+#pragma unroll
+        for (int q = p; q < n; ++q) {
+            A[p * n + q] = A[q * n + p] = quad<k>(G, rho[p], rho[q]);
+            Bm[p * n + q] = Bm[q * n + p] = quad<k>(G, e[p], e[q]);
+        }
+    const bool ok = lowest_geneig<n>(A, Bm, v) && v[0] != 0.0;
+#pragma unroll
+    for (int i = 0; i < n; ++i) c[i] = ok ? v[i] / v[0] : (i == 0 ? 1.0 : 0.0);
 }
 
-// Rayleigh quotient of iterate 1 = x + lambda d from the trial-step dots:
-// (<x|Hx> + lambda (<x|Hd> + <d|Hx>) + lambda^2 <d|Hd>) /
-// (<x|x> + 2 lambda <x|d> + lambda^2 <d|d>).
-__global__ void eps1_kernel(const double *__restrict__ d2, const double *__restrict__ d5,
-                            const double *__restrict__ lam, int N, double *__restrict__ eps1) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= N) return;
-    const double l = lam[c];
-    // lambda 0 (frozen states, whose trial-step dots are not formed): iterate
-    // 1 is iterate 0
-    const double num = l == 0.0 ? d2[1 * N + c]
-                                : d2[1 * N + c] + l * (d5[0 * N + c] + d5[1 * N + c]) + l * l * d5[2 * N + c];
-    const double den = l == 0.0 ? d2[0 * N + c] : d2[0 * N + c] + 2.0 * l * d5[3 * N + c] + l * l * d5[4 * N + c];
-    eps1[c] = den > 0.0 ? num / den : 0.0;
-}
+// What the second stage needs of the first, [kStage][N]: lambda, mu, delta1,
+// and the sums of OpGram1.
+constexpr int kStage = 11;
+
+// After OpGram1: the trial step (unless lam_in, with a network, holds it;
+// frozen or zero direction: 0), iterate 1's Rayleigh quotient eps0 + delta1,
+// and the DIIS coefficients of iterates 0 and 1.  R_bar's factors go to lin,
+// the update's to upd: psi_bar = psi + mu d1.
+struct Solve1 {
+    const double *d2, *rr, *eps, *lam_in;
+    const int *active;
+    double *stage, *lin, *upd;
+    int N, m;
+    __device__ void operator()(int c, const double *s) const {
+        const double xx = d2[c], RR = rr[c], e0 = eps[c];
+        const double xR = s[0], xd = s[1], xg = s[2], Rd = s[3], Rg = s[4], dd = s[5], dg = s[6], gg = s[7];
+        double lam = 0.0;
+        if (lam_in) {
+            lam = lam_in[c];
+        } else if (active[c] && dd > 0.0) {
+            // lowest pair of H - eps0 in {x, d / |d|}
+            const double sc = 1.0 / sqrt(dd), a12 = 0.5 * (xg + Rd) * sc, b12 = xd * sc;
+            const double A[4] = {xR, a12, a12, dg * sc * sc}, Bm[4] = {xx, b12, b12, 1.0};
+            double v[2];
+            if (lowest_geneig<2>(A, Bm, v) && v[0] != 0.0) lam = v[1] / v[0] * sc;
+        }
+        double mu = lam, delta = 0.0, f[3] = {0.0, 0.0, 0.0};
+        if (lam != 0.0 && m > 1) {
+            const double n1 = xx + lam * (2.0 * xd + lam * dd);
+            delta = n1 > 0.0 ? (xR + lam * (xg + Rd) + lam * lam * dg) / n1 : 0.0;
+            const double G[4][4] = {{xx, xR, xd, xg}, {xR, RR, Rd, Rg}, {xd, Rd, dd, dg}, {xg, Rg, dg, gg}};
+            const double rho[2][4] = {{-delta, 1.0, -delta * lam, lam}, {delta, 0.0, delta * lam, -lam}};
+            const double e[2][4] = {{1.0, 0.0, lam, 0.0}, {0.0, 0.0, -lam, 0.0}};
+            double co[2];
+            diis<2, 4>(G, rho, e, co);
+            const double k1 = 1.0 - co[1];
+            mu = lam * k1;
+            f[0] = -k1 * delta;
+            f[1] = -k1 * delta * lam - mu * e0;
+            f[2] = mu;
+        }
+        stage[c] = lam;
+        stage[N + c] = mu;
+        stage[2 * N + c] = delta;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) stage[(3 + k) * N + c] = s[k];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) lin[k * N + c] = f[k];
+        upd[c] = mu;
+        upd[N + c] = 0.0;
+        upd[2 * N + c] = lam;
+    }
+};
+
+// After OpGram2: iterate 2 = psi + mu d1 + lambda d2, its Rayleigh quotient
+// eps0 + delta2, and the DIIS coefficients of iterates 0, 1 and 2.
+struct Solve2 {
+    const double *d2, *rr, *eps, *stage;
+    double *lin, *upd;
+    int N;
+    __device__ void operator()(int c, const double *s) const {
+        const double lam = stage[c], mu = stage[N + c], del1 = stage[2 * N + c], e0 = eps[c];
+        double f[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, a1 = 0.0, a2 = 0.0;
+        if (lam != 0.0) {
+            double p[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) p[k] = stage[(3 + k) * N + c];
+            // order x, R, d1, g1, d2, g2
+            const double G[6][6] = {{d2[c], p[0], p[1], p[2], s[0], s[1]}, {p[0], rr[c], p[3], p[4], s[2], s[3]},
+                                    {p[1], p[3], p[5], p[6], s[4], s[5]},  {p[2], p[4], p[6], p[7], s[6], s[7]},
+                                    {s[0], s[2], s[4], s[6], s[8], s[9]},  {s[1], s[3], s[5], s[7], s[9], s[10]}};
+            const double x2[6] = {1.0, 0.0, mu, 0.0, lam, 0.0}, g2[6] = {0.0, 1.0, 0.0, mu, 0.0, lam};
+            const double n2 = quad<6>(G, x2, x2);
+            const double del2 = n2 > 0.0 ? quad<6>(G, x2, g2) / n2 : 0.0;
+            const double r1[6] = {-del1, 1.0, -del1 * lam, lam, 0.0, 0.0};
+            double rho[3][6], e[3][6];
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                rho[0][k] = g2[k] - del2 * x2[k];
+                rho[1][k] = (k == 1 ? 1.0 : 0.0) - rho[0][k];
+                rho[2][k] = r1[k] - rho[0][k];
+                e[0][k] = x2[k];
+                e[1][k] = (k == 0 ? 1.0 : 0.0) - x2[k];
+                e[2][k] = (k == 0 ? 1.0 : k == 2 ? lam : 0.0) - x2[k];
+            }
+            double co[3], r[6];
+            diis<3, 6>(G, rho, e, co);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) r[k] = rho[0][k] + co[1] * rho[1][k] + co[2] * rho[2][k];
+            const double k2 = 1.0 - co[1] - co[2];
+            a1 = mu * k2 + lam * co[2];
+            a2 = lam * k2;
+            f[0] = r[0];
+            f[1] = r[2] - e0 * r[3];
+            f[2] = r[3];
+            f[3] = r[4] - e0 * r[5];
+            f[4] = r[5];
+        }
+#pragma unroll
+        for (int k = 0; k < 5; ++k) lin[k * N + c] = f[k];
+        upd[c] = a1;
+        upd[N + c] = a2;
+        upd[2 * N + c] = lam;
+    }
+};
 
 // Filter and network coefficients of the trial step (state frozen: lambda
 // 0).  d2: [<x|x>, <x|Hx>]; d13: the dots of OpLam3.  The Rayleigh quotient
@@ -461,41 +585,6 @@ mixdir_kernel(T *__restrict__ d, const T *__restrict__ e, T *__restrict__ hd, co
     if (hd) hd[i] = (T)(a * (double)hd[i] + b * (double)he[i]);
 }
 
-// eps of the newest iterate from its dots [<x|x>, <x|Hx>]
-__global__ void eps_kernel(const double *__restrict__ d2, int N, double *__restrict__ eps_out) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= N) return;
-    const double nn = d2[0 * N + c];
-    eps_out[c] = nn > 0.0 ? d2[1 * N + c] / nn : 0.0;     // zero (padding) states: 0
-}
-
-// DIIS coefficients per state (c_0 = 1); frozen or degenerate -> e_0.
-template <int n>
-__global__ void diis_kernel(const double *__restrict__ mats, const double *__restrict__ lam, int N,
-                            double *__restrict__ coef) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= N) return;
-    double out[kMaxHist] = {1.0, 0.0, 0.0, 0.0};
-    if (lam[c] != 0.0) {
-        double A[n * n], Bm[n * n], v[n];
-        constexpr int nt = n * (n + 1) / 2;
-        int t = 0;
-#pragma unroll
-        for (int p = 0; p < n; ++p)
-#pragma unroll
-            for (int q = p; q < n; ++q) {
-                A[p * n + q] = A[q * n + p] = mats[(int64_t)t * N + c];
-                Bm[p * n + q] = Bm[q * n + p] = mats[(int64_t)(t + nt) * N + c];
-                ++t;
-            }
-        if (lowest_geneig<n>(A, Bm, v) && v[0] != 0.0)
-#pragma unroll
-            for (int i = 0; i < n; ++i) out[i] = v[i] / v[0];
-    }
-#pragma unroll
-    for (int i = 0; i < kMaxHist; ++i) coef[c * kMaxHist + i] = out[i];
-}
-
 // eps0 = <x|Hx>/<x|x>; after the residual pass: res = sqrt(<R|R>), and a
 // block is active unless every state in it is below tol.
 // sigma_k = -<psi_k|T psi_k> / <psi_k|psi_k>
@@ -532,9 +621,10 @@ struct rs_solver {
     rs_solver_opts opts{};
     rs_ctx *ctx = nullptr;
     size_t field_bytes = 0;
-    rs::DevBuf hx[kMaxHist], hh[kMaxHist];  // history of iterates and H applied
-    rs::DevBuf R, d, hd, hpsi;
-    rs::DevBuf partial, d2, d5, rr, res, eig, lam, eps, mats, coef, active;
+    rs::DevBuf h;                // H psi; from the first DIIS iteration on R_bar
+    rs::DevBuf R;                // R0
+    rs::DevBuf d[2], hd[2];      // the directions that H was applied to (the second one for m = 3)
+    rs::DevBuf partial, d2, rr, res, eig, lam, eps, stage, lin, upd, active;
     rs::DevBuf sigma, R0;        // shifts, recorded residuals
     rs::DevBuf dn, hdn;          // network direction and H applied (with a network)
     rs::DevBuf d13, mix;         // trial-subspace dots; filter / network coefficients
@@ -575,7 +665,7 @@ extern "C" rs_status rs_eigensolve_create(const rs_grid *g, const rs_nl *nl, con
     o.record = 0;
     o.rr_sweeps = 0;
     if (opts) o = *opts;
-    if (o.m < 1 || o.m > kMaxHist - 1) { delete s; return fail(RS_EINVAL, "rs_eigensolve_create: m must be 1..3"); }
+    if (o.m < 1 || o.m > kMaxIter) { delete s; return fail(RS_EINVAL, "rs_eigensolve_create: m must be 1..3"); }
     if (o.rr_sweeps < 0 || o.rr_sweeps > kMaxSweeps) {
         delete s;
         return fail(RS_EINVAL, "rs_eigensolve_create: rr_sweeps must be 0..30");
@@ -588,23 +678,22 @@ extern "C" rs_status rs_eigensolve_create(const rs_grid *g, const rs_nl *nl, con
     s->field_bytes = (size_t)g->np * s->N * es;
     const int N = s->N;
     const int nchunks = rsred::chunk_count(g->np, B, s->nblk);
-    for (int i = 0; i <= o.m && !st; ++i) {   // iterate 0 is the caller's psi
-        if (i > 0) st = s->hx[i].alloc(s->field_bytes);
-        if (!st) st = s->hh[i].alloc(s->field_bytes);
-    }
+    st = s->h.alloc(s->field_bytes);
     if (!st) st = s->R.alloc(s->field_bytes);
-    if (!st) st = s->d.alloc(s->field_bytes);
-    if (!st) st = s->hd.alloc(s->field_bytes);
+    for (int i = 0; i < (o.m == 3 ? 2 : 1) && !st; ++i) {
+        st = s->d[i].alloc(s->field_bytes);
+        if (!st) st = s->hd[i].alloc(s->field_bytes);
+    }
     if (!st) st = s->partial.alloc(sizeof(double) * 13 * (size_t)nchunks * N);
     if (!st) st = s->d2.alloc(sizeof(double) * 2 * N);
-    if (!st) st = s->d5.alloc(sizeof(double) * 5 * N);
     if (!st) st = s->rr.alloc(sizeof(double) * N);
     if (!st) st = s->res.alloc(sizeof(double) * N);
     if (!st) st = s->eig.alloc(sizeof(double) * N);
     if (!st) st = s->lam.alloc(sizeof(double) * N);
-    if (!st) st = s->eps.alloc(sizeof(double) * kMaxHist * N);
-    if (!st) st = s->mats.alloc(sizeof(double) * 12 * N);
-    if (!st) st = s->coef.alloc(sizeof(double) * kMaxHist * N);
+    if (!st) st = s->eps.alloc(sizeof(double) * N);
+    if (!st) st = s->stage.alloc(sizeof(double) * kStage * N);
+    if (!st) st = s->lin.alloc(sizeof(double) * 5 * N);
+    if (!st) st = s->upd.alloc(sizeof(double) * 3 * N);
     if (!st) st = s->active.alloc(sizeof(int) * N);
     if (!st) st = s->sigma.alloc(sizeof(double) * N);
     if (!st) st = s->d13.alloc(sizeof(double) * 13 * N);
@@ -687,7 +776,7 @@ rs_status step_impl(rs_solver *S, T *psi, hipStream_t st) {
     const int B = S->B, nblk = S->nblk, N = S->N, m = S->opts.m;
     const double dv = g->h * g->h * g->h;
     const unsigned gs = (unsigned)((N + 63) / 64);
-    T *h0 = S->hh[0].as<T>();
+    T *h0 = S->h.as<T>(), *R = S->R.as<T>(), *d1 = S->d[0].as<T>(), *hd1 = S->hd[0].as<T>();
     double *partial = S->partial.as<double>();
     rs_status e;
     // 1. H psi, Rayleigh-Ritz
@@ -697,17 +786,15 @@ rs_status step_impl(rs_solver *S, T *psi, hipStream_t st) {
         return e;
     // shifts for the learned preconditioner: sigma = -<psi|T psi>
     if (S->cnn || S->opts.record) {
-        if ((e = kinetic_apply(g, psi, S->d.p, nblk, B, S->dtype, st))) return e;
-        if ((e = colreduce<2>(OpDots2<T>{psi, S->d.as<T>()}, np, B, nblk, dv, partial, S->d2.as<double>(), st)))
+        if ((e = kinetic_apply(g, psi, d1, nblk, B, S->dtype, st))) return e;
+        if ((e = colreduce<2>(OpDots2<T>{psi, d1}, np, B, nblk, dv, partial, S->d2.as<double>(), st)))
             return e;
         hipLaunchKernelGGL(sigma_kernel, dim3(gs), dim3(64), 0, st, S->d2.as<double>(), N, S->sigma.as<double>());
     }
     // 2. eps0, residual, activity
-    if ((e = colreduce<2>(OpDots2<T>{psi, h0}, np, B, nblk, dv, partial, S->d2.as<double>(), st))) return e;
-    hipLaunchKernelGGL(eps_kernel, dim3(gs), dim3(64), 0, st, S->d2.as<double>(), N, S->eps.as<double>());
-    if ((e = colreduce<1>(OpResid<T>{psi, h0, S->R.as<T>(), S->eps.as<double>()}, np, B, nblk, dv, partial,
-                          S->rr.as<double>(), st)))
-        return e;
+    double *eps = S->eps.as<double>(), *rr = S->rr.as<double>(), *d2 = S->d2.as<double>();
+    if ((e = colreduce_then<2>(OpDots2<T>{psi, h0}, np, B, nblk, dv, partial, Eps0{d2, eps, N}, st))) return e;
+    if ((e = colreduce<1>(OpResid<T>{psi, h0, R, eps}, np, B, nblk, dv, partial, rr, st))) return e;
     hipLaunchKernelGGL(active_kernel, dim3(gs), dim3(64), 0, st, S->rr.as<double>(), N, B, S->opts.tol,
                        S->opts.block_stop, S->res.as<double>(), S->active.as<int>());
     if (S->opts.record) RS_HIP(hipMemcpyAsync(S->R0.p, S->R.p, S->field_bytes, hipMemcpyDeviceToDevice, st));
@@ -742,118 +829,76 @@ rs_status step_impl(rs_solver *S, T *psi, hipStream_t st) {
             }
         }
     }
-    const dim3 ga((unsigned)((np * B + 255) / 256), bs.n);   // grid over the active blocks (y: map entry)
     // 3. trial step
     for (const auto &run : bs.runs) {
         const int64_t off = run.first * np * B;
-        if ((e = filter_apply(g, S->opts.alpha, S->R.as<T>() + off, S->d.as<T>() + off, run.second, B, S->dtype,
-                              st)))
-            return e;
+        if ((e = filter_apply(g, S->opts.alpha, R + off, d1 + off, run.second, B, S->dtype, st, nullptr))) return e;
     }
-    if ((e = hpsi_blocks<T>(S, S->d.as<T>(), S->hd.as<T>(), bs, st))) return e;
-    if (!S->cnn) {
-        if ((e = colreduce<5>(OpLam<T>{psi, h0, S->d.as<T>(), S->hd.as<T>()}, np, B, nblk, dv, partial,
-                              S->d5.as<double>(), st, bs.map, bs.n)))
-            return e;
-        hipLaunchKernelGGL(lambda_kernel, dim3(gs), dim3(64), 0, st, S->d2.as<double>(), S->d5.as<double>(),
-                           S->active.as<int>(), N, S->lam.as<double>());
-    } else {
+    if ((e = hpsi_blocks<T>(S, d1, hd1, bs, st))) return e;
+    if (S->cnn) {
         // the network's direction and the 3x3 trial problem; the mixed
         // direction replaces d (and H d) for the states that use it
         for (const auto &run : bs.runs) {
             const int64_t off = run.first * np * B;
-            if ((e = cnn_precondition(S->cnn, g, S->R.as<T>() + off, S->sigma.as<double>() + run.first * B,
+            if ((e = cnn_precondition(S->cnn, g, R + off, S->sigma.as<double>() + run.first * B,
                                       S->dn.as<T>() + off, run.second, B, S->dtype, st)))
                 return e;
         }
         if ((e = hpsi_blocks<T>(S, S->dn.as<T>(), S->hdn.as<T>(), bs, st))) return e;
-        if ((e = colreduce<13>(OpLam3<T>{psi, h0, S->d.as<T>(), S->hd.as<T>(), S->dn.as<T>(), S->hdn.as<T>()}, np,
-                               B, nblk, dv, partial, S->d13.as<double>(), st, bs.map, bs.n)))
+        if ((e = colreduce<13>(OpLam3<T>{psi, h0, d1, hd1, S->dn.as<T>(), S->hdn.as<T>()}, np, B, nblk, dv, partial,
+                               S->d13.as<double>(), st, bs.map, bs.n)))
             return e;
-        hipLaunchKernelGGL(mix_kernel, dim3(gs), dim3(64), 0, st, S->d2.as<double>(), S->d13.as<double>(),
-                           S->active.as<int>(), N, S->lam.as<double>(), S->mix.as<double>());
-        hipLaunchKernelGGL(mixdir_kernel<T>, ga, dim3(256), 0, st, S->d.as<T>(), S->dn.as<T>(), S->hd.as<T>(),
-                           S->hdn.as<T>(), S->mix.as<double>(), np, B, N, bs.map);
+        hipLaunchKernelGGL(mix_kernel, dim3(gs), dim3(64), 0, st, d2, S->d13.as<double>(), S->active.as<int>(), N,
+                           S->lam.as<double>(), S->mix.as<double>());
+        hipLaunchKernelGGL(mixdir_kernel<T>, dim3((unsigned)((np * B + 255) / 256), bs.n), dim3(256), 0, st, d1,
+                           S->dn.as<T>(), hd1, S->hdn.as<T>(), S->mix.as<double>(), np, B, N, bs.map);
         RS_HIP(hipGetLastError());
     }
-    // history: iterate 0 is psi itself
-    const T *xs[kMaxHist], *hs[kMaxHist];
-    xs[0] = psi;
-    hs[0] = h0;
+    double *stage = S->stage.as<double>(), *lin = S->lin.as<double>(), *upd = S->upd.as<double>();
+    const dim3 ga = map_grid(np, B, bs.n);
+    if ((e = colreduce_then<8>(OpGram1<T>{psi, R, d1, hd1, eps}, np, B, nblk, dv, partial,
+                               Solve1{d2, rr, eps, S->cnn ? S->lam.as<double>() : nullptr, S->active.as<int>(), stage,
+                                      lin, upd, N, m},
+                               st, bs.map, bs.n)))
+        return e;
     if (m == 1) {
-        // the trial iterate is the newest: straight into psi (in place)
-        hipLaunchKernelGGL(axpy1_kernel<T>, ga, dim3(256), 0, st, psi, S->d.as<T>(), psi,
-                           S->lam.as<double>(), np, B, bs.map);
+        // the trial iterate is the newest: straight into psi
+        hipLaunchKernelGGL(update_kernel<T>, ga, dim3(256), 0, st, psi, (const T *)nullptr, (const T *)nullptr, d1,
+                           upd, np, B, N, bs.map);
         RS_HIP(hipGetLastError());
         return RS_OK;
     }
-    // iterate 1: with the filter alone its Rayleigh quotient follows from
-    // the trial-step dots and the first DIIS pass writes it; with a network
-    // (mixed directions) a pass of its own writes it and its dots
-    const bool fused1 = !S->cnn;
-    if (fused1) {
-        hipLaunchKernelGGL(eps1_kernel, dim3(gs), dim3(64), 0, st, S->d2.as<double>(), S->d5.as<double>(),
-                           S->lam.as<double>(), N, S->eps.as<double>() + N);
-    } else if ((e = colreduce<2>(OpAxpy2Dots<T>{psi, h0, S->d.as<T>(), S->hd.as<T>(), S->hx[1].as<T>(),
-                                               S->hh[1].as<T>(), S->lam.as<double>()},
-                                 np, B, nblk, dv, partial, S->d2.as<double>(), st, bs.map, bs.n))) {
-        return e;
-    }
-    xs[1] = S->hx[1].as<T>();
-    hs[1] = S->hh[1].as<T>();
-    for (int n = 2; n <= m; ++n) {
-        // 4. DIIS iteration over the n iterates 0..n-1: eps of the newest
-        // (its dots were accumulated when it was written)
-        if (n > 2 || !fused1)
-            hipLaunchKernelGGL(eps_kernel, dim3(gs), dim3(64), 0, st, S->d2.as<double>(), N,
-                               S->eps.as<double>() + (int64_t)(n - 1) * N);
-        if (n == 2 && fused1) {
-            OpDiis2New<T> op{psi, h0, S->d.as<T>(), S->hd.as<T>(), S->hx[1].as<T>(), S->hh[1].as<T>(),
-                             S->lam.as<double>(), S->eps.as<double>(), N};
-            if ((e = colreduce<6>(op, np, B, nblk, dv, partial, S->mats.as<double>(), st, bs.map, bs.n))) return e;
-        } else if (n == 2) {
-            OpDiis<T, 2> op{{xs[0], xs[1]}, {hs[0], hs[1]}, S->eps.as<double>(), N};
-            if ((e = colreduce<6>(op, np, B, nblk, dv, partial, S->mats.as<double>(), st, bs.map, bs.n))) return e;
-        } else {
-            OpDiis<T, 3> op{{xs[0], xs[1], xs[2]}, {hs[0], hs[1], hs[2]}, S->eps.as<double>(), N};
-            if ((e = colreduce<12>(op, np, B, nblk, dv, partial, S->mats.as<double>(), st, bs.map, bs.n)))
-                return e;
-        }
-        hipLaunchKernelGGL(n == 2 ? diis_kernel<2> : diis_kernel<3>, dim3(gs), dim3(64), 0, st, S->mats.as<double>(),
-                           S->lam.as<double>(), N, S->coef.as<double>());
-        // psi_bar, H psi_bar into slot n; R_bar into R.  The last iteration
-        // needs no H psi_bar (nothing follows that would use it)
-        T *xb = S->hx[n].as<T>(), *hb = n < m ? S->hh[n].as<T>() : nullptr;
-        Hist<T> hist{};
-        for (int i = 0; i < n; ++i) {
-            hist.x[i] = xs[i];
-            hist.h[i] = hs[i];
-        }
-        if (n == 2)
-            hipLaunchKernelGGL((combine_kernel<T, 2>), ga, dim3(256), 0, st, hist, S->eps.as<double>(),
-                               S->coef.as<double>(), xb, hb, S->R.as<T>(), np, B, N, bs.map);
-        else
-            hipLaunchKernelGGL((combine_kernel<T, 3>), ga, dim3(256), 0, st, hist, S->eps.as<double>(),
-                               S->coef.as<double>(), xb, hb, S->R.as<T>(), np, B, N, bs.map);
-        RS_HIP(hipGetLastError());
-        if ((e = precond<T>(S, S->R.as<T>(), S->d.as<T>(), bs, st))) return e;
-        // H d only where another DIIS iteration follows: the last update
-        // needs d alone
-        if (n < m && (e = hpsi_blocks<T>(S, S->d.as<T>(), S->hd.as<T>(), bs, st))) return e;
-        if (n < m) {
-            if ((e = colreduce<2>(OpAxpy2Dots<T>{xb, hb, S->d.as<T>(), S->hd.as<T>(), xb, hb, S->lam.as<double>()},
-                                  np, B, nblk, dv, partial, S->d2.as<double>(), st, bs.map, bs.n)))
-                return e;
-        } else {
-            // the newest iterate goes straight into psi; its H psi is not
-            // needed
-            hipLaunchKernelGGL(axpy1_kernel<T>, ga, dim3(256), 0, st, xb, S->d.as<T>(), psi,
-                               S->lam.as<double>(), np, B, bs.map);
-        }
-        xs[n] = xb;
-        hs[n] = hb;
-    }
+    // 4. DIIS: R_bar (over H psi, which nothing reads any more)
+    T *rb = h0, *d2f = nullptr, *dl = hd1;
+    hipLaunchKernelGGL(residual_mix_kernel<T>, ga, dim3(256), 0, st, psi, R, d1, hd1, (const T *)nullptr,
+                       (const T *)nullptr, lin, rb, np, B, N, bs.map);
     RS_HIP(hipGetLastError());
+    if (m == 3) {
+        T *hd2 = S->hd[1].as<T>();
+        d2f = S->d[1].as<T>();
+        dl = hd2;
+        if ((e = precond<T>(S, rb, d2f, bs, st))) return e;
+        if ((e = hpsi_blocks<T>(S, d2f, hd2, bs, st))) return e;
+        if ((e = colreduce_then<11>(OpGram2<T>{psi, R, d1, hd1, d2f, hd2, eps}, np, B, nblk, dv, partial,
+                                    Solve2{d2, rr, eps, stage, lin, upd, N}, st, bs.map, bs.n)))
+            return e;
+        hipLaunchKernelGGL(residual_mix_kernel<T>, ga, dim3(256), 0, st, psi, R, d1, hd1, d2f, hd2, lin, rb, np, B, N,
+                           bs.map);
+        RS_HIP(hipGetLastError());
+    }
+    // the newest iterate, straight into psi: formed by the filter, or with a
+    // network after its direction (which goes where H d is no longer read)
+    if (S->cnn) {
+        if ((e = precond<T>(S, rb, dl, bs, st))) return e;
+        hipLaunchKernelGGL(update_kernel<T>, ga, dim3(256), 0, st, psi, d1, d2f, dl, upd, np, B, N, bs.map);
+        RS_HIP(hipGetLastError());
+        return RS_OK;
+    }
+    for (const auto &run : bs.runs) {
+        const int64_t off = run.first * np * B;
+        const FilterUpdate u{psi + off, d1 + off, d2f ? d2f + off : nullptr, upd + run.first * B, N};
+        if ((e = filter_apply(g, S->opts.alpha, rb + off, psi + off, run.second, B, S->dtype, st, &u))) return e;
+    }
     return RS_OK;
 }
 

@@ -46,6 +46,13 @@ template <> __device__ __forceinline__ float bload<float>(rsrc_t r, uint32_t off
 template <> __device__ __forceinline__ double bload<double>(rsrc_t r, uint32_t off) {
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
 }
+// Non-temporal: values that nothing reads again.
+template <typename T> __device__ __forceinline__ T bload_nt(rsrc_t r, uint32_t off) {
+    if constexpr (sizeof(T) == 4)
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 2));
+    else
+        return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 2));
+}
 // Cache policy of the field stores: non-temporal (the outputs are not read
 // again by this kernel, so they should not evict neighbour data from L2).
 constexpr int kStoreAux = 2;
@@ -143,6 +150,11 @@ struct Slots {
             bstore<T>(v, r, __builtin_elementwise_add_sat(lane_off, tbl[q]));
         }
     }
+    // byte offset of slot q plus the lane's (beyond every buffer when empty)
+    __device__ __forceinline__ uint32_t offset(uint32_t lane_off, int q) const {
+        if constexpr (FAST) return lane_off + base + (uint32_t)(q * ROW);
+        else return __builtin_elementwise_add_sat(lane_off, tbl[q]);
+    }
     __device__ __forceinline__ bool has(int q) const {
         if constexpr (FAST) return true;
         else return tbl[q] != kOOB;
@@ -153,6 +165,37 @@ struct Slots {
         else return (int)(tbl[q] / ROW);
     }
 };
+
+// The fields and per-state factors of a fused state update (FilterUpdate) for
+// one lane's state column; UPD false: none.
+template <typename T, bool UPD> struct Update {};
+template <typename T> struct Update<T, true> {
+    rsrc_t x, d1, d2;
+    double a1, a2, lam;
+    __device__ __forceinline__ void load(T (&v)[3], uint32_t off) const {
+        // without d1 or d2 the loads read past a zero-sized buffer (0)
+        v[0] = bload_nt<T>(x, off);
+        v[1] = bload_nt<T>(d1, off);
+        v[2] = bload_nt<T>(d2, off);
+    }
+    __device__ __forceinline__ T operator()(T kr, const T (&v)[3]) const {
+        return (T)((double)v[0] + a1 * (double)v[1] + a2 * (double)v[2] + lam * (double)kr);
+    }
+};
+// off: byte offset of the buffers' first element, c: the lane's state
+template <typename T, bool UPD>
+__device__ __forceinline__ Update<T, UPD> make_update(const FilterUpdate &u, int64_t off, uint32_t bytes, int c) {
+    Update<T, UPD> r;
+    if constexpr (UPD) {
+        r.x = make_rsrc((const char *)u.x + off, bytes);
+        r.d1 = make_rsrc((const char *)u.d1 + off, u.d1 ? bytes : 0u);
+        r.d2 = make_rsrc((const char *)u.d2 + off, u.d2 ? bytes : 0u);
+        r.a1 = u.d1 ? u.coef[c] : 0.0;
+        r.a2 = u.d2 ? u.coef[u.stride + c] : 0.0;
+        r.lam = u.coef[2 * u.stride + c];
+    }
+    return r;
+}
 
 // Phase fence: the accumulators are materialised (an empty asm that
 // reads and writes them) and the scheduler may not move instructions
@@ -174,13 +217,13 @@ constexpr int kPhaseLines = 4;     // stencil lines per phase
 // Everything that locates points (brick records, masks, offsets) is uniform
 // in the wave and lives in scalar registers; a lane's address is its column
 // offset plus the uniform slot offset.
-template <typename T, int ROW, int NZ, int Z0, bool FAST, int R>
+template <typename T, int ROW, int NZ, int Z0, bool FAST, int R, bool UPD>
 __device__ __forceinline__ void
 hpsi_wave(const BrickRec &br, const BrickRec *__restrict__ bricks, int b, rsrc_t rp, rsrc_t rh,
           uint32_t lane_off, const uint32_t *tbl, const T *__restrict__ vloc, T vconst, T pre, T w0,
           T w1, T w2, T w3, const int32_t *__restrict__ brick_nl, const int32_t *__restrict__ pt_ptr,
           const int32_t *__restrict__ ent_atom, const T *__restrict__ ent_gamma,
-          const T *__restrict__ dpl, int B) {
+          const T *__restrict__ dpl, int B, const Update<T, UPD> &upd) {
     constexpr int NP = 16 * NZ;
     Slots<T, ROW, FAST> nb[6], me;
 #pragma unroll
@@ -280,9 +323,21 @@ hpsi_wave(const BrickRec &br, const BrickRec *__restrict__ bricks, int b, rsrc_t
             }
         }
     }
+    if constexpr (UPD) {
+        // eight points' fields are loaded before any is used (left alone, the
+        // compiler waits for one load at a time)
 #pragma unroll
-    for (int k = 0; k < NP; ++k) {
-        me.store(acc[k], rh, lane_off, Z0 * 16 + k);
+        for (int k0 = 0; k0 < NP; k0 += 8) {
+            T f[8][3];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) upd.load(f[k], me.offset(lane_off, Z0 * 16 + k0 + k));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) me.store(upd(acc[k0 + k], f[k]), rh, lane_off, Z0 * 16 + k0 + k);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) me.store(acc[k], rh, lane_off, Z0 * 16 + k);
     }
 }
 
@@ -291,7 +346,7 @@ hpsi_wave(const BrickRec &br, const BrickRec *__restrict__ bricks, int b, rsrc_t
 // interior bricks, FAST, whose neighbours are all full, and the rest).  A
 // brick is split into 4/NZ parts of NZ z-planes, one wave each.  B is a
 // template parameter so that the row size B * sizeof(T) is a constant.
-template <typename T, int B, int NZ, bool FAST, int R>
+template <typename T, int B, int NZ, bool FAST, int R, bool UPD>
 __global__ void __launch_bounds__(256)
 hpsi_brick_kernel(const BrickRec *__restrict__ bricks, const int32_t *__restrict__ exec,
                   int nexec, int nwg, int nwg_pad, const T *__restrict__ psi,
@@ -299,7 +354,7 @@ hpsi_brick_kernel(const BrickRec *__restrict__ bricks, const int32_t *__restrict
                   T pre, T w0, T w1, T w2, T w3,
                   const int32_t *__restrict__ brick_nl, const int32_t *__restrict__ pt_ptr,
                   const int32_t *__restrict__ ent_atom, const T *__restrict__ ent_gamma,
-                  const T *__restrict__ dp, int nat) {
+                  const T *__restrict__ dp, int nat, FilterUpdate u) {
     constexpr int PARTS = 4 / NZ;
     constexpr int ROW = B * (int)sizeof(T);
     __shared__ uint32_t tbl_all[FAST ? 1 : 4 * 7 * 64];
@@ -344,9 +399,10 @@ hpsi_brick_kernel(const BrickRec *__restrict__ bricks, const int32_t *__restrict
     const uint32_t lane_off = (uint32_t)(((blk - blk0) * blk_elems + s) * sizeof(T));
     const T *dpl = dp ? dp + (int64_t)blk * nat * 4 * B + s : nullptr;
     const BrickRec br = bricks[b];
+    const Update<T, UPD> upd = make_update<T, UPD>(u, blk0 * blk_elems * (int64_t)sizeof(T), bytes, col);
 #define RS_PART(ZZ)                                                                            \
-    hpsi_wave<T, ROW, NZ, ZZ, FAST, R>(br, bricks, b, rp, rh, lane_off, tbl, vloc, vconst, pre, w0, w1, w2, w3, \
-                                    brick_nl, pt_ptr, ent_atom, ent_gamma, dpl, B)
+    hpsi_wave<T, ROW, NZ, ZZ, FAST, R, UPD>(br, bricks, b, rp, rh, lane_off, tbl, vloc, vconst, pre, w0, w1, w2, w3, \
+                                    brick_nl, pt_ptr, ent_atom, ent_gamma, dpl, B, upd)
     if (part == 0) RS_PART(0);
     if constexpr (PARTS >= 2) { if (part == 1) RS_PART(NZ); }
     if constexpr (PARTS == 4) { if (part == 2) RS_PART(2 * NZ); if (part == 3) RS_PART(3 * NZ); }
@@ -363,13 +419,13 @@ hpsi_brick_kernel(const BrickRec *__restrict__ bricks, const int32_t *__restrict
 // and L2 and is bound by that (about 90 G outputs/s in FP64, 100 in FP32),
 // where the other kernels reach 150-200 and 250-400 once they fill the chip:
 // see point_kernel for where the line lies.
-template <typename T, int B, int R>
+template <typename T, int B, int R, bool UPD>
 __global__ void __launch_bounds__(256)
 hpsi_point_kernel(const BrickRec *__restrict__ bricks, const int32_t *__restrict__ exec, int nbricks, int nwg,
                   int nwg_pad, const T *__restrict__ psi, T *__restrict__ hpsi, const T *__restrict__ vloc, T vconst,
                   int64_t np, T pre, T w0, T w1, T w2, T w3, const int32_t *__restrict__ brick_nl,
                   const int32_t *__restrict__ pt_ptr, const int32_t *__restrict__ ent_atom,
-                  const T *__restrict__ ent_gamma, const T *__restrict__ dp, int nat) {
+                  const T *__restrict__ ent_gamma, const T *__restrict__ dp, int nat, FilterUpdate u) {
     constexpr uint32_t ROW = B * sizeof(T);
     const int wg = xcd_remap(blockIdx.x, nwg_pad);
     if (wg >= nwg) return;
@@ -440,7 +496,15 @@ hpsi_point_kernel(const BrickRec *__restrict__ bricks, const int32_t *__restrict
             acc += g[0] * d[0] + g[1] * d[B] + g[2] * d[2 * B] + g[3] * d[3 * B];
         }
     }
-    bstore<T>(acc, rh, (uint32_t)p * ROW + so);
+    const uint32_t off = (uint32_t)p * ROW + so;
+    if constexpr (UPD) {
+        const Update<T, UPD> upd =
+            make_update<T, UPD>(u, blockIdx.y * bel * (int64_t)sizeof(T), bytes, (int)blockIdx.y * B + s);
+        T f[3];
+        upd.load(f, off);
+        acc = upd(acc, f);
+    }
+    bstore<T>(acc, rh, off);
 }
 
 // ---------------------------------------------------------------------------
@@ -880,10 +944,11 @@ template <typename T> bool point_kernel(const rs_grid *g, int nblk, int B) {
 // Applies out = pre * L psi + V psi (+ V_nl psi when nl is given), L the
 // star stencil with first-difference weights w0..w3 (see line_lap); V is
 // vloc, or the constant vconst when vloc is null.  R = 1: nearest
-// neighbours only (w1 = w2 = w3 = 0).
-template <typename T, int R = 4>
+// neighbours only (w1 = w2 = w3 = 0).  UPD: out is updated as FilterUpdate says.
+template <typename T, int R = 4, bool UPD = false>
 rs_status launch_stencil(const rs_grid *g, const rs_nl *nl, const T *vloc, T vconst, const T *psi, T *hpsi,
-                         int nblk, int B, double pre_d, const double w[4], hipStream_t st) {
+                         int nblk, int B, double pre_d, const double w[4], hipStream_t st,
+                         const FilterUpdate &upd = FilterUpdate{}) {
     if (g->nbricks == 0) return RS_OK;
     if ((uint64_t)g->np * 64 * sizeof(T) > kMaxField)
         return fail(RS_ENOTSUP, "stencil: 64 state columns of the grid exceed 4 GiB");
@@ -908,9 +973,9 @@ rs_status launch_stencil(const rs_grid *g, const rs_nl *nl, const T *vloc, T vco
         const dim3 grid(nwg_pad, nblk);
 #define RS_POINT(BB)                                                                                        \
     case BB:                                                                                                \
-        hipLaunchKernelGGL((hpsi_point_kernel<T, BB, R>), grid, dim3(256), 0, st, g->bricks.as<BrickRec>(), \
+        hipLaunchKernelGGL((hpsi_point_kernel<T, BB, R, UPD>), grid, dim3(256), 0, st, g->bricks.as<BrickRec>(), \
                            g->exec.as<int32_t>(), (int)g->nbricks, nwg, nwg_pad, psi, hpsi, vloc, vconst,   \
-                           g->np, pre, w0, w1, w2, w3, fuse ? bnl : nullptr, ptp, eat, egm, dp, nat);       \
+                           g->np, pre, w0, w1, w2, w3, fuse ? bnl : nullptr, ptp, eat, egm, dp, nat, upd);  \
         break;
         switch (B) {
             RS_POINT(1) RS_POINT(2) RS_POINT(4) RS_POINT(8) RS_POINT(16) RS_POINT(32) RS_POINT(64)
@@ -976,15 +1041,15 @@ rs_status launch_stencil(const rs_grid *g, const rs_nl *nl, const T *vloc, T vco
 #define RS_HPSI(BB)                                                                                \
     case BB:                                                                                       \
         if (fast)                                                                                  \
-            hipLaunchKernelGGL((hpsi_brick_kernel<T, BB, NZF, true, R>), grid, dim3(256), 0, st,     \
+            hipLaunchKernelGGL((hpsi_brick_kernel<T, BB, NZF, true, R, UPD>), grid, dim3(256), 0, st,     \
                                g->bricks.as<BrickRec>(), ex, (int)nexec, nwg, nwg_pad, psi, hpsi, \
                                vloc, vconst, g->np, nblk, pre, w0, w1, w2, w3, bnl, ptp, eat, egm, \
-                               dp, nat);                                                          \
+                               dp, nat, upd);                                                     \
         else                                                                                       \
-            hipLaunchKernelGGL((hpsi_brick_kernel<T, BB, NZS, false, R>), grid, dim3(256), 0, st,    \
+            hipLaunchKernelGGL((hpsi_brick_kernel<T, BB, NZS, false, R, UPD>), grid, dim3(256), 0, st,    \
                                g->bricks.as<BrickRec>(), ex, (int)nexec, nwg, nwg_pad, psi, hpsi, \
                                vloc, vconst, g->np, nblk, pre, w0, w1, w2, w3, bnl, ptp, eat, egm, \
-                               dp, nat);                                                          \
+                               dp, nat, upd);                                                     \
         break;
         switch (B) {
             RS_HPSI(1) RS_HPSI(2) RS_HPSI(4) RS_HPSI(8) RS_HPSI(16) RS_HPSI(32) RS_HPSI(64)
@@ -1097,15 +1162,20 @@ rs_status hpsi_apply(const rs_grid *g, const rs_nl *nl, const void *vloc, const 
 
 // Filter preconditioner: K r = alpha r + (1 - alpha)/6 (sum of the six nearest
 // neighbours) = r + (1 - alpha)/6 L7 r, L7 the 7-point second difference
-// (first-difference weights (1, 0, 0, 0)); zero outside the domain.
+// (first-difference weights (1, 0, 0, 0)); zero outside the domain.  With upd
+// the states are updated instead of K r being stored (r must not be out).
 rs_status filter_apply(const rs_grid *g, double alpha, const void *r, void *out, int nblk, int B, int dtype,
-                       hipStream_t st) {
+                       hipStream_t st, const FilterUpdate *upd) {
     const double w[4] = {1.0, 0.0, 0.0, 0.0};
     const double pre = (1.0 - alpha) / 6.0;
-    if (dtype == RS_F64)
-        return launch_stencil<double, 1>(g, nullptr, nullptr, 1.0, (const double *)r, (double *)out, nblk, B, pre, w,
-                                         st);
-    return launch_stencil<float, 1>(g, nullptr, nullptr, 1.0f, (const float *)r, (float *)out, nblk, B, pre, w, st);
+    auto go = [&](auto t) {
+        typedef decltype(t) T;
+        if (upd)
+            return launch_stencil<T, 1, true>(g, nullptr, nullptr, T(1), (const T *)r, (T *)out, nblk, B, pre, w, st,
+                                              *upd);
+        return launch_stencil<T, 1>(g, nullptr, nullptr, T(1), (const T *)r, (T *)out, nblk, B, pre, w, st);
+    };
+    return dtype == RS_F64 ? go(0.0) : go(0.0f);
 }
 
 }  // namespace rs

@@ -93,6 +93,15 @@ struct MarchChunk {
     int32_t nz;    // brick layers written
 };
 
+// What filter_apply does with K r when the update of the states follows at
+// once: out = x + coef[0] d1 + coef[1] d2 + coef[2] K r, coef [3][stride] per
+// state (FP64 sums, rounded once), x == out allowed; d1 may be null, and d2.
+struct FilterUpdate {
+    const void *x, *d1, *d2;
+    const double *coef;
+    int64_t stride;
+};
+
 }  // namespace rs
 
 struct rs_grid {

@@ -51,6 +51,27 @@ def test_one_step_matches_oracle(m):
     assert np.max(np.abs(got - want["psi"])) < 1e-10 * np.max(np.abs(want["psi"]))
 
 
+# the field kernels' edges: one and two states a block, a last block of
+# padding states, fewer columns than a reduction's 8, a grid whose rows end
+# inside a thread's four values
+@pytest.mark.parametrize("N,B,radius", [(5, 1, 2.0), (7, 2, 2.1), (13, 8, 2.2), (20, 64, 2.0)])
+@pytest.mark.parametrize("m", [2, 3])
+def test_step_block_edges_match_oracle(N, B, radius, m):
+    w = synthetic.make_workload("sphere_r12_h0.2", radius=radius, nat=2, atom_radius=1.0)
+    og, H, g, solver, psi = _setup(w, N, B, m=m, tol=1e-12)
+    opts = rmmdiis.Options(m=m, block=B, tol=1e-12)
+    for _ in range(2):
+        psi = rmmdiis.rmmdiis_step(H, psi, opts)["psi"]
+    want = rmmdiis.rmmdiis_step(H, psi, opts)
+    t = torch.from_numpy(rsd.to_blocks(psi, B)).to(DEV)
+    eig, res, _ = solver.step(t)
+    got = rsd.from_blocks(t.cpu().numpy(), N)
+    assert np.max(np.abs(eig - want["eig"])) < 1e-12 * np.max(np.abs(want["eig"]))
+    assert np.max(np.abs(res - want["resnorm"])) < 1e-10 * np.max(want["resnorm"])
+    assert np.max(np.abs(got - want["psi"])) < 1e-10 * np.max(np.abs(want["psi"]))
+    assert not np.any(t.cpu().numpy()[-1, :, N - (N - 1) // B * B:])      # padding stays zero
+
+
 def test_block_stop_freezes_converged_blocks():
     w = synthetic.make_workload("sphere_r12_h0.2", radius=2.4, nat=3, atom_radius=1.2)
     N, B = 16, 8
