@@ -55,10 +55,7 @@ constexpr size_t kJacobiLds = 136 * 1024;   // dynamic LDS for the Jacobi matrix
 constexpr int kMaxSweeps = 30;             // Jacobi sweep cap (rotation record size)
 constexpr int MAXB = 16;    // 16x16 blocks per wave
 
-// NBW > 0: every wave owns exactly NBW blocks (b1 - b0 == 4 * NBW), and the
-// MFMAs run k outer, blocks inner, so consecutive ones feed independent
-// accumulators; NBW == 0: any share, one block's k steps at a time.
-template <bool SYRK, int NBW>
+template <bool SYRK>
 __global__ void __launch_bounds__(256)
 gram_f64_kernel(const double *__restrict__ X, const double *__restrict__ Y, int64_t np, int B, int N,
                 int N16, int CP, const int2 *__restrict__ blocks, int nblocks, int bps,
@@ -74,14 +71,6 @@ gram_f64_kernel(const double *__restrict__ X, const double *__restrict__ Y, int6
     d4 acc[MAXB];
 #pragma unroll
     for (int i = 0; i < MAXB; ++i) acc[i] = d4{0, 0, 0, 0};
-    constexpr int NB = NBW > 0 ? NBW : 1;
-    int bx[NB], by[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        const int2 blk = NBW > 0 ? blocks[b0 + wave + 4 * i] : int2{0, 0};
-        bx[i] = blk.x;
-        by[i] = blk.y;
-    }
     for (int64_t p0 = p_beg; p0 < p_end; p0 += KC64) {
         for (int e = tid; e < KC64 * N16; e += 256) {
             const int p = e / N16, j = e % N16;
@@ -90,30 +79,17 @@ gram_f64_kernel(const double *__restrict__ X, const double *__restrict__ Y, int6
             if constexpr (!SYRK) ty[e] = ok ? Y[bidx(np, B, p0 + p, j)] : 0.0;
         }
         __syncthreads();
-        if constexpr (NBW > 0) {
 #pragma unroll
-            for (int kk = 0; kk < KC64 / 4; ++kk) {
-                const int p = kk * 4 + lane / 16;
+        for (int i = 0; i < MAXB; ++i) {
+            const int bb = b0 + wave + 4 * i;
+            if (bb < b1) {
+                const int2 blk = blocks[bb];
 #pragma unroll
-                for (int i = 0; i < NBW; ++i) {
-                    const double a = tx[p * N16 + bx[i] * 16 + lane % 16];
-                    const double b = ty[p * N16 + by[i] * 16 + lane % 16];
+                for (int kk = 0; kk < KC64 / 4; ++kk) {
+                    const int p = kk * 4 + lane / 16;
+                    const double a = tx[p * N16 + blk.x * 16 + lane % 16];
+                    const double b = ty[p * N16 + blk.y * 16 + lane % 16];
                     acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[i], 0, 0, 0);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < MAXB; ++i) {
-                const int bb = b0 + wave + 4 * i;
-                if (bb < b1) {
-                    const int2 blk = blocks[bb];
-#pragma unroll
-                    for (int kk = 0; kk < KC64 / 4; ++kk) {
-                        const int p = kk * 4 + lane / 16;
-                        const double a = tx[p * N16 + blk.x * 16 + lane % 16];
-                        const double b = ty[p * N16 + blk.y * 16 + lane % 16];
-                        acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[i], 0, 0, 0);
-                    }
                 }
             }
         }
@@ -479,6 +455,253 @@ gram_bf16x3_kernel(const float *__restrict__ X, const float *__restrict__ Y, int
             for (int r = 0; r < 4; ++r)
                 out[(int64_t)(blk.x * 16 + 4 * (lane / 16) + r) * N16 + blk.y * 16 + lane % 16] = acc[i][r];
         }
+    }
+}
+
+// ------------------------------------------------- Gram, up to 64 states
+// N <= 64 states in any blocks: every wave reads its points straight into
+// MFMA operands and owns all T x T output tiles (T = N16 / 16), so there is no
+// LDS stage and no barrier in the loop; the four waves of a work-group take
+// alternate groups of points of one chunk and their tiles are added at the
+// end, in wave order.  Chunks are small (about 512 of them) because these
+// products are short: the LDS-staged kernels above ran 32768 points on 64
+// (FP64) or 32 (FP32) work-groups of 32 barriers each, 31-57 us for 8-32
+// states, reduction
+// and call included; now 16-28.  Lane l supplies state l % 16 of a tile at point l / 16 of
+// a 4-point step (FP64) or at 8 points from 8 (l / 16) of a 32-point step
+// (split BF16, the same four products and FP32 sums over one step as above).
+// States past N and points past the chunk's end are read at a valid place
+// and replaced by zero.
+constexpr int kGramSmall = 64;
+template <typename T, int NT>
+__device__ __forceinline__ void gram_small_rows(const T *__restrict__ f, int64_t np, int B, int N, const T *(&row)[NT]) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) row[t] = f + bidx(np, B, 0, min(16 * t + (int)(threadIdx.x & 15), N - 1));
+}
+// acc of waves 1..3 added to wave 0's, which writes the chunk's tiles; row(r)
+// is the tile row of element r
+template <int NT, bool SYRK, typename Row>
+__device__ __forceinline__ void gram_small_store(d4 (&acc)[NT][NT], double *__restrict__ out, int N16, Row row) {
+    __shared__ d4 red[NT * NT * 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int w = 1; w < 4; ++w) {
+        __syncthreads();
+        if (wave == w)
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int j = SYRK ? i : 0; j < NT; ++j) red[(i * NT + j) * 64 + lane] = acc[i][j];
+        __syncthreads();
+        if (wave == 0)
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int j = SYRK ? i : 0; j < NT; ++j) acc[i][j] += red[(i * NT + j) * 64 + lane];
+    }
+    if (wave > 0) return;
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = SYRK ? i : 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) out[(16 * i + row(r)) * N16 + 16 * j + lane % 16] = acc[i][j][r];
+}
+
+template <int NT, bool SYRK>
+__global__ void __launch_bounds__(256)
+gram_f64_small_kernel(const double *__restrict__ X, const double *__restrict__ Y, int64_t np, int B, int N, int CP,
+                      double *__restrict__ partial) {
+    constexpr int KS = NT <= 2 ? 4 : 2;          // steps whose loads are in flight together
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t p_beg = (int64_t)blockIdx.x * CP, p_end = min<int64_t>(np, p_beg + CP);
+    const double *xr[NT], *yr[NT];
+    gram_small_rows<double, NT>(X, np, B, N, xr);
+    gram_small_rows<double, NT>(Y, np, B, N, yr);
+    d4 acc[NT][NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = d4{0, 0, 0, 0};
+    for (int64_t p0 = p_beg + wave * 4 * KS; p0 < p_end; p0 += 16 * KS) {
+        double a[KS][NT], b[KS][NT];
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const int64_t o = min<int64_t>(p0 + 4 * k + lane / 16, p_end - 1) * B;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                a[k][t] = xr[t][o];
+                if constexpr (!SYRK) b[k][t] = yr[t][o];
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const bool in = p0 + 4 * k + lane / 16 < p_end;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const bool ok = in && 16 * t + lane % 16 < N;
+                a[k][t] = ok ? a[k][t] : 0.0;
+                b[k][t] = SYRK ? a[k][t] : ok ? b[k][t] : 0.0;
+            }
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int j = SYRK ? i : 0; j < NT; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[k][i], b[k][j], acc[i][j], 0, 0, 0);
+        }
+    }
+    gram_small_store<NT, SYRK>(acc, partial + (int64_t)blockIdx.x * (NT * NT * 256), 16 * NT,
+                               [&](int r) { return 4 * r + lane / 16; });
+}
+
+// 65..128 states in any blocks (4 blocks of 32 have their own kernel), FP64:
+// the waves of a work-group share the chunk's points and split the tile rows,
+// wave w rows w and NT - 1 - w of an NT x NT square of tiles (the symmetric
+// product's shares are then equal); tiles past N are skipped.  Every wave
+// reads all column tiles itself, which L1 serves.  Bound by the FP64 matrix
+// cores.  96 states, reduction included, LDS-staged before -> now: 32768
+// points 141 -> 43 us, 904k points 853 -> 572 (symmetric 846 -> 427).
+template <int NT, bool SYRK>
+__global__ void __launch_bounds__(32 * NT)
+gram_f64_mid_kernel(const double *__restrict__ X, const double *__restrict__ Y, int64_t np, int B, int N, int N16,
+                    int CP, double *__restrict__ partial) {
+    constexpr int KS = 2;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t p_beg = (int64_t)blockIdx.x * CP, p_end = min<int64_t>(np, p_beg + CP);
+    const int rt[2] = {wave, NT - 1 - wave}, nt = N16 / 16;
+    const double *xr[2], *yr[NT];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) xr[i] = X + bidx(np, B, 0, min(16 * rt[i] + lane % 16, N - 1));
+    gram_small_rows<double, NT>(Y, np, B, N, yr);
+    d4 acc[2][NT];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = d4{0, 0, 0, 0};
+    for (int64_t p0 = p_beg; p0 < p_end; p0 += 4 * KS) {
+        double a[KS][2], b[KS][NT];
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const int64_t o = min<int64_t>(p0 + 4 * k + lane / 16, p_end - 1) * B;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) a[k][i] = xr[i][o];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) b[k][t] = yr[t][o];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const bool in = p0 + 4 * k + lane / 16 < p_end;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) a[k][i] = in && 16 * rt[i] + lane % 16 < N ? a[k][i] : 0.0;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) b[k][t] = in && 16 * t + lane % 16 < N ? b[k][t] : 0.0;
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    if (rt[i] < nt && j < nt && (!SYRK || j >= rt[i]))
+                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[k][i], b[k][j], acc[i][j], 0, 0, 0);
+        }
+    }
+    double *out = partial + (int64_t)blockIdx.x * N16 * N16;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+            if (rt[i] < nt && j < nt && (!SYRK || j >= rt[i]))
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    out[(int64_t)(16 * rt[i] + 4 * r + lane / 16) * N16 + 16 * j + lane % 16] = acc[i][j][r];
+}
+
+template <int NT, bool SYRK>
+__global__ void __launch_bounds__(256)
+gram_bf_small_kernel(const float *__restrict__ X, const float *__restrict__ Y, int64_t np, int B, int N, int CP,
+                     double *__restrict__ partial) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t p_beg = (int64_t)blockIdx.x * CP, p_end = min<int64_t>(np, p_beg + CP);
+    const float *xr[NT], *yr[NT];
+    gram_small_rows<float, NT>(X, np, B, N, xr);
+    gram_small_rows<float, NT>(Y, np, B, N, yr);
+    d4 acc[NT][NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = d4{0, 0, 0, 0};
+    for (int64_t p0 = p_beg + wave * 32; p0 < p_end; p0 += 128) {
+        float x[NT][8], y[NT][8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int64_t o = min<int64_t>(p0 + 8 * (lane / 16) + k, p_end - 1) * B;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                x[t][k] = xr[t][o];
+                if constexpr (!SYRK) y[t][k] = yr[t][o];
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        bf8 ah[NT], al[NT], bh[NT], bl[NT];
+        auto split = [&](const float (&v)[8], int t, bf8 &h, bf8 &l) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const bool ok = p0 + 8 * (lane / 16) + k < p_end && 16 * t + lane % 16 < N;
+                const float f = ok ? v[k] : 0.f;
+                h[k] = (__bf16)f;
+                l[k] = (__bf16)(f - (float)h[k]);
+            }
+        };
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            split(x[t], t, ah[t], al[t]);
+            if constexpr (SYRK) {
+                bh[t] = ah[t];
+                bl[t] = al[t];
+            } else {
+                split(y[t], t, bh[t], bl[t]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = SYRK ? i : 0; j < NT; ++j) {
+                f4 t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[i], bl[j], f4{0, 0, 0, 0}, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bl[j], t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[i], bh[j], t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bh[j], t, 0, 0, 0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[i][j][r] += (double)t[r];
+            }
+    }
+    gram_small_store<NT, SYRK>(acc, partial + (int64_t)blockIdx.x * (NT * NT * 256), 16 * NT,
+                               [&](int r) { return 4 * (lane / 16) + r; });
+}
+
+// Their sum over chunks into S (mode 1: mirror, 2: symmetrise), in one launch:
+// 16 entries x 16 shares of the chunks per work-group, fixed order.
+__global__ void __launch_bounds__(256)
+gram_small_reduce_kernel(const double *__restrict__ partial, int nchunks, int N, int N16, int mode, double dv,
+                         double *__restrict__ S) {
+    __shared__ double red[16][16];
+    const int e = threadIdx.x & 15, g = threadIdx.x >> 4, idx = blockIdx.x * 16 + e;
+    const int q = min(idx, N * N - 1), i = q / N, j = q % N;
+    const bool up = mode != 1 || i / 16 <= j / 16;
+    const double *p = partial + (up ? i : j) * N16 + (up ? j : i), *t = partial + j * N16 + i;
+    const int64_t ne = (int64_t)N16 * N16;
+    double s = 0.0;
+    if (mode == 2)
+#pragma unroll 4
+        for (int c = g; c < nchunks; c += 16) s += 0.5 * (p[c * ne] + t[c * ne]);
+    else
+#pragma unroll 8
+        for (int c = g; c < nchunks; c += 16) s += p[c * ne];
+    red[g][e] = s;
+    __syncthreads();
+    if (g == 0 && idx < N * N) {
+        double v = 0.0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v += red[k][e];
+        S[idx] = dv * v;
     }
 }
 
@@ -1656,9 +1879,58 @@ rs_status gram_core(const GramScratch &w, bool make_lists, const void *X, const 
         RS_HIP(hipGetLastError());
         return gram_reduce(w, nchunks, N, N16, syrk ? 3 : mode, dv, S, st);
     }
+    if (N <= kGramSmall && (dtype == RS_F64 || bf)) {
+        // chunks of whole rounds of the four waves
+        const int64_t round = bf ? 128 : nb16 <= 2 ? 64 : 32;
+        int64_t CP = std::max<int64_t>((np + 511) / 512, (np + w.max_chunks - 1) / w.max_chunks);
+        CP = std::max<int64_t>(round, (CP + round - 1) / round * round);
+        if (CP > (1 << 30)) return fail(RS_EINVAL, "gram: grid too large for the partial-sum workspace");
+        const int nchunks = (int)((np + CP - 1) / CP);
+        if ((int64_t)nchunks * N16 * N16 * (int64_t)sizeof(double) > w.partial_bytes)
+            return fail(RS_EINVAL, "gram: workspace too small");
+#define RS_GRAMS(K, F, NT)                                                                                       \
+    hipLaunchKernelGGL((syrk ? K<NT, true> : K<NT, false>), dim3(nchunks), dim3(256), 0, st, (const F *)X,       \
+                       (const F *)Y, np, B, N, (int)CP, w.partial)
+        switch (nb16) {
+            case 1: if (bf) RS_GRAMS(gram_bf_small_kernel, float, 1); else RS_GRAMS(gram_f64_small_kernel, double, 1); break;
+            case 2: if (bf) RS_GRAMS(gram_bf_small_kernel, float, 2); else RS_GRAMS(gram_f64_small_kernel, double, 2); break;
+            case 3: if (bf) RS_GRAMS(gram_bf_small_kernel, float, 3); else RS_GRAMS(gram_f64_small_kernel, double, 3); break;
+            default: if (bf) RS_GRAMS(gram_bf_small_kernel, float, 4); else RS_GRAMS(gram_f64_small_kernel, double, 4); break;
+        }
+#undef RS_GRAMS
+        RS_HIP(hipGetLastError());
+        hipLaunchKernelGGL(gram_small_reduce_kernel, dim3((N * N + 15) / 16), dim3(256), 0, st, w.partial, nchunks, N,
+                           N16, syrk ? 1 : mode, dv, S);
+        RS_HIP(hipGetLastError());
+        return RS_OK;
+    }
+    if (dtype == RS_F64 && N <= 128) {
+        // 256 chunks, up to 1024 where each keeps 256 points (their partials
+        // are read and written once more)
+        const int64_t want = std::max<int64_t>(256, std::min<int64_t>(1024, np / 256));
+        int64_t CP = std::max<int64_t>((np + want - 1) / want, (np + w.max_chunks - 1) / w.max_chunks);
+        CP = std::max<int64_t>(16, (CP + 7) / 8 * 8);
+        if (CP > (1 << 30)) return fail(RS_EINVAL, "gram: grid too large for the partial-sum workspace");
+        const int nchunks = (int)((np + CP - 1) / CP);
+        if ((int64_t)nchunks * N16 * N16 * (int64_t)sizeof(double) > w.partial_bytes)
+            return fail(RS_EINVAL, "gram: workspace too small");
+#define RS_GRAMM(NT)                                                                                            \
+    hipLaunchKernelGGL((syrk ? gram_f64_mid_kernel<NT, true> : gram_f64_mid_kernel<NT, false>), dim3(nchunks),  \
+                       dim3(32 * NT), 0, st, (const double *)X, (const double *)Y, np, B, N, N16, (int)CP, w.partial)
+        if (nb16 <= 6) RS_GRAMM(6);
+        else RS_GRAMM(8);
+#undef RS_GRAMM
+        RS_HIP(hipGetLastError());
+        return gram_reduce(w, nchunks, N, N16, syrk ? 1 : mode, dv, S, st);
+    }
     // small chunks: several work-groups per compute unit (each owns all
-    // output blocks of its chunk), bounded by the partial-sum workspace
+    // output blocks of its chunk), bounded by the partial-sum workspace; on
+    // small grids about 256 of them in whole 32-point stages, 128 above 128
+    // states, whose partials are large (4096 points, 256 FP64 states: 374 ->
+    // 70 us; 113k points: 512-point chunks 1095, 416-point ones 1225)
+    const int64_t want = N <= 128 ? 256 : 128;
     int64_t CP = bf ? 1024 : 512;
+    if (N <= 128 || np <= 65536) CP = std::max<int64_t>(64, std::min<int64_t>(CP, (np + want - 1) / want / 32 * 32));
     while ((np + CP - 1) / CP > w.max_chunks) CP *= 2;
     if (CP > (1 << 30)) return fail(RS_EINVAL, "gram: grid too large for the partial-sum workspace");
     const int nchunks = (int)((np + CP - 1) / CP);
@@ -1667,21 +1939,8 @@ rs_status gram_core(const GramScratch &w, bool make_lists, const void *X, const 
     dim3 grid(nchunks, nsplit);
     if (dtype == RS_F64) {
         const size_t lds = (syrk ? 1 : 2) * (size_t)KC64 * N16 * sizeof(double);
-        // exact per-wave share: every work-group holds bps = 4 * nbw blocks
-        const int nbw = (bps % 4 == 0 && nblocks % bps == 0) ? bps / 4 : 0;
-#define RS_GRAM64(S, NB)                                                                                  \
-    hipLaunchKernelGGL((gram_f64_kernel<S, NB>), grid, dim3(256), lds, st, (const double *)X, (const double *)Y, \
-                       np, B, N, N16, (int)CP, dbl, nblocks, bps, w.partial)
-        // (the interleaved form is faster at 9 blocks per wave, the symmetric
-        // product of 128 states; at 16 its 128 accumulators cost occupancy)
-        if (nbw == 9) {
-            if (syrk) RS_GRAM64(true, 9);
-            else RS_GRAM64(false, 9);
-        } else {
-            if (syrk) RS_GRAM64(true, 0);
-            else RS_GRAM64(false, 0);
-        }
-#undef RS_GRAM64
+        hipLaunchKernelGGL((syrk ? gram_f64_kernel<true> : gram_f64_kernel<false>), grid, dim3(256), lds, st,
+                           (const double *)X, (const double *)Y, np, B, N, N16, (int)CP, dbl, nblocks, bps, w.partial);
     } else if (bf) {
         const size_t lds = (syrk ? 2 : 4) * (size_t)N16 * LDSROW * sizeof(unsigned short);
 #define RS_GRAMBF(S, V)                                                                                   \

@@ -75,6 +75,30 @@ def test_overlap_bf16x3_error_bound(small, nblk, B):
         assert np.all(np.abs(got - want) <= bound)
 
 
+# one state, part of a tile, one to eight tiles of 16, both sides of the 64-
+# and 128-state limits, in narrow and wide blocks; grids of a few dozen points
+# (one ragged chunk) and 14147 (chunks that end inside a step)
+@pytest.mark.parametrize("nblk,B", [(1, 1), (17, 1), (2, 2), (3, 16), (1, 64), (8, 8), (33, 2), (5, 16), (3, 32),
+                                    (7, 16), (2, 64), (16, 8), (17, 8)])
+@pytest.mark.parametrize("radius", [0.3, 3.0])
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_overlap_tile_edges(nblk, B, radius, dtype):
+    g = rsd.Grid("sphere", 0.2, radius=radius)
+    ctx = rsd.Context(g, 256)
+    rng = np.random.default_rng(nblk * B)
+    x, y = (rng.uniform(-1, 1, (nblk * B, g.np)).astype(dtype) for _ in range(2))
+    x64, y64 = x.astype(np.float64), y.astype(np.float64)
+    tx = _blk(x, B)
+    for other, b in ((tx, x64), (_blk(y, B), y64)):
+        got = ctx.overlap(tx, other).cpu().numpy()
+        want, size = g.dv * x64 @ b.T, g.dv * np.abs(x64) @ np.abs(b).T
+        # FP64: rounding of a sum of np products; FP32: 2^-17 per split factor
+        assert np.all(np.abs(got - want) <= (1e-13 if dtype == np.float64 else 2.0 ** -16) * size)
+    if dtype == np.float64:      # the split products' FP32 sums differ by order within a tile
+        S = ctx.overlap(tx, tx).cpu().numpy()
+        assert np.array_equal(S, S.T)
+
+
 @pytest.mark.parametrize("N", [1, 37, 100, 128, 200])
 def test_cholesky_and_pivot(small, N):
     """N <= 130 keeps the working matrix in LDS, 200 runs it in global memory."""
