@@ -112,7 +112,7 @@ rs_status orthonormalize_impl(rs_ctx *c, void *psi, int nblk, int B, int dtype, 
     if ((st = rs::gram(c->w, psi, psi, c->g->np, B, nblk, dtype, prec, dv, S, 0, s))) return st;
     if ((st = rs::pad_identity(S, N, nreal, s))) return st;
     if ((st = rs::cholesky(c->w, S, c->U.as<double>(), N, c->info.as<int>(), s))) return st;
-    if ((st = rs::trinv(c->U.as<double>(), c->T.as<double>(), N, c->info.as<int>(), s))) return st;
+    if ((st = rs::trinv(c->w, c->U.as<double>(), c->T.as<double>(), N, c->info.as<int>(), s))) return st;
     if ((st = rs::rotate(c->w, psi, c->T.as<double>(), c->g->np, B, nblk, dtype, prec, c->info.as<int>(), s,
                          true)))
         return st;

@@ -333,7 +333,8 @@ wgrad_kernel(const float *__restrict__ xin, const float *__restrict__ d, int n, 
     constexpr int NXS = HZ * HY * kTX * CI, NDS = kTZ * kTY * HX * CO, NRED = 3 * MT * NT * 256;
     __shared__ __attribute__((aligned(16))) float buf[NXS + NDS > NRED ? NXS + NDS : NRED];
     float *xs = buf, *ds = buf + NXS;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k4 = lane / 16;
+    const int tid = threadIdx.x, lane = tid & 63, k4 = lane / 16;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: it guards matrix instructions
     const int vol = Z * Y * X;
     // operand offsets of this lane's rows and columns; those past the matrix
     // read a valid word and are dropped at the end

@@ -512,7 +512,7 @@ __global__ void __launch_bounds__(256)
 gram_f64_small_kernel(const double *__restrict__ X, const double *__restrict__ Y, int64_t np, int B, int N, int CP,
                       double *__restrict__ partial) {
     constexpr int KS = NT <= 2 ? 4 : 2;          // steps whose loads are in flight together
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t p_beg = (int64_t)blockIdx.x * CP, p_end = min<int64_t>(np, p_beg + CP);
     const double *xr[NT], *yr[NT];
     gram_small_rows<double, NT>(X, np, B, N, xr);
@@ -619,7 +619,7 @@ template <int NT, bool SYRK>
 __global__ void __launch_bounds__(256)
 gram_bf_small_kernel(const float *__restrict__ X, const float *__restrict__ Y, int64_t np, int B, int N, int CP,
                      double *__restrict__ partial) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t p_beg = (int64_t)blockIdx.x * CP, p_end = min<int64_t>(np, p_beg + CP);
     const float *xr[NT], *yr[NT];
     gram_small_rows<float, NT>(X, np, B, N, xr);
@@ -1212,21 +1212,133 @@ rotate_bf16x3_px_kernel(float *__restrict__ psi, const unsigned short *__restric
 }
 
 // ------------------------------------------------------------- Cholesky
-// S = U^T U, U upper with positive diagonal (right-looking, one work-group;
-// the working copy W lives in LDS when it fits, else in global memory).
-// Thread (c, g) owns the columns j = c (mod 128) and the rows i = g (mod
-// nt/128) of the trailing update, so no index is divided.  Step k reads only
-// row k of W (unscaled: the update subtracts W[k][i] W[k][j] / d) and writes
-// only rows below it, so a step needs one barrier; row k of U goes straight
-// to U.  Every thread reads the same pivot d, so all leave the loop together
-// on a bad pivot.  info = 0, or the 1-based column whose pivot is not
-// positive (that row of U and all after it stay zero).
-template <bool LDSW>
+// S = U^T U, U upper with positive diagonal, one work-group.  info = 0, or the
+// 1-based column whose pivot is not positive (that row of U and all after it
+// stay zero).
+//
+// N <= 128, in LDS by panels of 16 rows: one wave factors the 16 x 16 diagonal
+// block in registers (lane l holds column l; a pivot's root and reciprocal
+// from one refined estimate), one thread per later column solves the panel's
+// rows against it, and the waves subtract the panel from the trailing tiles
+// with FP64 MFMA.  Three barriers a panel instead of one a column: 128 columns
+// 153 us before (a barrier, a root and two divisions per column), now 48; 32
+// columns 25, now 17.  Bound by the diagonal blocks' serial chain.
+constexpr int kDenseLd = 130;                // LDS row stride: column walks hit different banks
+constexpr size_t kDenseLds = 128 * kDenseLd * sizeof(double);
+__device__ __forceinline__ double readlane_f64(double v, int l) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, l);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), l);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+// Lane L of each row of 16 lanes, to the whole row (row_newbcast).
+template <int L> __device__ __forceinline__ double row_bcast_f64(double v) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)u, 0x150 + L, 0xF, 0xF, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), 0x150 + L, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+// a[i] -= a[k] of lane i * a[k], i = I..15
+template <int I> __device__ __forceinline__ void chol_update(double (&a)[16], double ak) {
+    if constexpr (I < 16) {
+        a[I] -= row_bcast_f64<I>(ak) * ak;
+        chol_update<I + 1>(a, ak);
+    }
+}
+// column steps K..15 of the 16 x 16 block whose column l % 16 lane l holds
+template <int K> __device__ __forceinline__ void chol_steps(double (&a)[16], double &rinv, int &good, int l) {
+    if constexpr (K < 16) {
+        const double d = readlane_f64(a[K], K);
+        if (good == 16 && (!(d > 0.0) || !isfinite(d))) good = K;
+        double piv, r;
+        if (d > 1e-280) {
+            rs::sqrt_rsqrt(d, piv, r);
+        } else {
+            piv = sqrt(d);
+            r = 1.0 / piv;
+        }
+        a[K] = l == K ? piv : a[K] * r;
+        rinv = l == K ? r : rinv;
+        chol_update<K + 1>(a, a[K]);
+        chol_steps<K + 1>(a, rinv, good, l);
+    }
+}
+__global__ void __launch_bounds__(512)
+cholesky_lds_kernel(const double *__restrict__ S, double *__restrict__ U, int N, int *__restrict__ info) {
+    extern __shared__ double W[];
+    __shared__ double inv[16];
+    __shared__ int rows;                     // rows of the panel that were factored
+    constexpr int ld = kDenseLd;
+    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, nw = nt >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: it guards matrix instructions
+    const int N16 = (N + 15) / 16 * 16;
+    for (int i = wave; i < N16; i += nw)
+        for (int j = lane; j < N16; j += 64) W[i * ld + j] = i < N && j < N ? S[i * N + j] : (i == j ? 1.0 : 0.0);
+    __syncthreads();
+    int done = 0;                            // rows of U that hold
+    for (int k0 = 0; k0 < N16; k0 += 16) {
+        if (wave == 0) {
+            const int l = lane & 15;
+            double a[16], rinv = 1.0;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) a[r] = W[(k0 + r) * ld + k0 + l];
+            int good = 16;
+            chol_steps<0>(a, rinv, good, l);
+            if (lane < 16) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) W[(k0 + r) * ld + k0 + l] = r <= l ? a[r] : 0.0;
+                inv[l] = rinv;
+            }
+            if (lane == 0) rows = good;
+        }
+        __syncthreads();
+        const int good = rows;
+        // the panel's rows right of the block, one column per thread
+        for (int j = k0 + 16 + tid; j < N16; j += nt) {
+            double b[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) b[r] = W[(k0 + r) * ld + j];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                b[k] *= inv[k];      // (rows past a bad pivot are not used)
+                W[(k0 + k) * ld + j] = b[k];
+#pragma unroll
+                for (int r = k + 1; r < 16; ++r) b[r] -= W[(k0 + k) * ld + k0 + r] * b[k];
+            }
+        }
+        __syncthreads();
+        done = min(k0 + good, N);
+        if (good < 16) break;
+        // trailing tiles (i <= j), 16 x 16 x 16 each
+        const int n = (N16 - k0) / 16 - 1;
+        for (int t = wave, i = 0, row = 0; t < n * (n + 1) / 2; t += nw) {
+            while (row + (n - i) <= t) row += n - i++;
+            const int i0 = k0 + 16 + 16 * i, j0 = k0 + 16 + 16 * (i + t - row);
+            d4 acc = d4{0, 0, 0, 0};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const double *p = W + (k0 + 4 * k + lane / 16) * ld + lane % 16;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(p[i0], p[j0], acc, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) W[(i0 + 4 * r + lane / 16) * ld + j0 + lane % 16] -= acc[r];
+        }
+        __syncthreads();
+    }
+    for (int i = wave; i < N; i += nw)
+        for (int j = lane; j < N; j += 64) U[i * N + j] = i < done && j >= i ? W[i * ld + j] : 0.0;
+    if (tid == 0) *info = done < N ? done + 1 : 0;
+}
+
+// N > 128: right-looking in global memory.  Thread (c, g) owns the columns
+// j = c (mod 128) and the rows i = g (mod nt/128) of the trailing update, so
+// no index is divided.  Step k reads only row k of W (unscaled: the update
+// subtracts W[k][i] W[k][j] / d) and writes only rows below it, so a step
+// needs one barrier; row k of U goes straight to U.  Every thread reads the
+// same pivot d, so all leave the loop together on a bad pivot.
 __global__ void __launch_bounds__(1024)
-cholesky_kernel(const double *__restrict__ S, double *__restrict__ Wg, double *__restrict__ U, int N,
+cholesky_kernel(const double *__restrict__ S, double *__restrict__ W, double *__restrict__ U, int N,
                 int *__restrict__ info) {
-    extern __shared__ double ldsW[];
-    double *W = LDSW ? ldsW : Wg;
     const int tid = threadIdx.x, nt = blockDim.x;
     const int c = tid & 127, g = tid >> 7, ng = nt >> 7;
     for (int e = tid; e < N * N; e += nt) {
@@ -1254,68 +1366,109 @@ cholesky_kernel(const double *__restrict__ S, double *__restrict__ Wg, double *_
     if (tid == 0) *info = bad;
 }
 
-// Inverse of an upper-triangular U: one wave per column j solves U t = e_j
-// by back substitution.  T = U^-1 is upper triangular.  Skipped when
-// info != 0.
-//  - LDSU (N <= 128): column-oriented.  U^T is staged in LDS; lane l keeps
-//    the running sums s_m = sum_(k > m) U[m][k] t_k of rows m = l, l + 64;
-//    for k = j down to 0, t_k = -s_k / U[k][k] (t_j = 1 / U[j][j]) is read
-//    from the lane that owns row k, and every lane adds U[m][k] t_k to its
-//    rows m < k.  Each step is one broadcast instead of a wave reduction;
-//    the sums run in a fixed order (k descending).
-//  - otherwise: row-oriented, the inner products split over the 64 lanes
-//    and summed in a fixed butterfly, U read from global memory.
-constexpr size_t kTrinvLds = 128 * 128 * sizeof(double);
-__device__ __forceinline__ double readlane_f64(double v, int l) {
-    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, l);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), l);
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+// Inverse T of an upper-triangular U (T upper triangular); skipped when info
+// != 0.
+//
+// N <= 128, by 16 x 16 blocks: wave w inverts diagonal block w (one column per
+// lane), then forms block column w from the bottom up,
+//   T_ij = -T_ii sum_(i < k <= j) U_ik T_kj,
+// on FP64 MFMA.  A block in the accumulator layout is already laid out as the
+// right operand of the next product, so a block column stays in registers and
+// the waves share only U and the diagonal inverses.  Column by column from LDS
+// (one broadcast step per row) 128 columns took 177 us, now 21.
+__global__ void __launch_bounds__(512)
+trinv_lds_kernel(const double *__restrict__ U, double *__restrict__ T, int N, const int *__restrict__ info) {
+    extern __shared__ double W[];            // U [N16][ld], then the diagonal inverses [nb][16][17]
+    constexpr int ld = kDenseLd;
+    double *diag = W + (N + 15) / 16 * 16 * ld;
+    if (*info) return;
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: it guards matrix instructions
+    const int N16 = (N + 15) / 16 * 16, nb = N16 / 16;
+    for (int i = wave; i < N16; i += nw)
+        for (int j = lane; j < N16; j += 64)
+            W[i * ld + j] = i < N && j < N ? (j >= i ? U[i * N + j] : 0.0) : (i == j ? 1.0 : 0.0);
+    __syncthreads();
+    const int w0 = 16 * wave, l = lane & 15;
+    double *dw = diag + wave * (16 * 17);
+    if (wave < nb) {
+        const double own = 1.0 / W[(w0 + l) * ld + w0 + l];
+        double t[16];
+#pragma unroll
+        for (int i = 15; i >= 0; --i) {
+            const double *u = W + (w0 + i) * ld + w0;
+            double s = 0.0;
+#pragma unroll
+            for (int k = i + 1; k < 16; ++k) s += u[k] * t[k];
+            const double r = readlane_f64(own, i);
+            t[i] = i == l ? r : (i < l ? -s * r : 0.0);
+        }
+        if (lane < 16)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) dw[i * 17 + l] = t[i];
+    }
+    __syncthreads();
+    if (wave >= nb) return;
+    d4 col[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) col[k] = d4{0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        if (k == wave)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) col[k][r] = dw[(4 * r + lane / 16) * 17 + l];
+#pragma unroll
+    for (int i = 6; i >= 0; --i) {
+        if (i >= wave) continue;
+        d4 acc = d4{0, 0, 0, 0};
+#pragma unroll
+        for (int k = i + 1; k < 8; ++k) {
+            if (k > wave) break;
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(W[(16 * i + l) * ld + 16 * k + 4 * s + lane / 16], col[k][s],
+                                                           acc, 0, 0, 0);
+        }
+        const double *di = diag + i * (16 * 17) + l * 17 + lane / 16;
+        d4 out = d4{0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) out = __builtin_amdgcn_mfma_f64_16x16x4f64(-di[4 * s], acc[s], out, 0, 0, 0);
+        col[i] = out;
+    }
+    const int j = w0 + l;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 16 * k + 4 * r + lane / 16;
+            if (i < N && j < N) T[i * N + j] = i <= j ? col[k][r] : 0.0;
+        }
 }
-template <bool LDSU>
+
+// N > 128: one wave per column, row-oriented back substitution, the inner
+// products split over the 64 lanes and summed in a fixed butterfly, U read
+// from global memory.
 __global__ void __launch_bounds__(1024)
 trinv_kernel(const double *__restrict__ U, double *__restrict__ T, int N, const int *__restrict__ info) {
-    extern __shared__ double ut[];              // LDSU: U^T [N][N]
-    __shared__ double cols[LDSU ? 1 : 16 * 256];
+    __shared__ double cols[16 * 256];
     if (*info) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    if constexpr (LDSU) {
-        for (int e = threadIdx.x; e < N * N; e += blockDim.x) ut[(e % N) * N + e / N] = U[e];
-        __syncthreads();
-        for (int j = wave; j < N; j += nw) {
-            double s0 = 0.0, s1 = 0.0, t0 = 0.0, t1 = 0.0;
-            for (int k = j; k >= 0; --k) {
-                const double sk = readlane_f64(k < 64 ? s0 : s1, k & 63);
-                const double ukk = ut[k * N + k];
-                const double tk = k == j ? 1.0 / ukk : -sk / ukk;
-                if (lane == (k & 63)) {
-                    if (k < 64) t0 = tk;
-                    else t1 = tk;
-                }
-                if (lane < k) s0 += ut[k * N + lane] * tk;
-                if (lane + 64 < k) s1 += ut[k * N + lane + 64] * tk;
-            }
-            if (lane < N) T[lane * N + j] = lane <= j ? t0 : 0.0;
-            if (lane + 64 < N) T[(lane + 64) * N + j] = lane + 64 <= j ? t1 : 0.0;
-        }
-    } else {
-        double *t = cols + wave * 256;
-        for (int j = wave; j < N; j += nw) {
-            for (int i = lane; i < N; i += 64) t[i] = 0.0;
-            if (lane == 0) t[j] = 1.0 / U[j * N + j];
+    double *t = cols + wave * 256;
+    for (int j = wave; j < N; j += nw) {
+        for (int i = lane; i < N; i += 64) t[i] = 0.0;
+        if (lane == 0) t[j] = 1.0 / U[j * N + j];
+        __builtin_amdgcn_wave_barrier();
+        for (int i = j - 1; i >= 0; --i) {
+            double s = 0.0;
+            for (int k = i + 1 + lane; k <= j; k += 64) s += U[i * N + k] * t[k];
+            s = wave_sum(s);
+            if (lane == 0) t[i] = -s / U[i * N + i];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            for (int i = j - 1; i >= 0; --i) {
-                double s = 0.0;
-                for (int k = i + 1 + lane; k <= j; k += 64) s += U[i * N + k] * t[k];
-                s = wave_sum(s);
-                if (lane == 0) t[i] = -s / U[i * N + i];
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            }
-            for (int i = lane; i < N; i += 64) T[i * N + j] = t[i];
-            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
+        for (int i = lane; i < N; i += 64) T[i * N + j] = t[i];
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -2034,31 +2187,35 @@ rs_status rotate(DenseWork &w, void *psi, const double *Xm, int64_t np, int B, i
 }
 
 rs_status cholesky(DenseWork &w, const double *S, double *U, int N, int *info_dev, hipStream_t st) {
-    const size_t lds = (size_t)N * N * sizeof(double);
-    if (lds <= kJacobiLds) {
+    if (N <= 128) {
         if (!w.chol_lds_set) {
-            RS_HIP(hipFuncSetAttribute((const void *)cholesky_kernel<true>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kJacobiLds));
+            RS_HIP(hipFuncSetAttribute((const void *)cholesky_lds_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)kDenseLds));
             w.chol_lds_set = true;
         }
-        hipLaunchKernelGGL(cholesky_kernel<true>, dim3(1), dim3(1024), lds, st, S, w.mwork.as<double>(), U, N,
-                           info_dev);
+        // enough waves for the trailing tiles of the first panel
+        const int nb = (N + 15) / 16, nt = 64 * std::max(2, std::min(8, nb * (nb - 1) / 2));
+        hipLaunchKernelGGL(cholesky_lds_kernel, dim3(1), dim3(nt), (size_t)16 * nb * kDenseLd * sizeof(double), st, S,
+                           U, N, info_dev);
     } else {
-        hipLaunchKernelGGL(cholesky_kernel<false>, dim3(1), dim3(1024), 0, st, S, w.mwork.as<double>(), U, N,
-                           info_dev);
+        hipLaunchKernelGGL(cholesky_kernel, dim3(1), dim3(1024), 0, st, S, w.mwork.as<double>(), U, N, info_dev);
     }
     RS_HIP(hipGetLastError());
     return RS_OK;
 }
 
-rs_status trinv(const double *U, double *T, int N, const int *info_dev, hipStream_t st) {
+rs_status trinv(DenseWork &w, const double *U, double *T, int N, const int *info_dev, hipStream_t st) {
     if (N <= 128) {
-        RS_HIP(hipFuncSetAttribute((const void *)trinv_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)kTrinvLds));
-        const size_t lds = (size_t)N * N * sizeof(double);
-        hipLaunchKernelGGL(trinv_kernel<true>, dim3(1), dim3(1024), lds, st, U, T, N, info_dev);
+        constexpr size_t block_row = (16 * kDenseLd + 16 * 17) * sizeof(double);   // 16 rows of U, one inverse
+        if (!w.trinv_lds_set) {
+            RS_HIP(hipFuncSetAttribute((const void *)trinv_lds_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)(8 * block_row)));
+            w.trinv_lds_set = true;
+        }
+        const int nb = (N + 15) / 16;
+        hipLaunchKernelGGL(trinv_lds_kernel, dim3(1), dim3(64 * nb), nb * block_row, st, U, T, N, info_dev);
     } else {
-        hipLaunchKernelGGL(trinv_kernel<false>, dim3(1), dim3(1024), 0, st, U, T, N, info_dev);
+        hipLaunchKernelGGL(trinv_kernel, dim3(1), dim3(1024), 0, st, U, T, N, info_dev);
     }
     RS_HIP(hipGetLastError());
     return RS_OK;

@@ -21,7 +21,7 @@ struct DenseWork {
     DevBuf sweeps;                     // int
     DevBuf diag;                       // double [N] Jacobi diagonal
     DevBuf rot;                        // double2 [30][M-1][M/2] Jacobi rotations
-    bool jacobi_lds_set = false, chol_lds_set = false, rot_lds_set = false, rotbf_lds_set = false;
+    bool jacobi_lds_set = false, chol_lds_set = false, trinv_lds_set = false, rot_lds_set = false, rotbf_lds_set = false;
     int ncu = 0;                       // compute units of the device (persistent rotation)
 };
 
@@ -50,7 +50,7 @@ rs_status gram(DenseWork &w, const void *X, const void *Y, int64_t np, int B, in
 rs_status rotate(DenseWork &w, void *psi, const double *Xm, int64_t np, int B, int nblk, int dtype,
                  int prec, const int *skip, hipStream_t st, bool upper = false);
 rs_status cholesky(DenseWork &w, const double *S, double *U, int N, int *info_dev, hipStream_t st);
-rs_status trinv(const double *U, double *T, int N, const int *info_dev, hipStream_t st);
+rs_status trinv(DenseWork &w, const double *U, double *T, int N, const int *info_dev, hipStream_t st);
 // Jacobi eigensolver for a symmetric A (overwritten); max_sweeps (at most
 // 30) bounds the work (30 reaches full FP64 accuracy from any start).
 rs_status eigh(DenseWork &w, double *A, double *V, double *evals, int N, hipStream_t st,

@@ -132,6 +132,36 @@ def test_cholesky_and_pivot(small, N):
         assert np.allclose(Ug[:k, :k], Lk.T, atol=1e-12 * np.max(np.abs(S2)))
 
 
+# one block, its edges, two to eight blocks, and past the blocked kernels; a
+# bad pivot at the first and last row of a block and inside one
+@pytest.mark.parametrize("N", [2, 15, 16, 17, 33, 64, 111, 112, 127, 129])
+def test_cholesky_and_orthonormal_factor_at_block_edges(small, N):
+    w, og, H, g, ctx = small
+    rng = np.random.default_rng(N)
+    A = rng.normal(size=(N, 2 * N))
+    S = A @ A.T
+    U, info = ctx.cholesky(_dev(S))
+    assert int(info.item()) == 0
+    want = np.linalg.cholesky(S).T
+    assert np.max(np.abs(U.cpu().numpy() - want)) < 1e-12 * np.max(np.abs(want))
+    for k in sorted({0, 15, 16, N // 2, N - 1} & set(range(N))):
+        B = S.copy()
+        B[k, k] = want[:k, k] @ want[:k, k] - 1.0      # pivot k is -1
+        U, info = ctx.cholesky(_dev(B))
+        Ug = U.cpu().numpy()
+        assert int(info.item()) == k + 1
+        assert np.all(Ug[k:] == 0.0)
+        assert np.max(np.abs(Ug[:k, :k] - want[:k, :k]), initial=0.0) < 1e-12 * np.max(np.abs(want))
+    # psi <- psi U^-1 through the triangular inverse
+    B = 1 if N % 2 else 2 if N % 16 else 16
+    x = rng.uniform(-1, 1, (N, og.np))
+    t = _blk(x, B)
+    assert ctx.orthonormalize(t) == 0
+    want, _, _ = linalg.orthonormalize(x, og.dv)
+    got = rsd.from_blocks(t.cpu().numpy())
+    assert np.max(np.abs(got - want)) < 1e-11 * np.max(np.abs(want))
+
+
 @pytest.mark.parametrize("N", [8, 37, 128, 200, 256])
 def test_eigh_jacobi(small, N):
     w, og, H, g, ctx = small
