@@ -58,6 +58,8 @@ extern "C" void rs_ctx_destroy(rs_ctx *c) { delete c; }
 
 // Jacobi sweeps of the context's last symmetric eigensolve (device int).
 const int *ctx_sweeps(const rs_ctx *c) { return c->w.sweeps.as<int>(); }
+// Bad pivot of its last orthonormalisation, 1-based, or 0 (device int).
+const int *ctx_info(const rs_ctx *c) { return c->info.as<int>(); }
 
 extern "C" rs_status rs_overlap(rs_ctx *c, const void *x, const void *y, double *S, int32_t nblk, int32_t B,
                                 int32_t dtype, int32_t prec, void *stream) {
@@ -99,10 +101,11 @@ extern "C" rs_status rs_eigh(rs_ctx *c, double *A, double *V, double *evals, int
     return rs::eigh(c->w, A, V, evals, N, (hipStream_t)stream);
 }
 
-// nreal < nblk * B: the states from nreal on are zero padding (they get an
-// identity pivot and stay zero).
-rs_status orthonormalize_impl(rs_ctx *c, void *psi, int nblk, int B, int dtype, int prec, double *S_out,
-                              int32_t *info, int nreal, hipStream_t s) {
+// Enqueues psi <- psi U^-1; ctx_info then holds the status.  nreal < nblk * B:
+// the states from nreal on are zero padding (they get an identity pivot and
+// stay zero).
+rs_status orthonormalize_async(rs_ctx *c, void *psi, int nblk, int B, int dtype, int prec, double *S_out, int nreal,
+                               hipStream_t s) {
     rs_status st = check(c, nblk, B, dtype, prec, "rs_orthonormalize_block");
     if (st) return st;
     if (!psi) return rs::fail(RS_EINVAL, "rs_orthonormalize_block: null psi");
@@ -113,16 +116,24 @@ rs_status orthonormalize_impl(rs_ctx *c, void *psi, int nblk, int B, int dtype, 
     if ((st = rs::pad_identity(S, N, nreal, s))) return st;
     if ((st = rs::cholesky(c->w, S, c->U.as<double>(), N, c->info.as<int>(), s))) return st;
     if ((st = rs::trinv(c->w, c->U.as<double>(), c->T.as<double>(), N, c->info.as<int>(), s))) return st;
-    if ((st = rs::rotate(c->w, psi, c->T.as<double>(), c->g->np, B, nblk, dtype, prec, c->info.as<int>(), s,
-                         true)))
-        return st;
+    return rs::rotate(c->w, psi, c->T.as<double>(), c->g->np, B, nblk, dtype, prec, c->info.as<int>(), s, true);
+}
+
+rs_status orthonormalize_status(int info) {
+    if (!info) return RS_OK;
+    return rs::fail(RS_ENOTPOSDEF,
+                    "rs_orthonormalize_block: overlap not positive definite at column " + std::to_string(info));
+}
+
+rs_status orthonormalize_impl(rs_ctx *c, void *psi, int nblk, int B, int dtype, int prec, double *S_out,
+                              int32_t *info, int nreal, hipStream_t s) {
+    rs_status st = orthonormalize_async(c, psi, nblk, B, dtype, prec, S_out, nreal, s);
+    if (st) return st;
     int h_info = 0;
     RS_HIP(hipMemcpyAsync(&h_info, c->info.p, sizeof(int), hipMemcpyDeviceToHost, s));
     RS_HIP(hipStreamSynchronize(s));
     if (info) *info = h_info;
-    if (h_info) return rs::fail(RS_ENOTPOSDEF, "rs_orthonormalize_block: overlap not positive definite at column " +
-                                                   std::to_string(h_info));
-    return RS_OK;
+    return orthonormalize_status(h_info);
 }
 
 extern "C" rs_status rs_orthonormalize_block(rs_ctx *c, void *psi, int32_t nblk, int32_t B, int32_t dtype,
