@@ -42,269 +42,438 @@ __device__ __forceinline__ int wrap_or_flag(int v, int n, bool wrap, bool &ok) {
 }
 
 // ------------------------------------------------------------ convolution
-// MODE 0: out = mask * tanh(conv(in));  MODE 1: out = mask * conv(in);
-// MODE 2: out = mask * conv(in) * (1 - act^2)  (backward through tanh).
-// W [CO][CI][27]; taps outside the box are zero (or wrap).  A work-group
-// owns a TZ x TY x TX block of outputs of one box: it stages the block and
-// its one-point border, channels last, in LDS once, then each thread
-// computes two x-neighbouring outputs from there, which share the loads of
-// their taps.  Per output the sum runs over taps t = 9 dz + 3 dy + dx, then
-// output channel, then input channel, one fused multiply-add each; the
-// weights are uniform across the work-group.
-constexpr int kTX = 16, kTY = 8, kTZ = 4;   // 512 outputs per work-group, 2 per thread
-
-template <int CI, int CO, int MODE>
-__global__ void __launch_bounds__(256)
-conv_kernel(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ W,
-            const float *__restrict__ act, const int32_t *__restrict__ boxpt, int n, int Z, int Y, int X,
-            int wrap, int ntx, int nty, int ntz) {
-    constexpr int HX = kTX + 2, HY = kTY + 2, HZ = kTZ + 2;
-    __shared__ __attribute__((aligned(16))) float tile[HZ * HY * HX * CI];
-    const int bid = blockIdx.x;
-    const int tx = bid % ntx, ty = (bid / ntx) % nty, tz = (bid / (ntx * nty)) % ntz;
-    const int img = bid / (ntx * nty * ntz);
-    const int x0 = tx * kTX, y0 = ty * kTY, z0 = tz * kTZ;
-    const int vol = Z * Y * X;
-    const float *base = in + (int64_t)img * vol * CI;
-    // stage the block and its border; positions more than one point past the
-    // box feed only outputs that are not computed and are left zero
-    for (int e = threadIdx.x; e < HZ * HY * HX; e += 256) {
-        const int hx = e % HX, hy = (e / HX) % HY, hz = e / (HX * HY);
-        const int gx = x0 + hx - 1, gy = y0 + hy - 1, gz = z0 + hz - 1;
-        bool ok = gx <= X && gy <= Y && gz <= Z;
-        const int xx = wrap_or_flag(gx, X, wrap, ok);
-        const int yy = wrap_or_flag(gy, Y, wrap, ok);
-        const int zz = wrap_or_flag(gz, Z, wrap, ok);
-        ok = ok && xx >= 0 && xx < X && yy >= 0 && yy < Y && zz >= 0 && zz < Z;
-        float *dst = tile + e * CI;
-        if constexpr (CI == 8) {
-            float4 lo = make_float4(0.f, 0.f, 0.f, 0.f), hi = lo;
-            if (ok) {
-                const float *src = base + ((int64_t)(zz * Y + yy) * X + xx) * CI;
-                lo = *(const float4 *)src;
-                hi = *(const float4 *)(src + 4);
-            }
-            *(float4 *)dst = lo;
-            *(float4 *)(dst + 4) = hi;
-        } else {
-#pragma unroll
-            for (int c = 0; c < CI; ++c) dst[c] = ok ? base[((int64_t)(zz * Y + yy) * X + xx) * CI + c] : 0.f;
-        }
-    }
-    __syncthreads();
-    const int t = threadIdx.x;
-    const int lx = 2 * (t % (kTX / 2)), ly = (t / (kTX / 2)) % kTY, lz = t / (kTX / 2 * kTY);
-    float acc0[CO], acc1[CO];
-#pragma unroll
-    for (int c = 0; c < CO; ++c) acc0[c] = acc1[c] = 0.f;
-    // (dz, dy) stays a loop: unrolled, the loads of all nine rows would be
-    // hoisted and the work-group would run at one wave per SIMD
-#pragma unroll 1
-    for (int dz = 0; dz < 3; ++dz)
-#pragma unroll 1
-        for (int dy = 0; dy < 3; ++dy) {
-            // border coordinates: output lx sits at lx + 1, tap dx reads lx + dx
-            const float *row = tile + (((lz + dz) * HY + (ly + dy)) * HX + lx) * CI;
-            float v[4][CI];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if constexpr (CI == 8) {
-                    const float4 lo = *(const float4 *)(row + j * CI), hi = *(const float4 *)(row + j * CI + 4);
-                    v[j][0] = lo.x; v[j][1] = lo.y; v[j][2] = lo.z; v[j][3] = lo.w;
-                    v[j][4] = hi.x; v[j][5] = hi.y; v[j][6] = hi.z; v[j][7] = hi.w;
-                } else {
-#pragma unroll
-                    for (int c = 0; c < CI; ++c) v[j][c] = row[j * CI + c];
-                }
-            }
-#pragma unroll
-            for (int dx = 0; dx < 3; ++dx) {
-                const int tap = 9 * dz + 3 * dy + dx;
-#pragma unroll
-                for (int co = 0; co < CO; ++co)
-#pragma unroll
-                    for (int ci = 0; ci < CI; ++ci) {
-                        const float w = W[(co * CI + ci) * 27 + tap];
-                        acc0[co] = fmaf(w, v[dx][ci], acc0[co]);
-                        acc1[co] = fmaf(w, v[dx + 1][ci], acc1[co]);
-                    }
-            }
-        }
-    const int y = y0 + ly, z = z0 + lz;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int x = x0 + lx + k;
-        if (x >= X || y >= Y || z >= Z) continue;
-        const int q = (z * Y + y) * X + x;
-        const int64_t gid = (int64_t)img * vol + q;
-        const bool inside = boxpt == nullptr || boxpt[q] >= 0;
-        float *dst = out + gid * CO;
-        float r[CO];
-#pragma unroll
-        for (int c = 0; c < CO; ++c) {
-            const float a = k == 0 ? acc0[c] : acc1[c];
-            float o;
-            if constexpr (MODE == 0) o = tanhf(a);
-            else if constexpr (MODE == 1) o = a;
-            else {
-                const float ac = act[gid * CO + c];
-                o = a * (1.f - ac * ac);
-            }
-            r[c] = inside ? o : 0.f;
-        }
-        if constexpr (CO == 8) {
-            *(float4 *)dst = make_float4(r[0], r[1], r[2], r[3]);
-            *(float4 *)(dst + 4) = make_float4(r[4], r[5], r[6], r[7]);
-        } else {
-#pragma unroll
-            for (int c = 0; c < CO; ++c) dst[c] = r[c];
-        }
-    }
-}
-
-// Launches conv_kernel over n boxes of Z x Y x X points.
-template <int CI, int CO, int MODE>
-void conv(const float *in, float *out, const float *W, const float *act, const int32_t *boxpt, int n, int Z, int Y,
-          int X, int wrap, hipStream_t st) {
-    const int ntx = (X + kTX - 1) / kTX, nty = (Y + kTY - 1) / kTY, ntz = (Z + kTZ - 1) / kTZ;
-    const int64_t nwg = (int64_t)ntx * nty * ntz * n;
-    hipLaunchKernelGGL((conv_kernel<CI, CO, MODE>), dim3((unsigned)nwg), dim3(256), 0, st, in, out, W, act, boxpt, n,
-                       Z, Y, X, wrap, ntx, nty, ntz);
-}
-
-// Layer 2 of the forward pass (8 -> 8 channels, tanh) on the matrix cores:
-// per row of 16 outputs an implicit GEMM D[point][co] = sum over k = (tap,
-// ci) of A[point][k] W[co][ci][tap], K = 27 taps x 8 channels in 7 chunks of
-// 32 (4 taps each; the 28th tap gets zero weights), N = the 8 channels of a
-// 16-wide tile.  Inputs and weights are split as hi + lo bfloat16 (the
-// input block once per work-group, into hi and lo planes in LDS) and the
-// four products lo.lo + hi.lo + lo.hi + hi.hi are summed in FP32 on
-// mfma_f32_16x16x32_bf16, which keeps FP32 accuracy.  Lane l supplies A row
-// l % 16 (point x0 + l % 16) and B column l % 16 (channel), both for k =
-// 8 (l / 16) .. + 7 (tap 4 c + l / 16 of chunk c, channels 0..7), and
-// receives D rows 4 (l / 16) + r, r < 4, of column l % 16.
+// Taps outside the box are zero (or wrap); W is [CO][CI][27].
+typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef unsigned short us8 __attribute__((ext_vector_type(8)));
+typedef float f2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-// bfloat16 with round-to-nearest-even (finite inputs)
-__device__ __forceinline__ unsigned short bf16_rne(float x) {
-    const uint32_t u = __builtin_bit_cast(uint32_t, x);
-    return (unsigned short)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+// x = hi + lo in bfloat16, each rounded to nearest even.
+__device__ __forceinline__ void split(f4 x, bf4 &hi, bf4 &lo) {
+    hi = __builtin_convertvector(x, bf4);
+    lo = __builtin_convertvector(x - __builtin_convertvector(hi, f4), bf4);
 }
-__device__ __forceinline__ float bf16_to_f(unsigned short h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
 
-__global__ void __launch_bounds__(256)
-conv2_mfma_kernel(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ W,
-                  const int32_t *__restrict__ boxpt, int n, int Z, int Y, int X, int wrap, int ntx, int nty,
-                  int ntz) {
-    constexpr int HX = kTX + 2, HY = kTY + 2, HZ = kTZ + 2, NH = HX * HY * HZ;
-    __shared__ __attribute__((aligned(16))) unsigned short th[NH * 8], tl[NH * 8];
-    const int vol = Z * Y * X;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // this lane's B operands (channel co, taps 4 c + g of the 7 chunks) and
-    // the LDS offsets of its A operands relative to the row's first point,
-    // once for all the tiles this work-group takes
-    const int co = lane % 16, g = lane / 16;
-    bf8 bh[7], bl[7];
-    int aoff[7];
+// tanh without a branch: an odd polynomial (weighted least squares, 1e-9 of
+// x) below 0.95 and 1 - 2 / (e^2x + 1) with the hardware's exponential and
+// reciprocal above.  Against FP64 over -20 .. 20 and down to 2^-20 it errs by
+// 1.38 units in the last place at most and 0.265 rms; the library's tanhf, whose two
+// branches both run in nearly every wave here, by 1.40 and 0.267.
+__device__ __forceinline__ float tanh_f(float x) {
+    const float a = fabsf(x), s = x * x;
+    float p = fmaf(s, -0x1.ac83ccp-12f, 0x1.41d0d2p-9f);
+    p = fmaf(s, p, -0x1.0a65b2p-7f);
+    p = fmaf(s, p, 0x1.61cbd4p-6f);
+    p = fmaf(s, p, -0x1.b9a448p-5f);
+    p = fmaf(s, p, 0x1.110e1ap-3f);
+    p = fmaf(s, p, -0x1.555548p-2f);
+    const float lo = fmaf(a * s, p, a);
+    const float e = __builtin_amdgcn_exp2f(a * 2.88539008f);   // 2 log2(e)
+    const float hi = fmaf(-2.f, __builtin_amdgcn_rcpf(e + 1.f), 1.f);
+    return copysignf(a < 0.95f ? lo : hi, x);
+}
+
+// The layers with 8 output channels, on the matrix cores.
+// MODE 0: out = mask * tanh(conv(in));  MODE 2: out = mask * conv(in) *
+// (1 - act^2) (backward through tanh).  A pair of rows of 16 outputs, y and
+// y + 1, is one implicit GEMM D[(row j, co)][point] = sum over k = (dz, dy',
+// dx, ci) of A[(j, co)][k] B[k][point], where the rows share the four input
+// rows dy' = dy + j: 36 taps (27 of them with weights per row) fill all 16
+// rows of D, where one output row at a time would fill 8 at 28.  Lane l
+// supplies A row and B column l % 16 and receives D rows 4 (l / 16) + r, r <
+// 4, of column l % 16: four channels of one point, stored in one access, a
+// pair of rows in whole lines.
+//   SPLIT (8 input channels, layer 2 forward): inputs and weights are hi + lo
+//     bfloat16 and the four products lo.lo + hi.lo + lo.hi + hi.hi are summed
+//     in FP32 on mfma_f32_16x16x32_bf16, an instruction per (dz, dx) and
+//     product with dy' = l / 16, the 8 channels in the lane.
+//   otherwise FP32 products on mfma_f32_16x16x4_f32: per (dz, dx) with dy' =
+//     l / 16 (one input channel), or per tap and channel parity with channels
+//     2 (l / 16) + {0, 1} (eight).
+// A work-group owns a column of 16 x 16 x cz points and runs down z: four
+// planes with their border in LDS, channels last, three in use while the
+// fourth is filled from registers, one barrier a plane; its four waves take two
+// row pairs each.  The weights stay in registers.  Consecutive work-groups of
+// an XCD take neighbouring columns, whose borders its L2 then holds.
+//   No single unit bounds it: for 32 boxes of 96^3 (28 M points) layer 2
+// takes 750 us, of which the matrix instructions are 250, the vector units (half
+// of it tanh) 330, and the 0.9 GB written 190 on top of both; blocks of 16 x 8 x
+// 4 with one output row per D tile took 1270.  Layer 1 takes 360 (418 with
+// fused multiply-adds on the vector units), for 32 boxes of 16^3 the adjoint of
+// layer 2 14 (34) and that of layer 3 6 (9).
+constexpr int kCX = 16, kCY = 16;          // a column's footprint
+constexpr int kPX = kCX + 2, kPY = kCY + 2, kPP = kPX * kPY;   // and its planes with their border
+
+// The pieces of a plane (half a point of 8 channels, or a point of one) that
+// thread tid of NT stages: off[k] is the point of piece tid + NT k in the
+// plane (any point where the piece is zero), bit k of the result says that
+// it is not zero.  Positions more than one point past the box feed only
+// outputs that are not computed.
+template <int CI, int NT, int NL>
+__device__ __forceinline__ unsigned plane_offsets(int tid, int x0, int y0, int Y, int X, int wrap, int off[NL]) {
+    unsigned valid = 0;
 #pragma unroll
-    for (int c = 0; c < 7; ++c) {
-        const int tap = 4 * c + g;
-        us8 h, l;
-#pragma unroll
-        for (int ci = 0; ci < 8; ++ci) {
-            const float w = co < 8 && tap < 27 ? W[(co * 8 + ci) * 27 + tap] : 0.f;
-            h[ci] = bf16_rne(w);
-            l[ci] = bf16_rne(w - bf16_to_f(h[ci]));
-        }
-        bh[c] = __builtin_bit_cast(bf8, h);
-        bl[c] = __builtin_bit_cast(bf8, l);
-        const int t = min(tap, 26);   // the 28th tap: zero weights, any finite input
-        aoff[c] = (((t / 9) * HY + (t / 3) % 3) * HX + t % 3 + co) * 8;
+    for (int k = 0; k < NL; ++k) {
+        const int e = tid + NT * k, p = e / (CI == 8 ? 2 : 1);
+        const int gx = x0 + p % kPX - 1, gy = y0 + p / kPX - 1;
+        bool ok = gx <= X && gy <= Y && p < kPP;
+        const int xx = wrap_or_flag(gx, X, wrap, ok), yy = wrap_or_flag(gy, Y, wrap, ok);
+        ok = ok && xx >= 0 && xx < X && yy >= 0 && yy < Y;
+        off[k] = ok ? yy * X + xx : 0;
+        valid |= (unsigned)ok << k;
     }
-    const int ntile = ntx * nty * ntz * n;
-    for (int bid = blockIdx.x; bid < ntile; bid += gridDim.x) {
-        const int tx = bid % ntx, ty = (bid / ntx) % nty, tz = (bid / (ntx * nty)) % ntz;
-        const int img = bid / (ntx * nty * ntz);
-        const int x0 = tx * kTX, y0 = ty * kTY, z0 = tz * kTZ;
-        const float *base = in + (int64_t)img * vol * 8;
-        __syncthreads();   // the previous tile's reads of the LDS block are done
-        for (int e = tid; e < NH; e += 256) {
-            const int hx = e % HX, hy = (e / HX) % HY, hz = e / (HX * HY);
-            const int gx = x0 + hx - 1, gy = y0 + hy - 1, gz = z0 + hz - 1;
-            bool ok = gx <= X && gy <= Y && gz <= Z;
-            const int xx = wrap_or_flag(gx, X, wrap, ok);
-            const int yy = wrap_or_flag(gy, Y, wrap, ok);
-            const int zz = wrap_or_flag(gz, Z, wrap, ok);
-            ok = ok && xx >= 0 && xx < X && yy >= 0 && yy < Y && zz >= 0 && zz < Z;
-            float v[8];
-            if (ok) {
-                const float *src = base + ((int64_t)(zz * Y + yy) * X + xx) * 8;
-                const float4 a = *(const float4 *)src, b = *(const float4 *)(src + 4);
-                v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    return valid;
+}
+// Loads them, without a branch; plane_piece selects afterwards.
+template <int CI, int NL>
+__device__ __forceinline__ void load_plane(const float *__restrict__ base, int gz, int Z, int plane, int wrap,
+                                           const int off[NL], f4 v[NL]) {
+    const int zz = gz < 0 ? (wrap ? gz + Z : 0) : gz >= Z ? (wrap ? gz - Z : 0) : gz;
+    const float *src = base + (int64_t)zz * plane * CI + (CI == 8 ? 4 * (threadIdx.x & 1) : 0);
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        if constexpr (CI == 8) v[k] = *(const f4 *)(src + (int64_t)off[k] * 8);
+        else v[k][0] = src[off[k]];
+    }
+}
+__device__ __forceinline__ f4 plane_piece(f4 v, unsigned valid, int k, int gz, int Z, int wrap) {
+    const bool ok = (valid >> k & 1) && (wrap || (gz >= 0 && gz < Z));
+    return ok ? v : f4{0.f, 0.f, 0.f, 0.f};
+}
+
+// Column of work-group bid of 8 per: a contiguous range of the n columns for
+// each of the 8 XCDs, or -1.
+__device__ __forceinline__ int xcd_column(int bid, int n) {
+    const int per = (n + 7) / 8, c = bid % 8 * per + bid / 8;
+    return c < n ? c : -1;
+}
+
+template <int CI, int MODE, bool SPLIT>
+__global__ void __launch_bounds__(256)
+conv8_kernel(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ W,
+             const float *__restrict__ act, const int32_t *__restrict__ boxpt, int ncol, int Z, int Y, int X,
+             int wrap, int ntx, int nty, int ntz, int cz) {
+    constexpr int NA = SPLIT ? 1 : CI == 8 ? 36 : 9;
+    constexpr int PIECES = kPP * (CI == 8 ? 2 : 1), NL = (PIECES + 255) / 256;
+    __shared__ __attribute__((aligned(16))) float ring[4][kPP * CI];   // SPLIT: kPP * 8 hi, then kPP * 8 lo
+    const int col = xcd_column(blockIdx.x, ncol);
+    if (col < 0) return;
+    const int tx = col % ntx, ty = (col / ntx) % nty, tz = (col / (ntx * nty)) % ntz;
+    const int64_t vol = (int64_t)Z * Y * X, img = col / (ntx * nty * ntz);
+    const int x0 = tx * kCX, y0 = ty * kCY, z0 = tz * cz, z1 = min(z0 + cz, Z);
+    const float *base = in + img * vol * CI;
+    const int tid = threadIdx.x, lane = tid & 63, g = lane / 16, px = lane % 16;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int off[NL];
+    const unsigned valid = plane_offsets<CI, 256, NL>(tid, x0, y0, Y, X, wrap, off);
+    auto store = [&](int z, const f4 *loaded) {
+        float *dst = ring[z & 3];
+#pragma unroll
+        for (int k = 0; k < NL; ++k) {
+            const int e = tid + 256 * k;
+            if (e >= PIECES) break;
+            const f4 v = plane_piece(loaded[k], valid, k, z, Z, wrap);
+            if constexpr (SPLIT) {
+                bf4 h, l;
+                split(v, h, l);
+                *(bf4 *)((__bf16 *)dst + 4 * e) = h;
+                *(bf4 *)((__bf16 *)dst + kPP * 8 + 4 * e) = l;
+            } else if constexpr (CI == 8) {
+                *(f4 *)(dst + 4 * e) = v;
             } else {
-#pragma unroll
-                for (int c = 0; c < 8; ++c) v[c] = 0.f;
+                dst[e] = v[0];
             }
-            us8 h, l;
+        }
+    };
+    f4 v[NL], v1[NL], v2[NL];
+    load_plane<CI, NL>(base, z0 - 1, Z, Y * X, wrap, off, v);
+    load_plane<CI, NL>(base, z0, Z, Y * X, wrap, off, v1);
+    load_plane<CI, NL>(base, z0 + 1, Z, Y * X, wrap, off, v2);
+    // A operands of row px: channel px % 8 of output row px / 8
+    bf8 ah[9], al[9];
+    f2 aw[NA];
+    {
+        const int co = px % 8, j = px / 8;
+        if constexpr (SPLIT) {
+            const int dy = g - j;
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                h[c] = bf16_rne(v[c]);
-                l[c] = bf16_rne(v[c] - bf16_to_f(h[c]));
+            for (int c = 0; c < 9; ++c) {
+#pragma unroll
+                for (int ci = 0; ci < 8; ci += 4) {
+                    f4 w;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        w[k] = dy >= 0 && dy < 3 ? W[(co * 8 + ci + k) * 27 + 9 * (c / 3) + 3 * dy + c % 3] : 0.f;
+                    bf4 h, l;
+                    split(w, h, l);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        ah[c][ci + k] = h[k];
+                        al[c][ci + k] = l[k];
+                    }
+                }
             }
-            *(us8 *)(th + e * 8) = h;
-            *(us8 *)(tl + e * 8) = l;
+        } else if constexpr (CI == 8) {
+#pragma unroll
+            for (int t = 0; t < 36; ++t) {
+                const int dy = (t / 3) % 4 - j;
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    aw[t][k] = dy >= 0 && dy < 3 ? W[(co * 8 + 2 * g + k) * 27 + 9 * (t / 12) + 3 * dy + t % 3] : 0.f;
+            }
+        } else {
+            const int dy = g - j;
+#pragma unroll
+            for (int c = 0; c < 9; ++c)
+                aw[c][0] = dy >= 0 && dy < 3 ? W[co * 27 + 9 * (c / 3) + 3 * dy + c % 3] : 0.f;
+        }
+    }
+    // this lane's point of the wave's two row pairs: in the box or not, and
+    // where its mask and activations are in a plane
+    bool ok[2];
+    int64_t qp[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int x = x0 + px, y = y0 + 2 * (wave + 4 * h) + g / 2;
+        ok[h] = x < X && y < Y;
+        qp[h] = (int64_t)min(y, Y - 1) * X + min(x, X - 1);
+    }
+    int m[2] = {0, 0};
+    f4 ac[2];
+    auto load_marks = [&](int z) {
+        const int64_t zp = (int64_t)z * Y * X;
+        if (boxpt != nullptr)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) m[h] = boxpt[zp + qp[h]];
+        if (MODE == 2)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) ac[h] = *(const f4 *)(act + (img * vol + zp + qp[h]) * 8 + 4 * (g & 1));
+    };
+    load_marks(z0);
+    store(z0 - 1, v);
+    store(z0, v1);
+    store(z0 + 1, v2);
+    __syncthreads();
+    for (int z = z0; z < z1; ++z) {
+        // loads of the next plane, its mask and activations: nothing below
+        // waits for them before the plane is stored to LDS
+        const bool more = z + 1 < z1;
+        const bool in0 = ok[0] && m[0] >= 0, in1 = ok[1] && m[1] >= 0;
+        const f4 ac0 = ac[0], ac1 = ac[1];
+        f4 res[2];
+        if (more) {
+            load_plane<CI, NL>(base, z + 2, Z, Y * X, wrap, off, v);
+            load_marks(z + 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const float *pl[3] = {ring[(z - 1) & 3], ring[z & 3], ring[(z + 1) & 3]};
+        // both row pairs of the wave in one block of code: the second's matrix
+        // instructions run beside the first's tanh
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int rb = 2 * (wave + 4 * h) * kPX + px;
+            f4 d;
+            if constexpr (SPLIT) {
+                f4 acc[4];   // one chain per product
+#pragma unroll
+                for (int k = 0; k < 4; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < 9; ++c) {
+                    const __bf16 *p = (const __bf16 *)pl[c / 3] + (rb + g * kPX + c % 3) * 8;
+                    const bf8 bh = *(const bf8 *)p, bl = *(const bf8 *)(p + kPP * 8);
+                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[c], bl, acc[0], 0, 0, 0);
+                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[c], bh, acc[1], 0, 0, 0);
+                    acc[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[c], bl, acc[2], 0, 0, 0);
+                    acc[3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[c], bh, acc[3], 0, 0, 0);
+                }
+                d = ((acc[0] + acc[1]) + acc[2]) + acc[3];   // the small products first
+            } else if constexpr (CI == 8) {
+                f4 acc[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+                for (int t = 0; t < 36; ++t) {
+                    const f2 b = *(const f2 *)(pl[t / 12] + (rb + (t / 3) % 4 * kPX + t % 3) * 8 + 2 * g);
+                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(aw[t][0], b[0], acc[0], 0, 0, 0);
+                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(aw[t][1], b[1], acc[1], 0, 0, 0);
+                }
+                d = acc[0] + acc[1];
+            } else {
+                f4 acc[3];   // one chain per plane
+#pragma unroll
+                for (int k = 0; k < 3; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < 9; ++c)
+                    acc[c / 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(aw[c][0], pl[c / 3][rb + g * kPX + c % 3],
+                                                                      acc[c / 3], 0, 0, 0);
+                d = (acc[0] + acc[1]) + acc[2];
+            }
+            const bool inside = h ? in1 : in0;
+            const f4 a = h ? ac1 : ac0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float o = MODE == 0 ? tanh_f(d[k]) : d[k] * (1.f - a[k] * a[k]);
+                res[h][k] = inside ? o : 0.f;
+            }
+        }
+        // to LDS first: waiting for the loads then does not wait for the results' stores
+        if (more) store(z + 2, v);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (ok[h])
+                __builtin_nontemporal_store(res[h], (f4 *)(out + (img * vol + (int64_t)z * Y * X + qp[h]) * 8 + 4 * (g & 1)));
+        __syncthreads();
+    }
+}
+
+// Columns of nbox boxes of Z x Y x X points: counts and depth cz.  32 planes a
+// column cost a sixteenth more border; fewer where that would leave fewer than
+// 2048 work-groups, about two rounds of what is resident, down to 2: single
+// planes read three for one and gain nothing (32 boxes of 16^3: 14 us either way).
+struct Columns {
+    int ntx, nty, ntz, cz, n;
+    Columns(int nbox, int Z, int Y, int X) : ntx((X + kCX - 1) / kCX), nty((Y + kCY - 1) / kCY), cz(32) {
+        while (cz > 2 && (int64_t)ntx * nty * ((Z + cz - 1) / cz) * nbox < 2048) cz /= 2;
+        ntz = (Z + cz - 1) / cz;
+        n = ntx * nty * ntz * nbox;
+    }
+    dim3 grid() const { return dim3((unsigned)((n + 7) / 8 * 8)); }
+};
+
+// Launches conv8_kernel over n boxes of Z x Y x X points.
+template <int CI, int MODE, bool SPLIT>
+void conv8(const float *in, float *out, const float *W, const float *act, const int32_t *boxpt, int n, int Z, int Y,
+           int X, int wrap, hipStream_t st) {
+    const Columns c(n, Z, Y, X);
+    hipLaunchKernelGGL((conv8_kernel<CI, MODE, SPLIT>), c.grid(), dim3(256), 0, st, in, out, W, act, boxpt, c.n, Z, Y,
+                       X, wrap, c.ntx, c.nty, c.ntz, c.cz);
+}
+
+// Layer 3, 8 -> 1 channels: out = mask * conv(in).  The vector units' 216
+// fused multiply-adds a point bound it if the inputs are not read from LDS
+// once per output: a thread runs down z over two y-neighbouring columns, a
+// plane's 12 points feeding six sums (two columns, three outputs in z), 12
+// 32-byte reads for two outputs.  The planes of a 16 x 16 block and its
+// border are staged in two buffers, four channels in each half of a plane,
+// so that 16 lanes read 256 contiguous bytes.  Per output the sum runs over
+// taps 9 dz + 3 dy + dx, then channels, one fused multiply-add each.  wt:
+// [27][8].  28 M points take 375 us, 190 of them the multiply-adds; two outputs
+// a thread that read their taps from blocks of 16 x 8 x 4 took 560.
+__global__ void __launch_bounds__(128)
+conv1_kernel(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ wt,
+             const int32_t *__restrict__ boxpt, int ncol, int Z, int Y, int X, int wrap, int ntx, int nty, int ntz,
+             int cz) {
+    constexpr int NL = (2 * kPP + 127) / 128;
+    __shared__ __attribute__((aligned(16))) f4 buf[2][2 * kPP];
+    const int col = xcd_column(blockIdx.x, ncol);
+    if (col < 0) return;
+    const int tx = col % ntx, ty = (col / ntx) % nty, tz = (col / (ntx * nty)) % ntz;
+    const int64_t vol = (int64_t)Z * Y * X, img = col / (ntx * nty * ntz);
+    const int x0 = tx * kCX, y0 = ty * kCY, z0 = tz * cz, z1 = min(z0 + cz, Z);
+    const float *base = in + img * vol * 8;
+    const int tid = threadIdx.x;
+    int off[NL];
+    const unsigned valid = plane_offsets<8, 128, NL>(tid, x0, y0, Y, X, wrap, off);
+    f4 v[NL];
+    auto store = [&](int b, int z) {
+#pragma unroll
+        for (int k = 0; k < NL; ++k) {
+            const int e = tid + 128 * k;
+            if (e < 2 * kPP) buf[b][(e & 1) * kPP + e / 2] = plane_piece(v[k], valid, k, z, Z, wrap);
+        }
+    };
+    const int lx = tid % kCX, ly = 2 * (tid / kCX);
+    bool ok[2];
+    int64_t qp[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int x = x0 + lx, y = y0 + ly + j;
+        ok[j] = x < X && y < Y;
+        qp[j] = (int64_t)min(y, Y - 1) * X + min(x, X - 1);
+    }
+    // sums of the outputs one plane back, of this plane and one ahead
+    float a0[2] = {0.f, 0.f}, a1[2] = {0.f, 0.f}, a2[2] = {0.f, 0.f};
+    load_plane<8, NL>(base, z0 - 1, Z, Y * X, wrap, off, v);
+    store(0, z0 - 1);
+    __syncthreads();
+    for (int z = z0 - 1, b = 0; z <= z1; ++z, b ^= 1) {
+        int m[2] = {0, 0};
+        if (boxpt != nullptr && z > z0)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) m[j] = boxpt[(int64_t)(z - 1) * Y * X + qp[j]];
+        if (z < z1) load_plane<8, NL>(base, z + 1, Z, Y * X, wrap, off, v);
+        __builtin_amdgcn_sched_barrier(0);
+        const f4 *row = buf[b] + ly * kPX + lx;
+        f4 r[2][6];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) r[0][k] = row[(k & 1) * kPP + k / 2];
+#pragma unroll
+        for (int dyp = 0; dyp < 4; ++dyp) {
+            if (dyp < 3)
+#pragma unroll
+                for (int k = 0; k < 6; ++k) r[(dyp + 1) & 1][k] = row[(k & 1) * kPP + (dyp + 1) * kPX + k / 2];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int dy = dyp - j;
+                if (dy < 0 || dy > 2) continue;
+                // the weights are loaded here, 72 at a time: all 216, kept
+                // over the planes, would not fit the scalar registers
+                int wo = 3 * dy * 8;
+                asm volatile("" : "+s"(wo));
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) {
+                        const float u = r[dyp & 1][2 * dx + c / 4][c % 4];
+                        const float *w = wt + wo + dx * 8 + c;
+                        a0[j] = fmaf(w[2 * 72], u, a0[j]);
+                        a1[j] = fmaf(w[72], u, a1[j]);
+                        a2[j] = fmaf(w[0], u, a2[j]);
+                    }
+                asm volatile("" : "+v"(a0[j]), "+v"(a1[j]), "+v"(a2[j]));
+            }
+        }
+        // to LDS first: waiting for the loads then does not wait for the results' stores
+        if (z < z1) store(b ^ 1, z + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            if (z > z0 && ok[j]) out[img * vol + (int64_t)(z - 1) * Y * X + qp[j]] = m[j] >= 0 ? a0[j] : 0.f;
+            a0[j] = a1[j];
+            a1[j] = a2[j];
+            a2[j] = 0.f;
         }
         __syncthreads();
-        for (int row = wave; row < kTZ * kTY; row += 4) {
-            const int lz = row / kTY, ly = row % kTY;
-            const int rb = (lz * HY + ly) * HX * 8;
-            // one accumulator per product: four independent chains
-            f4 acc[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int c = 0; c < 7; ++c) {
-                const bf8 ah = __builtin_bit_cast(bf8, *(const us8 *)(th + rb + aoff[c]));
-                const bf8 al = __builtin_bit_cast(bf8, *(const us8 *)(tl + rb + aoff[c]));
-                acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bl[c], acc[0], 0, 0, 0);
-                acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[c], acc[1], 0, 0, 0);
-                acc[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[c], acc[2], 0, 0, 0);
-                acc[3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[c], acc[3], 0, 0, 0);
-            }
-            // the small products first; lanes of channels 0..7 hold the 4
-            // outputs of rows 4 g .. 4 g + 3, and hand the last two to the
-            // lane 8 above (whose channel column is empty), so every lane
-            // evaluates two tanh
-            const f4 d = ((acc[0] + acc[1]) + acc[2]) + acc[3];
-            const float s0 = __shfl_xor(d[2], 8, 64), s1 = __shfl_xor(d[3], 8, 64);
-            const int cc = co & 7, r0 = co < 8 ? 0 : 2;
-            const float v0 = co < 8 ? d[0] : s0, v1 = co < 8 ? d[1] : s1;
-            const int y = y0 + ly, z = z0 + lz;
-            if (y >= Y || z >= Z) continue;
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int x = x0 + 4 * g + r0 + k;
-                if (x >= X) continue;
-                const int q = (z * Y + y) * X + x;
-                const bool inside = boxpt == nullptr || boxpt[q] >= 0;
-                out[((int64_t)img * vol + q) * 8 + cc] = inside ? tanhf(k == 0 ? v0 : v1) : 0.f;
-            }
-        }
     }
 }
 
-// Weights of the input adjoint: Wt[ci][co][26 - t] = W[co][ci][t].
-__global__ void flip_kernel(const float *__restrict__ params, float *__restrict__ wt) {
+// Launches conv1_kernel over n boxes of Z x Y x X points.
+void conv1(const float *in, float *out, const float *wt, const int32_t *boxpt, int n, int Z, int Y, int X, int wrap,
+           hipStream_t st) {
+    const Columns c(n, Z, Y, X);
+    hipLaunchKernelGGL(conv1_kernel, c.grid(), dim3(128), 0, st, in, out, wt, boxpt, c.n, Z, Y, X, wrap, c.ntx, c.nty,
+                       c.ntz, c.cz);
+}
+
+// Weights of the input adjoint, Wt[ci][co][26 - t] = W[co][ci][t] of layers 2
+// and 3, and the two layers with one output channel in conv1_kernel's order
+// [27][8]: layer 3, and layer 1's adjoint in place of its Wt.
+constexpr int kW3T = kNW, kNWT = kNW + 216;
+__device__ __forceinline__ void place_weight(int i, float w, float *__restrict__ wt) {
+    if (i < kW2) {
+        wt[kW1 + (26 - i % 27) * 8 + i / 27] = w;
+    } else if (i < kW3) {
+        const int j = i - kW2, t = j % 27, ci = (j / 27) % 8, co = j / (27 * 8);
+        wt[kW2 + (ci * 8 + co) * 27 + (26 - t)] = w;
+    } else {
+        const int j = i - kW3, t = j % 27, ci = j / 27;
+        wt[kW3 + ci * 27 + (26 - t)] = w;
+        wt[kW3T + t * 8 + ci] = w;
+    }
+}
+__global__ void place_kernel(const float *__restrict__ params, float *__restrict__ wt) {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= kNW) return;
-    int off, CI, CO;
-    if (i < kW2) { off = kW1; CI = 1; CO = 8; }
-    else if (i < kW3) { off = kW2; CI = 8; CO = 8; }
-    else { off = kW3; CI = 8; CO = 1; }
-    const int j = i - off, t = j % 27, ci = (j / 27) % CI, co = j / (27 * CI);
-    wt[off + (ci * CO + co) * 27 + (26 - t)] = params[i];
+    if (i < kNW) place_weight(i, params[i], wt);
 }
 
 // Weight gradient partials on the FP32 matrix cores.  With q = p + (dx - 1)
@@ -323,6 +492,7 @@ __global__ void flip_kernel(const float *__restrict__ params, float *__restrict_
 // short; wgrad_final_kernel adds the work-groups in FP64.  One thread per (tap, ci) that
 // gathered its taps from global memory took 792-843 us a layer for 32 crops of 16^3;
 // this takes 8 (1 -> 8), 15 (8 -> 8) and 17 us (8 -> 1).
+constexpr int kTX = 16, kTY = 8, kTZ = 4;   // points of a block
 constexpr int kWgMax = 1024;
 template <int CI, int CO>
 __global__ void __launch_bounds__(256)
@@ -584,7 +754,8 @@ __global__ void df_kernel(const float *__restrict__ ae, const double *__restrict
 
 // Adam (Kingma and Ba, 2015): c1 = 1 - beta1^t, c2 = 1 - beta2^t.
 __global__ void adam_kernel(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
-                            float *__restrict__ v, float lr, float b1, float b2, float eps, float c1, float c2) {
+                            float *__restrict__ v, float *__restrict__ wt, float lr, float b1, float b2, float eps,
+                            float c1, float c2) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= kNP) return;
     const float gi = g[i];
@@ -592,7 +763,9 @@ __global__ void adam_kernel(float *__restrict__ p, const float *__restrict__ g, 
     const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
     m[i] = mi;
     v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    p[i] = pi;
+    if (i < kNW) place_weight(i, pi, wt);
 }
 
 // ------------------------------------------------- grid <-> dense boxes
@@ -606,14 +779,27 @@ scatter_kernel(const T *__restrict__ r, const int32_t *__restrict__ boxpt, const
     const int blk = blockIdx.y, tid = threadIdx.x;
     const int q0 = blockIdx.x * 64;
     const int kb = k0 + blk * B;               // first state of the block
-    for (int e = tid; e < 64 * B; e += 256) {
-        const int qi = e / B, s = e % B, q = q0 + qi;
-        float v = 0.f;
-        if (q < vol) {
-            const int pt = boxpt[q];
-            if (pt >= 0) v = (float)((double)r[((int64_t)(kb / B) * np + pt) * B + s] * scale[kb + s]);
+    // loads in flight before their uses: the box point, then its field entry
+    for (int e0 = tid; e0 < 64 * B; e0 += 256 * 8) {
+        int pt[8];
+        T v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int e = e0 + 256 * k, q = q0 + e / B;
+            pt[k] = e < 64 * B && q < vol ? boxpt[q] : -1;
         }
-        tile[s][qi] = v;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            v[k] = T(0);
+            if (pt[k] >= 0) v[k] = r[((int64_t)(kb / B) * np + pt[k]) * B + (e0 + 256 * k) % B];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int e = e0 + 256 * k, s = e % B;
+            if (e < 64 * B) tile[s][e / B] = pt[k] >= 0 ? (float)((double)v[k] * scale[kb + s]) : 0.f;
+        }
     }
     __syncthreads();
     for (int e = tid; e < 64 * B; e += 256) {
@@ -627,13 +813,22 @@ __global__ void __launch_bounds__(256)
 gather_kernel(const float *__restrict__ f, const int32_t *__restrict__ boxidx, const double *__restrict__ scale,
               int k0, int B, int64_t np, int vol, T *__restrict__ out) {
     __shared__ float tile[64][65];
-    const int blk = blockIdx.y, tid = threadIdx.x;
-    const int64_t p0 = (int64_t)blockIdx.x * 64;
+    // bricks along x share lines of f: consecutive ones go to one XCD's L2
+    const int blk = blockIdx.y, tid = threadIdx.x, chunk = xcd_column(blockIdx.x, (int)((np + 63) / 64));
+    if (chunk < 0) return;
+    const int64_t p0 = (int64_t)chunk * 64;
     const int kb = k0 + blk * B;
-    for (int e = tid; e < 64 * B; e += 256) {
-        const int s = e / 64, pi = e % 64;
-        const int64_t p = p0 + pi;
-        tile[s][pi] = p < np ? f[(int64_t)(blk * B + s) * vol + boxidx[p]] : 0.f;
+    const int pi = tid % 64;
+    const bool in = p0 + pi < np;
+    const float *src = f + (int64_t)blk * B * vol + (in ? boxidx[p0 + pi] : 0);
+    for (int s0 = tid / 64; s0 < B; s0 += 4 * 8) {   // eight loads in flight
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = in && s0 + 4 * k < B ? src[(int64_t)(s0 + 4 * k) * vol] : 0.f;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (s0 + 4 * k < B) tile[s0 + 4 * k][pi] = v[k];
     }
     __syncthreads();
     for (int e = tid; e < 64 * B; e += 256) {
@@ -836,21 +1031,25 @@ rs_status set_box(rs_cnn *c, const rs_grid *g) {
     return RS_OK;
 }
 
+// Parameters from the host, in every layout the kernels read.
+rs_status upload_params(rs_cnn *c, const float *params) {
+    RS_HIP(hipMemcpy(c->params.p, params, kNP * sizeof(float), hipMemcpyHostToDevice));
+    hipLaunchKernelGGL(place_kernel, dim3((kNW + 255) / 256), dim3(256), 0, nullptr, c->params.as<float>(),
+                       c->wt.as<float>());
+    RS_HIP(hipGetLastError());
+    RS_HIP(hipStreamSynchronize(nullptr));
+    return RS_OK;
+}
+
 rs_status ensure(rs::DevBuf &b, size_t bytes) { return b.bytes >= bytes ? RS_OK : b.alloc(bytes); }
 
 // f = network(u) for n boxes; activations kept in a1, a2.
 rs_status forward(rs_cnn *c, const float *u, float *f, int n, int Z, int Y, int X, int wrap,
                   const int32_t *boxpt, hipStream_t st) {
     const float *P = c->params.as<float>();
-    conv<1, 8, 0>(u, c->a1.as<float>(), P + kW1, nullptr, boxpt, n, Z, Y, X, wrap, st);
-    {
-        const int ntx = (X + kTX - 1) / kTX, nty = (Y + kTY - 1) / kTY, ntz = (Z + kTZ - 1) / kTZ;
-        // at most three work-groups per CU resident; each takes tiles in turn
-        const int64_t nwg = std::min<int64_t>((int64_t)ntx * nty * ntz * n, 3 * 256);
-        hipLaunchKernelGGL(conv2_mfma_kernel, dim3((unsigned)nwg), dim3(256), 0, st, c->a1.as<float>(),
-                           c->a2.as<float>(), P + kW2, boxpt, n, Z, Y, X, wrap, ntx, nty, ntz);
-    }
-    conv<8, 1, 1>(c->a2.as<float>(), f, P + kW3, nullptr, boxpt, n, Z, Y, X, wrap, st);
+    conv8<1, 0, false>(u, c->a1.as<float>(), P + kW1, nullptr, boxpt, n, Z, Y, X, wrap, st);
+    conv8<8, 0, true>(c->a1.as<float>(), c->a2.as<float>(), P + kW2, nullptr, boxpt, n, Z, Y, X, wrap, st);
+    conv1(c->a2.as<float>(), f, c->wt.as<float>() + kW3T, boxpt, n, Z, Y, X, wrap, st);
     RS_HIP(hipGetLastError());
     return RS_OK;
 }
@@ -878,7 +1077,7 @@ extern "C" rs_status rs_cnn_create(int32_t max_batch, int64_t max_box, rs_cnn **
     c->max_box = max_box;
     const size_t pts = (size_t)max_batch * max_box;
     rs_status s = c->params.alloc(kNP * sizeof(float));
-    if (!s) s = c->wt.alloc(kNW * sizeof(float));
+    if (!s) s = c->wt.alloc(kNWT * sizeof(float));
     if (!s) s = c->grad.alloc(kNP * sizeof(float));
     if (!s) s = c->m.alloc(kNP * sizeof(float));
     if (!s) s = c->v.alloc(kNP * sizeof(float));
@@ -891,7 +1090,7 @@ extern "C" rs_status rs_cnn_create(int32_t max_batch, int64_t max_box, rs_cnn **
     if (!s) s = c->loss.alloc(sizeof(double));
     if (s) { delete c; return s; }
     std::vector<float> zero(kNP, 0.f);
-    if (hipMemcpy(c->params.p, zero.data(), kNP * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
+    if (upload_params(c, zero.data()) ||
         hipMemcpy(c->m.p, zero.data(), kNP * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c->v.p, zero.data(), kNP * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c->grad.p, zero.data(), kNP * sizeof(float), hipMemcpyHostToDevice) != hipSuccess) {
@@ -906,7 +1105,7 @@ extern "C" void rs_cnn_destroy(rs_cnn *c) { delete c; }
 
 extern "C" rs_status rs_cnn_set_params(rs_cnn *c, const float *params) {
     if (!c || !params) return rs::fail(RS_EINVAL, "rs_cnn_set_params: null argument");
-    RS_HIP(hipMemcpy(c->params.p, params, kNP * sizeof(float), hipMemcpyHostToDevice));
+    if (const rs_status s = upload_params(c, params)) return s;
     std::vector<float> zero(kNP, 0.f);
     RS_HIP(hipMemcpy(c->m.p, zero.data(), kNP * sizeof(float), hipMemcpyHostToDevice));
     RS_HIP(hipMemcpy(c->v.p, zero.data(), kNP * sizeof(float), hipMemcpyHostToDevice));
@@ -956,7 +1155,7 @@ extern "C" rs_status rs_cnn_load(rs_cnn *c, const char *path) {
                     std::fread(buf.data(), sizeof(float), buf.size(), f) == buf.size();
     std::fclose(f);
     if (!ok) return fail(RS_EINVAL, std::string("rs_cnn_load: not a network checkpoint of this layout: ") + path);
-    RS_HIP(hipMemcpy(c->params.p, buf.data(), kNP * sizeof(float), hipMemcpyHostToDevice));
+    if (const rs_status s = upload_params(c, buf.data())) return s;
     RS_HIP(hipMemcpy(c->m.p, buf.data() + kNP, kNP * sizeof(float), hipMemcpyHostToDevice));
     RS_HIP(hipMemcpy(c->v.p, buf.data() + 2 * kNP, kNP * sizeof(float), hipMemcpyHostToDevice));
     c->adam_t = hdr[1];
@@ -1010,24 +1209,22 @@ extern "C" rs_status rs_cnn_loss_grad(rs_cnn *c, const float *u, const float *t,
                        c->gz.as<double>(), c->coef.as<double>(), c->loss.as<double>(), G);
     hipLaunchKernelGGL(df_kernel, dim3(gsz), dim3(256), 0, st, ae, c->gz.as<double>(), c->coef.as<double>(), Z, Y, X,
                        margin, n, df);
-    hipLaunchKernelGGL(flip_kernel, dim3((kNW + 255) / 256), dim3(256), 0, st, P, WT);
     RS_HIP(hipGetLastError());
     // layer 3: weights, then delta of layer 2 (through tanh)
     float *wp = c->wpart.as<float>();
     const dim3 gw((unsigned)nwg);
     hipLaunchKernelGGL((wgrad_kernel<8, 1>), gw, dim3(256), 0, st, a2, df, n, Z, Y, X, ntx, nty, ntz,
                        wp + (int64_t)kW3 * nwg);
-    conv<1, 8, 2>(df, d2, WT + kW3, a2, nullptr, n, Z, Y, X, 0, st);
+    conv8<1, 2, false>(df, d2, WT + kW3, a2, nullptr, n, Z, Y, X, 0, st);
     // layer 2
     hipLaunchKernelGGL((wgrad_kernel<8, 8>), gw, dim3(256), 0, st, a1, d2, n, Z, Y, X, ntx, nty, ntz,
                        wp + (int64_t)kW2 * nwg);
-    conv<8, 8, 2>(d2, d1, WT + kW2, a1, nullptr, n, Z, Y, X, 0, st);
+    conv8<8, 2, false>(d2, d1, WT + kW2, a1, nullptr, n, Z, Y, X, 0, st);
     // layer 1
     hipLaunchKernelGGL((wgrad_kernel<1, 8>), gw, dim3(256), 0, st, u, d1, n, Z, Y, X, ntx, nty, ntz,
                        wp + (int64_t)kW1 * nwg);
     hipLaunchKernelGGL(wgrad_final_kernel, dim3((kNW + 63) / 64), dim3(1024), 0, st, wp, nwg, G);
-    if (du)
-        conv<8, 1, 1>(d1, du, WT + kW1, nullptr, nullptr, n, Z, Y, X, 0, st);
+    if (du) conv1(d1, du, WT + kW1, nullptr, n, Z, Y, X, 0, st);
     RS_HIP(hipGetLastError());
     if (loss) RS_HIP(hipMemcpyAsync(loss, c->loss.p, sizeof(double), hipMemcpyDeviceToHost, st));
     if (grad) RS_HIP(hipMemcpyAsync(grad, G, kNP * sizeof(float), hipMemcpyDeviceToHost, st));
@@ -1043,7 +1240,7 @@ extern "C" rs_status rs_cnn_adam_step(rs_cnn *c, float lr, float beta1, float be
     const float c1 = (float)(1.0 - std::pow((double)beta1, (double)c->adam_t));
     const float c2 = (float)(1.0 - std::pow((double)beta2, (double)c->adam_t));
     hipLaunchKernelGGL(adam_kernel, dim3((kNP + 255) / 256), dim3(256), 0, (hipStream_t)stream, c->params.as<float>(),
-                       c->grad.as<float>(), c->m.as<float>(), c->v.as<float>(), lr, beta1, beta2, eps, c1, c2);
+                       c->grad.as<float>(), c->m.as<float>(), c->v.as<float>(), c->wt.as<float>(), lr, beta1, beta2, eps, c1, c2);
     RS_HIP(hipGetLastError());
     return RS_OK;
 }
@@ -1089,11 +1286,11 @@ rs_status cnn_precondition(rs_cnn *c, const rs_grid *g, const void *r, const dou
         if ((s = forward(c, c->u.as<float>(), c->f.as<float>(), nb * B, Z, Y, X, wrap, c->boxpt.as<int32_t>(), st)))
             return s;
         if (dtype == RS_F64)
-            hipLaunchKernelGGL(gather_kernel<double>, dim3((unsigned)((np + 63) / 64), nb), dim3(256), 0, st,
+            hipLaunchKernelGGL(gather_kernel<double>, dim3((unsigned)((np + 511) / 512 * 8), nb), dim3(256), 0, st,
                                c->f.as<float>(), c->boxidx.as<int32_t>(), c->outs.as<double>(), k0, B, np, vol,
                                (double *)out);
         else
-            hipLaunchKernelGGL(gather_kernel<float>, dim3((unsigned)((np + 63) / 64), nb), dim3(256), 0, st,
+            hipLaunchKernelGGL(gather_kernel<float>, dim3((unsigned)((np + 511) / 512 * 8), nb), dim3(256), 0, st,
                                c->f.as<float>(), c->boxidx.as<int32_t>(), c->outs.as<double>(), k0, B, np, vol,
                                (float *)out);
         RS_HIP(hipGetLastError());

@@ -52,6 +52,24 @@ def test_forward_matches_oracle(dims, periodic):
         assert np.max(np.abs(f[i] - want)) <= 1e-5 * np.max(np.abs(want))
 
 
+# one point, rows of one column and past it, whole 16 x 16 columns, one point
+# past them on each axis, and enough boxes for columns of the full depth, whose
+# last one is cut short
+@pytest.mark.parametrize("n,dims,periodic", [(1, (1, 1, 1), True), (2, (1, 1, 40), False), (2, (4, 16, 16), True),
+                                             (3, (5, 17, 33), False), (2, (3, 18, 17), True),
+                                             (1100, (40, 3, 2), True), (1100, (33, 2, 3), False)])
+def test_forward_at_column_edges(n, dims, periodic):
+    p = _params(15)
+    net = rsd.Cnn(n, int(np.prod(dims)))
+    net.set_params(p)
+    u = np.random.default_rng(16).normal(size=(n,) + dims).astype(np.float32)
+    f = net.forward(_dev(u), periodic=periodic).cpu().numpy()
+    for i in sorted({0, n // 2, n - 1}):
+        want, _ = ocnn.forward(p, u[i].astype(np.float64), np.ones(dims), "wrap" if periodic else "zero")
+        # as above: layer 2's split products carry about 2^-16 per term
+        assert np.max(np.abs(f[i] - want)) <= 1e-5 * np.max(np.abs(want))
+
+
 def test_loss_gradient_and_adam_match_oracle():
     p = _params(3)
     net = rsd.Cnn(4, 4096)
