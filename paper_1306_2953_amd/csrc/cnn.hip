@@ -717,29 +717,44 @@ loss_partial_kernel(const float *__restrict__ em, const float *__restrict__ ae, 
 
 // loss = sum_i <e|Ae>_i / sum_i <t|At>_i; coef = 2 / sum_i <t|At>_i (so
 // dL/dpred = coef M A e); gain-parameter gradient into grad[kNW], grad[kNW + 1].
-__global__ void loss_final_kernel(const double *__restrict__ partial, int n, int nch, const double *__restrict__ gz,
-                                  double *__restrict__ coef, double *__restrict__ loss, float *__restrict__ grad) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double E2 = 0, T2 = 0;
-    for (int i = 0; i < n; ++i)
-        for (int c = 0; c < nch; ++c) {
-            E2 += partial[((int64_t)i * nch + c) * 3];
-            T2 += partial[((int64_t)i * nch + c) * 3 + 1];
-        }
-    const double cf = T2 > 0 ? 2.0 / T2 : 0.0;
-    double ga = 0, gb = 0;
-    for (int i = 0; i < n; ++i) {
-        double ef = 0;
-        for (int c = 0; c < nch; ++c) ef += partial[((int64_t)i * nch + c) * 3 + 2];
-        coef[i] = cf;
-        const double dg = cf * ef;
-        const double sg = sigmoid_d(gz[3 * i + 1]);
-        ga += dg * sg;
-        gb += dg * sg * gz[3 * i + 2];
+// One work-group, a thread per sample (samples i, i + 256, ... where there are
+// more), then sums over the threads in a fixed order; one thread doing it all
+// took 19 us for 32 samples, this 5.
+__device__ __forceinline__ double sum256(double v, double *red) {
+    const int t = threadIdx.x;
+    __syncthreads();
+    red[t] = v;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if (t < s) red[t] += red[t + s];
+        __syncthreads();
     }
+    return red[0];
+}
+__global__ void __launch_bounds__(256)
+loss_final_kernel(const double *__restrict__ partial, int n, int nch, const double *__restrict__ gz,
+                  double *__restrict__ coef, double *__restrict__ loss, float *__restrict__ grad) {
+    __shared__ double red[256];
+    double e2 = 0, t2 = 0, ga = 0, gb = 0;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        double ef = 0;
+        for (int c = 0; c < nch; ++c) {
+            const double *p = partial + ((int64_t)i * nch + c) * 3;
+            e2 += p[0];
+            t2 += p[1];
+            ef += p[2];
+        }
+        const double d = ef * sigmoid_d(gz[3 * i + 1]);
+        ga += d;
+        gb += d * gz[3 * i + 2];
+    }
+    const double E2 = sum256(e2, red), T2 = sum256(t2, red), GA = sum256(ga, red), GB = sum256(gb, red);
+    const double cf = T2 > 0 ? 2.0 / T2 : 0.0;
+    for (int i = threadIdx.x; i < n; i += 256) coef[i] = cf;
+    if (threadIdx.x) return;
     *loss = T2 > 0 ? E2 / T2 : 0.0;
-    grad[kNW] = (float)ga;
-    grad[kNW + 1] = (float)gb;
+    grad[kNW] = (float)(cf * GA);
+    grad[kNW + 1] = (float)(cf * GB);
 }
 
 __global__ void df_kernel(const float *__restrict__ ae, const double *__restrict__ gz,
@@ -1205,7 +1220,7 @@ extern "C" rs_status rs_cnn_loss_grad(rs_cnn *c, const float *u, const float *t,
     hipLaunchKernelGGL(kin_kernel, dim3(gsz), dim3(256), 0, st, tm, at, sigma, h, Z, Y, X, n);
     hipLaunchKernelGGL(loss_partial_kernel, dim3(nch, n), dim3(256), 0, st, em, ae, tm, at, f, Z, Y, X, margin, nch,
                        c->lpart.as<double>());
-    hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(64), 0, st, c->lpart.as<double>(), n, nch,
+    hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(256), 0, st, c->lpart.as<double>(), n, nch,
                        c->gz.as<double>(), c->coef.as<double>(), c->loss.as<double>(), G);
     hipLaunchKernelGGL(df_kernel, dim3(gsz), dim3(256), 0, st, ae, c->gz.as<double>(), c->coef.as<double>(), Z, Y, X,
                        margin, n, df);
