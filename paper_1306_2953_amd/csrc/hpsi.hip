@@ -786,13 +786,45 @@ nl_partial_kernel(const int32_t *__restrict__ chunk_beg, const int32_t *__restri
     double a[NPJ];
 #pragma unroll
     for (int i = 0; i < NPJ; ++i) a[i] = 0.0;
-    // unrolled so that several entries' gathers are in flight per thread
-#pragma unroll 4
-    for (int e = e0 + r; e < e1; e += R) {
-        const double x = (double)psi[sph_idx[e] * B + s];
-        const T *g = gamma + NPJ * (int64_t)e;
+    // batches of U entries: the next batch's field values and the indices of
+    // the one after it are in flight while a batch is summed (an index, then the
+    // value it points to, is the latency that bounds this loop).  Past the
+    // end the last entry is read again and counts as zero.  Loads of one batch
+    // of 4 at a time took 38.6 us for 60 spheres of 950 points with 16
+    // projectors and 128 FP32 columns, this 23; for 8 spheres, 4 projectors and 32
+    // FP64 columns 15.5 -> 11.
+    constexpr int U = NPJ <= 4 ? 8 : 4;
+    if (e0 < e1) {
+        int id[U];
+        T x[U], xn[U];
+        auto load_id = [&](int e) {
 #pragma unroll
-        for (int i = 0; i < NPJ; ++i) a[i] += (double)g[i] * x;
+            for (int k = 0; k < U; ++k) id[k] = sph_idx[min(e + k * R, e1 - 1)];
+        };
+        auto load_x = [&](int e) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) xn[k] = psi[id[k] * B + s];
+        };
+        load_id(e0 + r);
+        load_x(e0 + r);
+        load_id(e0 + r + U * R);
+        for (int e = e0 + r; e < e1; e += U * R) {
+            T g[U][NPJ];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                x[k] = e + k * R < e1 ? xn[k] : T(0);
+                const T *ge = gamma + NPJ * (int64_t)min(e + k * R, e1 - 1);
+#pragma unroll
+                for (int i = 0; i < NPJ; ++i) g[k][i] = ge[i];
+            }
+            load_x(e + U * R);
+            load_id(e + 2 * U * R);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+#pragma unroll
+                for (int i = 0; i < NPJ; ++i) a[i] += (double)g[k][i] * (double)x[k];
+        }
     }
 #pragma unroll
     for (int i = 0; i < NPJ; ++i) red[i][threadIdx.x] = a[i];
