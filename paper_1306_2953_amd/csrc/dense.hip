@@ -1330,15 +1330,19 @@ cholesky_lds_kernel(const double *__restrict__ S, double *__restrict__ U, int N,
     if (tid == 0) *info = done < N ? done + 1 : 0;
 }
 
-// N > 128: right-looking in global memory.  Thread (c, g) owns the columns
+// N > 128: right-looking, in LDS where the matrix fits (N <= 130) and in global
+// memory beyond.  Thread (c, g) owns the columns
 // j = c (mod 128) and the rows i = g (mod nt/128) of the trailing update, so
 // no index is divided.  Step k reads only row k of W (unscaled: the update
 // subtracts W[k][i] W[k][j] / d) and writes only rows below it, so a step
 // needs one barrier; row k of U goes straight to U.  Every thread reads the
 // same pivot d, so all leave the loop together on a bad pivot.
+template <bool LDSW>
 __global__ void __launch_bounds__(1024)
-cholesky_kernel(const double *__restrict__ S, double *__restrict__ W, double *__restrict__ U, int N,
+cholesky_kernel(const double *__restrict__ S, double *__restrict__ Wg, double *__restrict__ U, int N,
                 int *__restrict__ info) {
+    extern __shared__ double lds_w[];
+    double *W = LDSW ? lds_w : Wg;
     const int tid = threadIdx.x, nt = blockDim.x;
     const int c = tid & 127, g = tid >> 7, ng = nt >> 7;
     for (int e = tid; e < N * N; e += nt) {
@@ -2198,7 +2202,19 @@ rs_status cholesky(DenseWork &w, const double *S, double *U, int N, int *info_de
         hipLaunchKernelGGL(cholesky_lds_kernel, dim3(1), dim3(nt), (size_t)16 * nb * kDenseLd * sizeof(double), st, S,
                            U, N, info_dev);
     } else {
-        hipLaunchKernelGGL(cholesky_kernel, dim3(1), dim3(1024), 0, st, S, w.mwork.as<double>(), U, N, info_dev);
+        const size_t lds = (size_t)N * N * sizeof(double);
+        if (lds <= kJacobiLds) {
+            if (!w.chol_wide_set) {
+                RS_HIP(hipFuncSetAttribute((const void *)cholesky_kernel<true>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kJacobiLds));
+                w.chol_wide_set = true;
+            }
+            hipLaunchKernelGGL(cholesky_kernel<true>, dim3(1), dim3(1024), lds, st, S, w.mwork.as<double>(), U, N,
+                               info_dev);
+        } else {
+            hipLaunchKernelGGL(cholesky_kernel<false>, dim3(1), dim3(1024), 0, st, S, w.mwork.as<double>(), U, N,
+                               info_dev);
+        }
     }
     RS_HIP(hipGetLastError());
     return RS_OK;
