@@ -440,8 +440,7 @@ def cage_compare(max_steps=300):
 
 def hartree_rate(w, steps=10):
     """Hartree potential (Sec. 7) of a Gaussian density on the workload's grid:
-    time per solve, the FFT box, and the bytes the six 1-D FFT passes move
-    (each reads and writes the complex FP64 box once)."""
+    time per solve and the FFT box."""
     import torch
     import paper_1306_2953_amd as rsd
     g = rsd.Grid.for_workload(w)
@@ -454,10 +453,8 @@ def hartree_rate(w, steps=10):
     for _ in range(2):
         f()
     t = time_calls(f, steps, torch.cuda.current_stream())
-    fft_bytes = 6 * 2 * 16 * ps.nbox ** 3
     return {"workload": w.name, "grid_points": g.np, "fft_box": ps.nbox, "cutoff_radius_bohr": ps.rc,
-            "ms_per_solve": t * 1e3, "fft_pass_bytes": fft_bytes,
-            "fft_pass_bytes_over_solve_time_gbs": fft_bytes / t / 1e9}
+            "ms_per_solve": t * 1e3}
 
 
 def scf_run(w, nocc=8, nstates=32, max_iter=60, tol=1e-6):
