@@ -136,6 +136,32 @@ def test_hpsi_routes_agree(kind, n, nat, lmax, dtype, B):
         assert float((got[k] - one[0]).abs().max()) <= tol * float(one.abs().max()), (many, k)
 
 
+# The separate projector add takes four points a lane in large calls, one in
+# small ones: 15 blocks of 64 at once (a last group of blocks that is not
+# full) against one at a time, on spheres that overlap.
+@pytest.mark.parametrize("lmax", [0, 1, 2, 3])
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_projector_add_point_runs(lmax, dtype):
+    g = rsd.Grid("periodic", 0.25, n=40)
+    rng = np.random.default_rng(7)
+    pos, rc = rng.uniform(3.0, 7.0, (9, 3)), 2.0
+    near = np.zeros(g.np, bool)
+    for q in pos:
+        d = g.xyz() - q
+        near |= np.sum((d - 10.0 * np.round(d / 10.0)) ** 2, axis=1) <= rc * rc
+    assert near.sum() * 64 * 4 > (2 << 20) > near.sum() * 64       # either side of the line
+    nl = rsd.NonLocal(g, pos, rng.uniform(0.5, 2.0, (9, (lmax + 1) ** 2)), rc, 0.5, max_states=960, lmax=lmax)
+    tdt = torch.float64 if dtype == np.float64 else torch.float32
+    gen = torch.Generator(device=DEV).manual_seed(8)
+    psi = torch.rand((15, g.np, 64), generator=gen, device=DEV, dtype=tdt) - 0.5
+    v = torch.rand(g.np, generator=gen, device=DEV, dtype=tdt)
+    got = rsd.hpsi_block(g, nl, v, psi, torch.empty_like(psi))
+    tol = 1e-13 if dtype == np.float64 else 1e-6                   # the same sums in the same order
+    for k in (0, 7, 14):
+        one = rsd.hpsi_block(g, nl, v, psi[k:k + 1].clone(), torch.empty_like(psi[k:k + 1]))
+        assert float((got[k] - one[0]).abs().max()) <= tol * float(one.abs().max()), k
+
+
 def test_overlapping_spheres_no_race():
     w = synthetic.make_workload("sphere_r12_h0.2", radius=2.4, nat=8, atom_radius=0.8, rc=1.5)
     og, H, g, nl = _system(w)
