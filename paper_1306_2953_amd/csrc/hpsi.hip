@@ -727,36 +727,76 @@ hpsi_march_kernel(const MarchChunk *__restrict__ chunks, const MarchBrick *__res
 
 // Projector term added to an H psi computed without it: hpsi += sum over the
 // spheres holding the point of gamma_A,i(p) (D_A,i P_A,i), i < NPJ, one lane
-// per state of PTS consecutive points that lie in a sphere (eq. 6).  Such
-// points mostly share their atoms, so a lane keeps the D P of the last atom in
-// registers; read for every point they bound the kernel (16 of them per
-// block, entry and state against one H psi value).  A lane serves 2 or 4 blocks,
-// which share the entry loads; the H psi values are read before the
-// entries, so their latency overlaps the entry loads.  nnl * B < 2^32
-// (checked by the host).  119k points x 32 states in 4 blocks, one point a lane ->
-// four: 4 projectors FP64 83 -> 65 us (55 for its bytes), 16 projectors FP64
-// 191 -> 144, FP32 71 -> 65.
-template <typename T, int NPJ, int PTS> constexpr int add_blocks() { return PTS > 1 && sizeof(T) * NPJ > 64 ? 2 : 4; }
-template <typename T, int NPJ, int PTS>
+// per (state, point) of the points that lie in a sphere (eq. 6).  A lane
+// serves up to 4 blocks: the entry loads are shared and the 4 updates are
+// independent; the H psi values are read before the entries, so their
+// latency overlaps the entry loads.  nnl * B < 2^32 (checked by the host).
+template <typename T, int NPJ>
 __global__ void __launch_bounds__(256)
 nl_add_kernel(const int32_t *__restrict__ nl_pts, int64_t nnl, const int32_t *__restrict__ pt_ptr,
               const int32_t *__restrict__ ent_atom, const T *__restrict__ ent_gamma, const T *__restrict__ dp,
               T *__restrict__ hpsi, int64_t np, int B, int nat, int nblk) {
-    constexpr int KB = add_blocks<T, NPJ, PTS>();
     const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
-    const int64_t j0 = (int64_t)(idx / (uint32_t)B) * PTS;
+    if ((int64_t)idx >= nnl * B) return;
+    const int blk0 = 4 * blockIdx.y;
+    const int nb = min(4, nblk - blk0);
+    const int p = nl_pts[idx / (uint32_t)B];
+    const int s = (int)(idx % (uint32_t)B);
+    const int64_t dstride = (int64_t)nat * NPJ * B;
+    const T *dpl = dp + blk0 * dstride + s;
+    T acc[4] = {T(0), T(0), T(0), T(0)}, y[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (k < nb) y[k] = hpsi[((int64_t)(blk0 + k) * np + p) * B + s];
+    for (int e = pt_ptr[p], e1 = pt_ptr[p + 1]; e < e1; ++e) {
+        T g[NPJ];
+#pragma unroll
+        for (int i = 0; i < NPJ; ++i) g[i] = ent_gamma[NPJ * (int64_t)e + i];
+        const T *d = dpl + ent_atom[e] * NPJ * B;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (k < nb) {
+                const T *dk = d + k * dstride;
+                T t = g[0] * dk[0];
+#pragma unroll
+                for (int i = 1; i < NPJ; ++i) t += g[i] * dk[i * B];
+                acc[k] += t;
+            }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (k < nb) hpsi[((int64_t)(blk0 + k) * np + p) * B + s] = y[k] + acc[k];
+}
+
+// The same with one lane per state of kAddPts consecutive points.  Such points
+// mostly share their atoms, so a lane keeps the D P of the last atom in
+// registers; read for every point they bound the kernel above in large calls
+// (16 of them per block, entry and state against one H psi value).  A lane
+// serves 2 or 4 blocks.  119k points x 32 states in 4 blocks, one point a lane ->
+// four: 4 projectors FP64 83 -> 65 us (55 for its bytes), 16 projectors FP64
+// 191 -> 144, FP32 71 -> 65.
+constexpr int kAddPts = 4;
+template <typename T, int NPJ> constexpr int add_blocks() { return sizeof(T) * NPJ > 64 ? 2 : 4; }
+template <typename T, int NPJ>
+__global__ void __launch_bounds__(256)
+nl_add_run_kernel(const int32_t *__restrict__ nl_pts, int64_t nnl, const int32_t *__restrict__ pt_ptr,
+              const int32_t *__restrict__ ent_atom, const T *__restrict__ ent_gamma, const T *__restrict__ dp,
+              T *__restrict__ hpsi, int64_t np, int B, int nat, int nblk) {
+    constexpr int KB = add_blocks<T, NPJ>();
+    const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
+    const int64_t j0 = (int64_t)(idx / (uint32_t)B) * kAddPts;
     if (j0 >= nnl) return;
     const int blk0 = KB * blockIdx.y;
     const int nb = min(KB, nblk - blk0);
     const int s = (int)(idx % (uint32_t)B);
     const int64_t dstride = (int64_t)nat * NPJ * B;
     const T *dpl = dp + blk0 * dstride + s;
-    int p[PTS], e0[PTS], e1[PTS];
-    T y[PTS][KB];
+    int p[kAddPts], e0[kAddPts], e1[kAddPts];
+    T y[kAddPts][KB];
 #pragma unroll
-    for (int j = 0; j < PTS; ++j) p[j] = j0 + j < nnl ? nl_pts[j0 + j] : -1;
+    for (int j = 0; j < kAddPts; ++j) p[j] = j0 + j < nnl ? nl_pts[j0 + j] : -1;
 #pragma unroll
-    for (int j = 0; j < PTS; ++j) {
+    for (int j = 0; j < kAddPts; ++j) {
         e0[j] = p[j] < 0 ? 0 : pt_ptr[p[j]];
         e1[j] = p[j] < 0 ? 0 : pt_ptr[p[j] + 1];
 #pragma unroll
@@ -766,7 +806,7 @@ nl_add_kernel(const int32_t *__restrict__ nl_pts, int64_t nnl, const int32_t *__
     int atom = -1;
     T d[KB][NPJ];
 #pragma unroll
-    for (int j = 0; j < PTS; ++j) {
+    for (int j = 0; j < kAddPts; ++j) {
         if (p[j] < 0) break;
         T acc[KB];
 #pragma unroll
@@ -776,7 +816,7 @@ nl_add_kernel(const int32_t *__restrict__ nl_pts, int64_t nnl, const int32_t *__
 #pragma unroll
             for (int i = 0; i < NPJ; ++i) g[i] = ent_gamma[NPJ * (int64_t)e + i];
             const int a = ent_atom[e];
-            if (PTS == 1 || a != atom) {
+            if (a != atom) {
                 atom = a;
                 const T *da = dpl + a * NPJ * B;
 #pragma unroll
@@ -975,23 +1015,25 @@ rs_status launch_nl_add(const rs_grid *g, const rs_nl *nl, T *hpsi, int nblk, in
         return fail(RS_EINVAL, "stencil: too many projector points x states for one launch");
     const T *egm = sizeof(T) == 8 ? (const T *)nl->ent_gamma64.p : (const T *)nl->ent_gamma32.p;
     const bool four = nl->nnlpts * B * ((nblk + 3) / 4) >= kAddWide;
-#define RS_NLADD_PTS(NPJ, PTS)                                                                                   \
-    hipLaunchKernelGGL((nl_add_kernel<T, NPJ, PTS>),                                                             \
-                       dim3((unsigned)(((nl->nnlpts + PTS - 1) / PTS * B + 255) / 256),                          \
-                            (nblk + add_blocks<T, NPJ, PTS>() - 1) / add_blocks<T, NPJ, PTS>()),                 \
-                       dim3(256), 0, st, nl->nl_pts.as<int32_t>(), nl->nnlpts, nl->pt_ptr.as<int32_t>(),         \
-                       nl->ent_atom.as<int32_t>(), egm, (const T *)nl->dp.p, hpsi, g->np, B, nl->nat, nblk)
-#define RS_NLADD(NPJ)                            \
-    case NPJ:                                    \
-        if (four) RS_NLADD_PTS(NPJ, 4);          \
-        else RS_NLADD_PTS(NPJ, 1);               \
+    const dim3 one((unsigned)((nl->nnlpts * B + 255) / 256), (nblk + 3) / 4);
+    const unsigned gx = (unsigned)(((nl->nnlpts + kAddPts - 1) / kAddPts * B + 255) / 256);
+#define RS_NLADD_ARGS                                                                                      \
+    dim3(256), 0, st, nl->nl_pts.as<int32_t>(), nl->nnlpts, nl->pt_ptr.as<int32_t>(), nl->ent_atom.as<int32_t>(), egm, \
+        (const T *)nl->dp.p, hpsi, g->np, B, nl->nat, nblk
+#define RS_NLADD(NPJ)                                                                                      \
+    case NPJ:                                                                                              \
+        if (four)                                                                                          \
+            hipLaunchKernelGGL((nl_add_run_kernel<T, NPJ>),                                                \
+                               dim3(gx, (nblk + add_blocks<T, NPJ>() - 1) / add_blocks<T, NPJ>()), RS_NLADD_ARGS); \
+        else                                                                                               \
+            hipLaunchKernelGGL((nl_add_kernel<T, NPJ>), one, RS_NLADD_ARGS);                               \
         break;
     switch (nl->npj) {
         RS_NLADD(1) RS_NLADD(4) RS_NLADD(9) RS_NLADD(16)
         default: return fail(RS_EINVAL, "stencil: unsupported projector count");
     }
 #undef RS_NLADD
-#undef RS_NLADD_PTS
+#undef RS_NLADD_ARGS
     RS_HIP(hipGetLastError());
     return RS_OK;
 }
