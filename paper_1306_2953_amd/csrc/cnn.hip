@@ -326,13 +326,17 @@ conv8_kernel(const float *__restrict__ in, float *__restrict__ out, const float 
 }
 
 // Columns of nbox boxes of Z x Y x X points: counts and depth cz.  32 planes a
-// column cost a sixteenth more border; fewer where that would leave fewer than
-// 2048 work-groups, about two rounds of what is resident, down to 2: single
-// planes read three for one and gain nothing (32 boxes of 16^3: 14 us either way).
+// column cost a sixteenth more border; 16 or 8 where that would leave fewer than
+// 2048 work-groups, about two rounds of what is resident (32 boxes of 52^3: 363
+// us against 404); below that the border weighs more, and 1024 must do (16 boxes
+// of 36^3: 123 against 142).  At least 2: single planes read three for one and
+// gain nothing (layer 2 for 32 boxes of 16^3: 14 us either way).
 struct Columns {
     int ntx, nty, ntz, cz, n;
     Columns(int nbox, int Z, int Y, int X) : ntx((X + kCX - 1) / kCX), nty((Y + kCY - 1) / kCY), cz(32) {
-        while (cz > 2 && (int64_t)ntx * nty * ((Z + cz - 1) / cz) * nbox < 2048) cz /= 2;
+        auto count = [&] { return (int64_t)ntx * nty * ((Z + cz - 1) / cz) * nbox; };
+        while (cz > 8 && count() < 2048) cz /= 2;
+        while (cz > 2 && count() < 1024) cz /= 2;
         ntz = (Z + cz - 1) / cz;
         n = ntx * nty * ntz * nbox;
     }
