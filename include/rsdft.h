@@ -489,7 +489,9 @@ rs_status rs_cnn_adam_step(rs_cnn *c, float lr, float beta1, float beta2, float 
 rs_status rs_cnn_precondition(rs_cnn *c, const rs_grid *g, const void *r, const double *sigma,
                               void *out, int32_t nblk, int32_t B, int32_t dtype, void *stream);
 
-/* Dims {Z, Y, X} of the grid's box. */
+/* Dims {Z, Y, X} of the grid's box.  The handle keeps the tables of the
+ * last grid it was called with, not the grid: a grid may be destroyed once
+ * the calls that were given it have completed. */
 rs_status rs_cnn_box(rs_cnn *c, const rs_grid *g, int32_t dims[3]);
 
 /* Training crops: for crop i with desc (HOST int32 [ncrops][4]) = (state k,

@@ -1087,8 +1087,8 @@ struct rs_cnn {
     rs::DevBuf d1, d2, df, t;      // backward deltas (allocated on first training call)
     rs::DevBuf wpart, lpart, gz, coef, loss;
     rs::DevBuf ss, inv_s, outs, partial;   // preconditioner scratch
-    // dense box of the last grid used
-    const rs_grid *box_grid = nullptr;
+    // dense box of the last grid used (its id; 0: none)
+    uint64_t box_grid = 0;
     int bdims[3] = {0, 0, 0};      // Z, Y, X
     rs::DevBuf boxpt, boxidx;
 };
@@ -1096,7 +1096,7 @@ struct rs_cnn {
 namespace {
 
 rs_status set_box(rs_cnn *c, const rs_grid *g) {
-    if (c->box_grid == g) return RS_OK;
+    if (c->box_grid == g->id) return RS_OK;
     int32_t lo[3] = {INT32_MAX, INT32_MAX, INT32_MAX}, hi[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
     for (int64_t p = 0; p < g->np; ++p)
         for (int a = 0; a < 3; ++a) {
@@ -1113,13 +1113,14 @@ rs_status set_box(rs_cnn *c, const rs_grid *g) {
         pt[q] = (int32_t)p;
         idx[p] = (int32_t)q;
     }
+    c->box_grid = 0;   // until both tables are this grid's
     rs_status s = c->boxpt.upload(pt);
     if (!s) s = c->boxidx.upload(idx);
     if (s) return s;
     c->bdims[0] = Z;
     c->bdims[1] = Y;
     c->bdims[2] = X;
-    c->box_grid = g;
+    c->box_grid = g->id;
     return RS_OK;
 }
 

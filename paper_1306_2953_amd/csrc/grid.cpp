@@ -3,6 +3,7 @@
 // membership is integer-only and coordinates are (i - c) * h rounded as
 // written.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 
@@ -36,6 +37,8 @@ extern "C" rs_status rs_grid_create(const rs_grid_desc *d, rs_grid **out) {
 
     auto g = new (std::nothrow) rs_grid();
     if (!g) return fail(RS_ENOMEM, "host allocation failed");
+    static std::atomic<uint64_t> created{0};
+    g->id = ++created;
     g->kind = d->kind;
     g->h = d->h;
     g->n = d->n;

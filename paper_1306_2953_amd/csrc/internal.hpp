@@ -105,6 +105,9 @@ struct FilterUpdate {
 }  // namespace rs
 
 struct rs_grid {
+    // Never given out twice in a process: what a table made for a grid is kept
+    // under (a destroyed grid's address may come back with other points).
+    uint64_t id = 0;
     int kind = 0;
     double h = 0;
     int n = 0;

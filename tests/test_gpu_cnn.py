@@ -138,6 +138,24 @@ def test_precondition_matches_oracle(kind, dtype, B):
     assert np.max(np.abs(got - want)) <= 2e-5 * np.max(np.abs(want))
 
 
+def test_box_follows_the_grid_not_its_address():
+    """A grid made after another one was destroyed may get its address; the
+    network's box has to be the new grid's (dims only: no field is read)."""
+    net = rsd.Cnn(1, 40000)
+    reused = 0
+    for k in range(40):
+        g = rsd.Grid("box", 0.3, n=12)
+        assert net.box(g) == (12, 12, 12)
+        first = g.handle.value
+        del g
+        g = rsd.Grid("box", 0.3, n=8 + k % 3)
+        assert net.box(g) == (8 + k % 3,) * 3
+        reused += g.handle.value == first
+        del g
+    if not reused:
+        pytest.skip("the allocator gave out no address twice")
+
+
 def test_crops_match_direct_indexing():
     og = ogrid.build_grid("sphere", 0.3, radius=2.4)
     g = rsd.Grid("sphere", 0.3, radius=2.4)
