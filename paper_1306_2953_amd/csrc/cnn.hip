@@ -249,6 +249,15 @@ conv8_kernel(const float *__restrict__ in, float *__restrict__ out, const float 
 #pragma unroll
             for (int h = 0; h < 2; ++h) ac[h] = *(const f4 *)(act + (img * vol + zp + qp[h]) * 8 + 4 * (g & 1));
     };
+    auto activate = [](f4 d, f4 a, bool inside) {
+        f4 r;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float o = MODE == 0 ? tanh_f(d[k]) : d[k] * (1.f - a[k] * a[k]);
+            r[k] = inside ? o : 0.f;
+        }
+        return r;
+    };
     load_marks(z0);
     store(z0 - 1, v);
     store(z0, v1);
@@ -306,12 +315,36 @@ conv8_kernel(const float *__restrict__ in, float *__restrict__ out, const float 
                                                                       acc[c / 3], 0, 0, 0);
                 d = (acc[0] + acc[1]) + acc[2];
             }
-            const bool inside = h ? in1 : in0;
-            const f4 a = h ? ac1 : ac0;
+            res[h] = activate(d, h ? ac1 : ac0, h ? in1 : in0);
+        }
+        // the pair's other row brings 0 x Inf or 0 x NaN into a sum that does not
+        // have that input: a lane with a NaN forms its sums again, own taps only
+        const f4 both = res[0] + res[1];
+        if (__builtin_isnan((both[0] + both[1]) + (both[2] + both[3]))) {
+#pragma unroll 1
+            for (int h = 0; h < 2; ++h) {
+                const int e0 = (2 * (wave + 4 * h) + g / 2) * kPX + px;
+                f4 d = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                for (int t = 0; t < 27; ++t) {
+                    const float *p = ring[(z - 1 + t / 9) & 3];
+                    const int e = e0 + t / 3 % 3 * kPX + t % 3;
+#pragma unroll 1
+                    for (int ci = 0; ci < CI; ++ci) {
+                        float x;
+                        if constexpr (SPLIT) {
+                            const __bf16 *q = (const __bf16 *)p + e * 8 + ci;
+                            x = (float)q[0] + (float)q[kPP * 8];
+                        } else {
+                            x = p[e * CI + ci];
+                        }
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float o = MODE == 0 ? tanh_f(d[k]) : d[k] * (1.f - a[k] * a[k]);
-                res[h][k] = inside ? o : 0.f;
+                        for (int k = 0; k < 4; ++k) d[k] = fmaf(W[((4 * (g & 1) + k) * CI + ci) * 27 + t], x, d[k]);
+                    }
+                }
+                const f4 r = activate(d, h ? ac1 : ac0, h ? in1 : in0);
+                if (h) res[1] = r;
+                else res[0] = r;
             }
         }
         // to LDS first: waiting for the loads then does not wait for the results' stores
@@ -663,6 +696,7 @@ wgrad_kernel(const float *__restrict__ xin, const float *__restrict__ d, int n, 
     __syncthreads();
     if (wave > 0) return;
     float *out = partial + (int64_t)blockIdx.x * (CO * CI * 27);
+    bool nan = false;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -674,9 +708,39 @@ wgrad_kernel(const float *__restrict__ xin, const float *__restrict__ d, int n, 
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int m = 16 * i + 4 * k4 + r;
-                if (m < 9 * CI && c < 3 * CO) out[((c % CO) * CI + m % CI) * 27 + m / CI * 3 + c / CO] = v[r];
+                if (m < 9 * CI && c < 3 * CO) {
+                    out[((c % CO) * CI + m % CI) * 27 + m / CI * 3 + c / CO] = v[r];
+                    nan = nan || __builtin_isnan(v[r]);
+                }
             }
         }
+    // the zeros around a block times Inf or NaN are no part of a gradient: with a
+    // NaN among them the sums are formed again over the taps in the box, a lane
+    // per (tap, ci)
+    if (!__any(nan)) return;
+    for (int e = lane; e < 27 * CI; e += 64) {
+        const int t = e / CI, ci = e % CI;
+        float sum[CO];
+#pragma unroll
+        for (int c = 0; c < CO; ++c) sum[c] = 0.f;
+        for (int bid = blockIdx.x; bid < ntile; bid += gridDim.x) {
+            const int x0 = (bid % ntx) * kTX, y0 = (bid / ntx) % nty * kTY, z0 = (bid / (ntx * nty)) % ntz * kTZ;
+            const int64_t base = (int64_t)(bid / (ntx * nty * ntz)) * vol;
+#pragma unroll 1
+            for (int p = 0; p < kTZ * kTY * kTX; ++p) {
+                // x at (zx, yx, x), d at (z, y, xd): the pairs the matrix form has
+                const int x = x0 + p % kTX, y = y0 + p / kTX % kTY, z = z0 + p / (kTX * kTY);
+                const int xd = x + 1 - t % 3, yx = y + t / 3 % 3 - 1, zx = z + t / 9 - 1;
+                if (x >= X || y >= Y || z >= Z || xd < 0 || xd >= X || yx < 0 || yx >= Y || zx < 0 || zx >= Z) continue;
+                const float xv = xin[(base + (int64_t)(zx * Y + yx) * X + x) * CI + ci];
+                const float *dv = d + (base + (int64_t)(z * Y + y) * X + xd) * CO;
+#pragma unroll
+                for (int c = 0; c < CO; ++c) sum[c] = fmaf(xv, dv[c], sum[c]);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < CO; ++c) out[(c * CI + ci) * 27 + t] = sum[c];
+    }
 }
 
 // Work-groups of the weight gradients for n boxes of Z x Y x X points.

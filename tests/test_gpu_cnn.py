@@ -70,6 +70,58 @@ def test_forward_at_column_edges(n, dims, periodic):
         assert np.max(np.abs(f[i] - want)) <= 1e-5 * np.max(np.abs(want))
 
 
+# rows of a pair on both sides of the point, in the first, the last and an inner
+# row of a column, and across the periodic faces
+@pytest.mark.parametrize("periodic", [False, True])
+@pytest.mark.parametrize("at", [(2, 0, 3), (3, 7, 0), (0, 8, 16), (6, 15, 9), (4, 17, 5)])
+def test_nonfinite_inputs_reach_three_points(at, periodic):
+    dims, p = (7, 18, 17), _params(17)
+    net = rsd.Cnn(2, int(np.prod(dims)))
+    net.set_params(p)
+    u = np.random.default_rng(18).normal(size=(2,) + dims).astype(np.float32)
+    pad = "wrap" if periodic else "zero"
+    far = np.ones(dims, bool)
+    near = [np.arange(c - 3, c + 4) for c in at]
+    near = [a % d if periodic else a[(a >= 0) & (a < d)] for a, d in zip(near, dims)]
+    far[np.ix_(*near)] = False
+    u[(1,) + at] = 0.0
+    want, _ = ocnn.forward(p, u[1].astype(np.float64), np.ones(dims), pad)
+    u[(1,) + at] = np.nan
+    f = net.forward(_dev(u), periodic=periodic).cpu().numpy()
+    # three layers of reach one; the split products of layer 2 as above
+    assert np.all(np.isnan(f[1][~far])) and np.all(np.isfinite(f[0]))
+    assert np.max(np.abs(f[1] - want)[far], initial=0.0) <= 1e-5 * np.max(np.abs(want))
+    # layer 1 takes an infinity to +-1, as it does any large number
+    u[(1,) + at] = 1e9
+    want, _ = ocnn.forward(p, u[1].astype(np.float64), np.ones(dims), pad)
+    u[(1,) + at] = np.inf
+    f = net.forward(_dev(u), periodic=periodic).cpu().numpy()
+    assert np.max(np.abs(f[1] - want)) <= 1e-5 * np.max(np.abs(want))
+
+
+def test_nonfinite_input_and_the_gradients_it_is_no_part_of():
+    dims, p = (6, 9, 17), _params(19)
+    net = rsd.Cnn(2, int(np.prod(dims)))
+    net.set_params(p)
+    rng = np.random.default_rng(20)
+    u = rng.normal(size=(2,) + dims).astype(np.float32)
+    t = rng.normal(size=(2,) + dims).astype(np.float32)
+    sig = np.array([-0.7, -2.0])
+    # at the first point of a box layer 1's delta is zero and only taps up to the
+    # centre meet the input: 0 x Inf is NaN there, the others do not have it
+    u[1, 0, 0, 0] = 1e9
+    _, want, wdu = ocnn.loss_and_grad(p, u.astype(np.float64), t.astype(np.float64), sig, 0.25, 1)
+    u[1, 0, 0, 0] = np.inf
+    _, got, du = net.loss_grad(_dev(u), _dev(t), _dev(sig), 0.25, 1, want_du=True)
+    past = np.zeros((3, 3, 3), bool)
+    past[2], past[:, 2], past[:, :, 2] = True, True, True
+    past = np.tile(past.ravel(), 8)
+    assert np.all(np.isnan(got[:216][~past]))
+    assert _rel(got[:216][past], want[:216][past]) <= 1e-4
+    assert _rel(got[216:1944], want[216:1944]) <= 1e-4 and _rel(got[1944:2160], want[1944:2160]) <= 1e-4
+    assert _rel(du.cpu().numpy(), wdu) <= 1e-4
+
+
 def test_loss_gradient_and_adam_match_oracle():
     p = _params(3)
     net = rsd.Cnn(4, 4096)
