@@ -2082,12 +2082,14 @@ rs_status gram_core(const GramScratch &w, bool make_lists, const void *X, const 
     }
     // small chunks: several work-groups per compute unit (each owns all
     // output blocks of its chunk), bounded by the partial-sum workspace; on
-    // small grids about 256 of them in whole 32-point stages, 128 above 128
-    // states, whose partials are large (4096 points, 256 FP64 states: 374 ->
-    // 70 us; 113k points: 512-point chunks 1095, 416-point ones 1225)
-    const int64_t want = N <= 128 ? 256 : 128;
+    // small grids about 256 of them in whole 32-point stages.  Above 128 states,
+    // whose partials are large and whose blocks take up to four work-groups a
+    // chunk, at most 128: one more than the chip holds at once runs alone at the
+    // end (256 FP64 states, 64000 points: 125 chunks 525 us, 134 chunks 835; 4096
+    // points, 64 chunks 69, the 8 of 512 points 279)
     int64_t CP = bf ? 1024 : 512;
-    if (N <= 128 || np <= 65536) CP = std::max<int64_t>(64, std::min<int64_t>(CP, (np + want - 1) / want / 32 * 32));
+    if (N <= 128) CP = std::max<int64_t>(64, std::min<int64_t>(CP, (np + 255) / 256 / 32 * 32));
+    else if (np <= 65536) CP = std::max<int64_t>(64, std::min<int64_t>(CP, ((np + 127) / 128 + 31) / 32 * 32));
     while ((np + CP - 1) / CP > w.max_chunks) CP *= 2;
     if (CP > (1 << 30)) return fail(RS_EINVAL, "gram: grid too large for the partial-sum workspace");
     const int nchunks = (int)((np + CP - 1) / CP);
