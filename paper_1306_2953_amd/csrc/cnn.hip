@@ -93,8 +93,10 @@ __device__ __forceinline__ float tanh_f(float x) {
 // A work-group owns a column of 16 x 16 x cz points and runs down z: four
 // planes with their border in LDS, channels last, three in use while the
 // fourth is filled from registers, one barrier a plane; its four waves take two
-// row pairs each.  The weights stay in registers.  Consecutive work-groups of
-// an XCD take neighbouring columns, whose borders its L2 then holds.
+// row pairs each, one where only 8 rows or fewer are left (15625 boxes of 4^3, all
+// layers: 570 us with that, 779 without).  The weights stay in registers.
+// Consecutive work-groups of an XCD take neighbouring columns, whose borders its
+// L2 then holds.
 //   No single unit bounds it: for 32 boxes of 96^3 (28 M points) layer 2
 // takes 750 us, of which the matrix instructions are 250, the vector units (half
 // of it tanh) 330, and the 0.9 GB written 190 on top of both; blocks of 16 x 8 x
@@ -148,51 +150,11 @@ __device__ __forceinline__ int xcd_column(int bid, int n) {
     return c < n ? c : -1;
 }
 
-template <int CI, int MODE, bool SPLIT>
-__global__ void __launch_bounds__(256)
-conv8_kernel(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ W,
-             const float *__restrict__ act, const int32_t *__restrict__ boxpt, int ncol, int Z, int Y, int X,
-             int wrap, int ntx, int nty, int ntz, int cz) {
-    constexpr int NA = SPLIT ? 1 : CI == 8 ? 36 : 9;
-    constexpr int PIECES = kPP * (CI == 8 ? 2 : 1), NL = (PIECES + 255) / 256;
-    __shared__ __attribute__((aligned(16))) float ring[4][kPP * CI];   // SPLIT: kPP * 8 hi, then kPP * 8 lo
-    const int col = xcd_column(blockIdx.x, ncol);
-    if (col < 0) return;
-    const int tx = col % ntx, ty = (col / ntx) % nty, tz = (col / (ntx * nty)) % ntz;
-    const int64_t vol = (int64_t)Z * Y * X, img = col / (ntx * nty * ntz);
-    const int x0 = tx * kCX, y0 = ty * kCY, z0 = tz * cz, z1 = min(z0 + cz, Z);
-    const float *base = in + img * vol * CI;
-    const int tid = threadIdx.x, lane = tid & 63, g = lane / 16, px = lane % 16;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int off[NL];
-    const unsigned valid = plane_offsets<CI, 256, NL>(tid, x0, y0, Y, X, wrap, off);
-    auto store = [&](int z, const f4 *loaded) {
-        float *dst = ring[z & 3];
-#pragma unroll
-        for (int k = 0; k < NL; ++k) {
-            const int e = tid + 256 * k;
-            if (e >= PIECES) break;
-            const f4 v = plane_piece(loaded[k], valid, k, z, Z, wrap);
-            if constexpr (SPLIT) {
-                bf4 h, l;
-                split(v, h, l);
-                *(bf4 *)((__bf16 *)dst + 4 * e) = h;
-                *(bf4 *)((__bf16 *)dst + kPP * 8 + 4 * e) = l;
-            } else if constexpr (CI == 8) {
-                *(f4 *)(dst + 4 * e) = v;
-            } else {
-                dst[e] = v[0];
-            }
-        }
-    };
-    f4 v[NL], v1[NL], v2[NL];
-    load_plane<CI, NL>(base, z0 - 1, Z, Y * X, wrap, off, v);
-    load_plane<CI, NL>(base, z0, Z, Y * X, wrap, off, v1);
-    load_plane<CI, NL>(base, z0 + 1, Z, Y * X, wrap, off, v2);
-    // A operands of row px: channel px % 8 of output row px / 8
+// A operands of lane row px = l % 16: channel px % 8 of output row px / 8.
+template <int CI, bool SPLIT> struct Weights {
     bf8 ah[9], al[9];
-    f2 aw[NA];
-    {
+    f2 aw[SPLIT ? 1 : CI == 8 ? 36 : 9];
+    __device__ __forceinline__ void load(const float *__restrict__ W, int px, int g) {
         const int co = px % 8, j = px / 8;
         if constexpr (SPLIT) {
             const int dy = g - j;
@@ -228,26 +190,65 @@ conv8_kernel(const float *__restrict__ in, float *__restrict__ out, const float 
                 aw[c][0] = dy >= 0 && dy < 3 ? W[co * 27 + 9 * (c / 3) + 3 * dy + c % 3] : 0.f;
         }
     }
-    // this lane's point of the wave's two row pairs: in the box or not, and
-    // where its mask and activations are in a plane
-    bool ok[2];
-    int64_t qp[2];
+};
+
+// NH: row pairs a wave takes (1: a column of 16 x 8, for the rows left at the
+// end of a box); img: the box's first point.  LOAD: the weights are loaded here,
+// behind the first planes.
+template <int CI, int MODE, bool SPLIT, int NH, bool LOAD>
+__device__ __forceinline__ void
+conv8_column(const float *__restrict__ base, float *__restrict__ out, const float *__restrict__ W,
+             const float *__restrict__ act, const int32_t *__restrict__ boxpt, float (&ring)[4][kPP * CI], int64_t img,
+             int x0, int y0, int z0, int z1, int Z, int Y, int X, int wrap, Weights<CI, SPLIT> &w) {
+    constexpr int PIECES = kPX * (8 * NH + 2) * (CI == 8 ? 2 : 1), NL = (PIECES + 255) / 256;
+    const int tid = threadIdx.x, lane = tid & 63, g = lane / 16, px = lane % 16;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int off[NL];
+    const unsigned valid = plane_offsets<CI, 256, NL>(tid, x0, y0, Y, X, wrap, off);
+    auto store = [&](int z, const f4 *loaded) {
+        float *dst = ring[z & 3];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+        for (int k = 0; k < NL; ++k) {
+            const int e = tid + 256 * k;
+            if (e >= PIECES) break;
+            const f4 v = plane_piece(loaded[k], valid, k, z, Z, wrap);
+            if constexpr (SPLIT) {
+                bf4 h, l;
+                split(v, h, l);
+                *(bf4 *)((__bf16 *)dst + 4 * e) = h;
+                *(bf4 *)((__bf16 *)dst + kPP * 8 + 4 * e) = l;
+            } else if constexpr (CI == 8) {
+                *(f4 *)(dst + 4 * e) = v;
+            } else {
+                dst[e] = v[0];
+            }
+        }
+    };
+    f4 v[NL], v1[NL], v2[NL];
+    load_plane<CI, NL>(base, z0 - 1, Z, Y * X, wrap, off, v);
+    load_plane<CI, NL>(base, z0, Z, Y * X, wrap, off, v1);
+    load_plane<CI, NL>(base, z0 + 1, Z, Y * X, wrap, off, v2);
+    if constexpr (LOAD) w.load(W, px, g);
+    // this lane's point of the wave's row pairs: in the box or not, and where its
+    // mask and activations are in a plane
+    bool ok[NH];
+    int64_t qp[NH];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
         const int x = x0 + px, y = y0 + 2 * (wave + 4 * h) + g / 2;
         ok[h] = x < X && y < Y;
         qp[h] = (int64_t)min(y, Y - 1) * X + min(x, X - 1);
     }
-    int m[2] = {0, 0};
-    f4 ac[2];
+    int m[NH] = {};
+    f4 ac[NH];
     auto load_marks = [&](int z) {
         const int64_t zp = (int64_t)z * Y * X;
         if (boxpt != nullptr)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) m[h] = boxpt[zp + qp[h]];
+            for (int h = 0; h < NH; ++h) m[h] = boxpt[zp + qp[h]];
         if (MODE == 2)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) ac[h] = *(const f4 *)(act + (img * vol + zp + qp[h]) * 8 + 4 * (g & 1));
+            for (int h = 0; h < NH; ++h) ac[h] = *(const f4 *)(act + (img + zp + qp[h]) * 8 + 4 * (g & 1));
     };
     auto activate = [](f4 d, f4 a, bool inside) {
         f4 r;
@@ -267,9 +268,13 @@ conv8_kernel(const float *__restrict__ in, float *__restrict__ out, const float 
         // loads of the next plane, its mask and activations: nothing below
         // waits for them before the plane is stored to LDS
         const bool more = z + 1 < z1;
-        const bool in0 = ok[0] && m[0] >= 0, in1 = ok[1] && m[1] >= 0;
-        const f4 ac0 = ac[0], ac1 = ac[1];
-        f4 res[2];
+        bool in[NH];
+        f4 acn[NH], res[NH];
+#pragma unroll
+        for (int h = 0; h < NH; ++h) {
+            in[h] = ok[h] && m[h] >= 0;
+            acn[h] = ac[h];
+        }
         if (more) {
             load_plane<CI, NL>(base, z + 2, Z, Y * X, wrap, off, v);
             load_marks(z + 1);
@@ -279,7 +284,7 @@ conv8_kernel(const float *__restrict__ in, float *__restrict__ out, const float 
         // both row pairs of the wave in one block of code: the second's matrix
         // instructions run beside the first's tanh
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < NH; ++h) {
             const int rb = 2 * (wave + 4 * h) * kPX + px;
             f4 d;
             if constexpr (SPLIT) {
@@ -290,10 +295,10 @@ conv8_kernel(const float *__restrict__ in, float *__restrict__ out, const float 
                 for (int c = 0; c < 9; ++c) {
                     const __bf16 *p = (const __bf16 *)pl[c / 3] + (rb + g * kPX + c % 3) * 8;
                     const bf8 bh = *(const bf8 *)p, bl = *(const bf8 *)(p + kPP * 8);
-                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[c], bl, acc[0], 0, 0, 0);
-                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[c], bh, acc[1], 0, 0, 0);
-                    acc[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[c], bl, acc[2], 0, 0, 0);
-                    acc[3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[c], bh, acc[3], 0, 0, 0);
+                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.al[c], bl, acc[0], 0, 0, 0);
+                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.al[c], bh, acc[1], 0, 0, 0);
+                    acc[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.ah[c], bl, acc[2], 0, 0, 0);
+                    acc[3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.ah[c], bh, acc[3], 0, 0, 0);
                 }
                 d = ((acc[0] + acc[1]) + acc[2]) + acc[3];   // the small products first
             } else if constexpr (CI == 8) {
@@ -301,8 +306,8 @@ conv8_kernel(const float *__restrict__ in, float *__restrict__ out, const float 
 #pragma unroll
                 for (int t = 0; t < 36; ++t) {
                     const f2 b = *(const f2 *)(pl[t / 12] + (rb + (t / 3) % 4 * kPX + t % 3) * 8 + 2 * g);
-                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(aw[t][0], b[0], acc[0], 0, 0, 0);
-                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(aw[t][1], b[1], acc[1], 0, 0, 0);
+                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.aw[t][0], b[0], acc[0], 0, 0, 0);
+                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.aw[t][1], b[1], acc[1], 0, 0, 0);
                 }
                 d = acc[0] + acc[1];
             } else {
@@ -311,18 +316,19 @@ conv8_kernel(const float *__restrict__ in, float *__restrict__ out, const float 
                 for (int k = 0; k < 3; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int c = 0; c < 9; ++c)
-                    acc[c / 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(aw[c][0], pl[c / 3][rb + g * kPX + c % 3],
+                    acc[c / 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.aw[c][0], pl[c / 3][rb + g * kPX + c % 3],
                                                                       acc[c / 3], 0, 0, 0);
                 d = (acc[0] + acc[1]) + acc[2];
             }
-            res[h] = activate(d, h ? ac1 : ac0, h ? in1 : in0);
+            res[h] = activate(d, acn[h], in[h]);
         }
         // the pair's other row brings 0 x Inf or 0 x NaN into a sum that does not
         // have that input: a lane with a NaN forms its sums again, own taps only
-        const f4 both = res[0] + res[1];
-        if (__builtin_isnan((both[0] + both[1]) + (both[2] + both[3]))) {
+        f4 sum = res[0];
+        if constexpr (NH == 2) sum += res[1];
+        if (__builtin_isnan((sum[0] + sum[1]) + (sum[2] + sum[3]))) {
 #pragma unroll 1
-            for (int h = 0; h < 2; ++h) {
+            for (int h = 0; h < NH; ++h) {
                 const int e0 = (2 * (wave + 4 * h) + g / 2) * kPX + px;
                 f4 d = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
@@ -342,19 +348,47 @@ conv8_kernel(const float *__restrict__ in, float *__restrict__ out, const float 
                         for (int k = 0; k < 4; ++k) d[k] = fmaf(W[((4 * (g & 1) + k) * CI + ci) * 27 + t], x, d[k]);
                     }
                 }
-                const f4 r = activate(d, h ? ac1 : ac0, h ? in1 : in0);
-                if (h) res[1] = r;
-                else res[0] = r;
+#pragma unroll
+                for (int i = 0; i < NH; ++i)
+                    if (h == i) res[i] = activate(d, acn[i], in[i]);
             }
         }
         // to LDS first: waiting for the loads then does not wait for the results' stores
         if (more) store(z + 2, v);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < NH; ++h)
             if (ok[h])
-                __builtin_nontemporal_store(res[h], (f4 *)(out + (img * vol + (int64_t)z * Y * X + qp[h]) * 8 + 4 * (g & 1)));
+                __builtin_nontemporal_store(res[h], (f4 *)(out + (img + (int64_t)z * Y * X + qp[h]) * 8 + 4 * (g & 1)));
         __syncthreads();
+    }
+}
+
+// LOOP: the work-group takes further columns where there are more than
+// work-groups, with the weights kept: they take as long to load and split as
+// four planes.  It has to keep to 168 registers (the two column forms' weights
+// came to 171): three waves per SIMD.
+template <int CI, int MODE, bool SPLIT, bool LOOP>
+__global__ void __launch_bounds__(256, LOOP ? 3 : 1)
+conv8_kernel(const float *__restrict__ in, float *__restrict__ out, const float *__restrict__ W,
+             const float *__restrict__ act, const int32_t *__restrict__ boxpt, int ncol, int Z, int Y, int X,
+             int wrap, int ntx, int nty, int ntz, int cz) {
+    __shared__ __attribute__((aligned(16))) float ring[4][kPP * CI];   // SPLIT: kPP * 8 hi, then kPP * 8 lo
+    Weights<CI, SPLIT> w;
+    if constexpr (LOOP) w.load(W, threadIdx.x % 16, (threadIdx.x & 63) / 16);
+    for (int bid = blockIdx.x; bid < (ncol + 7) / 8 * 8; bid += gridDim.x) {
+        const int col = xcd_column(bid, ncol);
+        if (col < 0) return;
+        const int tx = col % ntx, ty = (col / ntx) % nty, tz = (col / (ntx * nty)) % ntz;
+        const int64_t img = (int64_t)(col / (ntx * nty * ntz)) * Z * Y * X;
+        const int x0 = tx * kCX, y0 = ty * kCY, z0 = tz * cz, z1 = min(z0 + cz, Z);
+        const float *base = in + img * CI;
+        // half of a column's rows are left out where they lie outside the box
+        if (y0 + 8 < Y)
+            conv8_column<CI, MODE, SPLIT, 2, !LOOP>(base, out, W, act, boxpt, ring, img, x0, y0, z0, z1, Z, Y, X, wrap, w);
+        else
+            conv8_column<CI, MODE, SPLIT, 1, !LOOP>(base, out, W, act, boxpt, ring, img, x0, y0, z0, z1, Z, Y, X, wrap, w);
+        if (!LOOP) return;
     }
 }
 
@@ -362,27 +396,41 @@ conv8_kernel(const float *__restrict__ in, float *__restrict__ out, const float 
 // column cost a sixteenth more border; 16 or 8 where that would leave fewer than
 // 2048 work-groups, about two rounds of what is resident (32 boxes of 52^3: 363
 // us against 404); below that the border weighs more, and 1024 must do (16 boxes
-// of 36^3: 123 against 142).  At least 2: single planes read three for one and
-// gain nothing (layer 2 for 32 boxes of 16^3: 14 us either way).
+// of 36^3: 123 against 142), 512 for columns of 4 (740 boxes of 3^3: all layers 33
+// us against 41, 128 of 16^3 47 against 50).  At least 2: single planes read three
+// for one and gain nothing (layer 2 for 32 boxes of 16^3: 14 us either way).
 struct Columns {
     int ntx, nty, ntz, cz, n;
     Columns(int nbox, int Z, int Y, int X) : ntx((X + kCX - 1) / kCX), nty((Y + kCY - 1) / kCY), cz(32) {
         auto count = [&] { return (int64_t)ntx * nty * ((Z + cz - 1) / cz) * nbox; };
         while (cz > 8 && count() < 2048) cz /= 2;
-        while (cz > 2 && count() < 1024) cz /= 2;
+        while (cz > 4 && count() < 1024) cz /= 2;
+        while (cz > 2 && count() < 512) cz /= 2;
         ntz = (Z + cz - 1) / cz;
         n = ntx * nty * ntz * nbox;
     }
     dim3 grid() const { return dim3((unsigned)((n + 7) / 8 * 8)); }
 };
 
+constexpr unsigned kLoopGroups = 768;   // three a compute unit
+
 // Launches conv8_kernel over n boxes of Z x Y x X points.
 template <int CI, int MODE, bool SPLIT>
 void conv8(const float *in, float *out, const float *W, const float *act, const int32_t *boxpt, int n, int Z, int Y,
            int X, int wrap, hipStream_t st) {
     const Columns c(n, Z, Y, X);
-    hipLaunchKernelGGL((conv8_kernel<CI, MODE, SPLIT>), c.grid(), dim3(256), 0, st, in, out, W, act, boxpt, c.n, Z, Y,
-                       X, wrap, c.ntx, c.nty, c.ntz, c.cz);
+    dim3 grid = c.grid();
+    if constexpr (SPLIT) {
+        // shallow columns: as many work-groups as are resident (15625 boxes of
+        // 4^3, all layers: 402 us, one column a work-group 546; 390 of 8^3 46, 50)
+        if (std::min(c.cz, Z) < 8 && grid.x > kLoopGroups) {
+            hipLaunchKernelGGL((conv8_kernel<CI, MODE, SPLIT, true>), dim3(kLoopGroups), dim3(256), 0, st, in, out, W,
+                               act, boxpt, c.n, Z, Y, X, wrap, c.ntx, c.nty, c.ntz, c.cz);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((conv8_kernel<CI, MODE, SPLIT, false>), grid, dim3(256), 0, st, in, out, W, act, boxpt, c.n, Z,
+                       Y, X, wrap, c.ntx, c.nty, c.ntz, c.cz);
 }
 
 // Layer 3, 8 -> 1 channels: out = mask * conv(in).  The vector units' 216
@@ -427,6 +475,8 @@ conv1_kernel(const float *__restrict__ in, float *__restrict__ out, const float 
         ok[j] = x < X && y < Y;
         qp[j] = (int64_t)min(y, Y - 1) * X + min(x, X - 1);
     }
+    // a wave without rows in the box only stages
+    const bool live = y0 + 8 * __builtin_amdgcn_readfirstlane(tid >> 6) < Y;
     // sums of the outputs one plane back, of this plane and one ahead
     float a0[2] = {0.f, 0.f}, a1[2] = {0.f, 0.f}, a2[2] = {0.f, 0.f};
     load_plane<8, NL>(base, z0 - 1, Z, Y * X, wrap, off, v);
@@ -439,35 +489,37 @@ conv1_kernel(const float *__restrict__ in, float *__restrict__ out, const float 
             for (int j = 0; j < 2; ++j) m[j] = boxpt[(int64_t)(z - 1) * Y * X + qp[j]];
         if (z < z1) load_plane<8, NL>(base, z + 1, Z, Y * X, wrap, off, v);
         __builtin_amdgcn_sched_barrier(0);
-        const f4 *row = buf[b] + ly * kPX + lx;
-        f4 r[2][6];
+        if (live) {
+            const f4 *row = buf[b] + ly * kPX + lx;
+            f4 r[2][6];
 #pragma unroll
-        for (int k = 0; k < 6; ++k) r[0][k] = row[(k & 1) * kPP + k / 2];
+            for (int k = 0; k < 6; ++k) r[0][k] = row[(k & 1) * kPP + k / 2];
 #pragma unroll
-        for (int dyp = 0; dyp < 4; ++dyp) {
-            if (dyp < 3)
+            for (int dyp = 0; dyp < 4; ++dyp) {
+                if (dyp < 3)
 #pragma unroll
-                for (int k = 0; k < 6; ++k) r[(dyp + 1) & 1][k] = row[(k & 1) * kPP + (dyp + 1) * kPX + k / 2];
-            __builtin_amdgcn_sched_barrier(0);
+                    for (int k = 0; k < 6; ++k) r[(dyp + 1) & 1][k] = row[(k & 1) * kPP + (dyp + 1) * kPX + k / 2];
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int dy = dyp - j;
-                if (dy < 0 || dy > 2) continue;
-                // the weights are loaded here, 72 at a time: all 216, kept
-                // over the planes, would not fit the scalar registers
-                int wo = 3 * dy * 8;
-                asm volatile("" : "+s"(wo));
+                for (int j = 0; j < 2; ++j) {
+                    const int dy = dyp - j;
+                    if (dy < 0 || dy > 2) continue;
+                    // the weights are loaded here, 72 at a time: all 216, kept
+                    // over the planes, would not fit the scalar registers
+                    int wo = 3 * dy * 8;
+                    asm volatile("" : "+s"(wo));
 #pragma unroll
-                for (int dx = 0; dx < 3; ++dx)
+                    for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) {
-                        const float u = r[dyp & 1][2 * dx + c / 4][c % 4];
-                        const float *w = wt + wo + dx * 8 + c;
-                        a0[j] = fmaf(w[2 * 72], u, a0[j]);
-                        a1[j] = fmaf(w[72], u, a1[j]);
-                        a2[j] = fmaf(w[0], u, a2[j]);
-                    }
-                asm volatile("" : "+v"(a0[j]), "+v"(a1[j]), "+v"(a2[j]));
+                        for (int c = 0; c < 8; ++c) {
+                            const float u = r[dyp & 1][2 * dx + c / 4][c % 4];
+                            const float *w = wt + wo + dx * 8 + c;
+                            a0[j] = fmaf(w[2 * 72], u, a0[j]);
+                            a1[j] = fmaf(w[72], u, a1[j]);
+                            a2[j] = fmaf(w[0], u, a2[j]);
+                        }
+                    asm volatile("" : "+v"(a0[j]), "+v"(a1[j]), "+v"(a2[j]));
+                }
             }
         }
         // to LDS first: waiting for the loads then does not wait for the results' stores
@@ -549,13 +601,14 @@ conv1_block_kernel(const float *__restrict__ in, float *__restrict__ out, const 
     }
 }
 
-// Layer 3 over n boxes of Z x Y x X points.  Columns cut down to a few planes
-// stage most of them twice and run few waves: 32 boxes of 16^3 in columns of 2
-// take 12.6 us, in blocks 7.6; 32 boxes of 96^3 in columns of 32 375, in blocks 560.
+// Layer 3 over n boxes of Z x Y x X points.  Columns of a few planes stage most
+// of them twice, or two planes more than they write, and run few waves: 32 boxes
+// of 16^3 in columns of 2 take 12.6 us, in blocks 7.6; 15625 of 4^3 214 and 141;
+// 32 boxes of 96^3 in columns of 32 375, in blocks 560.
 void conv1(const float *in, float *out, const float *wt, const int32_t *boxpt, int n, int Z, int Y, int X, int wrap,
            hipStream_t st) {
     const Columns c(n, Z, Y, X);
-    if (c.cz >= 8) {
+    if (std::min(c.cz, Z) >= 8) {
         hipLaunchKernelGGL(conv1_kernel, c.grid(), dim3(128), 0, st, in, out, wt, boxpt, c.n, Z, Y, X, wrap, c.ntx,
                            c.nty, c.ntz, c.cz);
         return;

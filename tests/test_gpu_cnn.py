@@ -70,6 +70,31 @@ def test_forward_at_column_edges(n, dims, periodic):
         assert np.max(np.abs(f[i] - want)) <= 1e-5 * np.max(np.abs(want))
 
 
+# columns of 8 and of 16 rows: both sides of the line, alone and after whole ones,
+# shallow and deep, and more shallow ones than work-groups
+@pytest.mark.parametrize("n,dims,periodic", [(2, (4, 8, 17), True), (2, (5, 9, 5), False), (1, (4, 24, 16), False),
+                                             (1, (4, 25, 33), True), (1100, (9, 8, 4), False), (1100, (9, 9, 4), True),
+                                             (1601, (5, 5, 4), True), (801, (4, 20, 4), False)])
+def test_network_at_half_columns(n, dims, periodic):
+    p = _params(21)
+    net = rsd.Cnn(n, int(np.prod(dims)))
+    net.set_params(p)
+    rng = np.random.default_rng(22)
+    u = rng.normal(size=(n,) + dims).astype(np.float32)
+    f = net.forward(_dev(u), periodic=periodic).cpu().numpy()
+    for i in sorted({0, n // 2, n - 1}):
+        want, _ = ocnn.forward(p, u[i].astype(np.float64), np.ones(dims), "wrap" if periodic else "zero")
+        # as above: layer 2's split products carry about 2^-16 per term
+        assert np.max(np.abs(f[i] - want)) <= 1e-5 * np.max(np.abs(want))
+    t = rng.normal(size=(n,) + dims).astype(np.float32)
+    sig = -rng.uniform(0.5, 5.0, n)
+    _, grad, du = net.loss_grad(_dev(u), _dev(t), _dev(sig), 0.25, 0, want_du=True)
+    _, wg, wdu = ocnn.loss_and_grad(p, u.astype(np.float64), t.astype(np.float64), sig, 0.25, 0)
+    for a, b in ((0, 216), (216, 1944), (1944, 2160), (2160, 2162)):
+        assert _rel(grad[a:b], wg[a:b]) <= 1e-4, (a, b)
+    assert _rel(du.cpu().numpy(), wdu) <= 1e-4
+
+
 # rows of a pair on both sides of the point, in the first, the last and an inner
 # row of a column, and across the periodic faces
 @pytest.mark.parametrize("periodic", [False, True])
