@@ -1468,17 +1468,20 @@ rs_status cnn_precondition(rs_cnn *c, const rs_grid *g, const void *r, const dou
     const int cb = c->max_batch / B;          // blocks per chunk
     if (cb < 1) return fail(RS_EINVAL, "cnn precondition: max_batch of the network handle is below B");
     const int64_t np = g->np;
-    const int nchunks = chunk_count(np, B, nblk);
+    // one chunk size for any number of blocks: a solver that leaves out frozen
+    // blocks calls with parts of them, which then neither round differently nor
+    // need more scratch than the whole
+    const int nchunks = chunk_count(np, B, 1);
     if ((s = ensure(c->ss, (size_t)N * sizeof(double)))) return s;
     if ((s = ensure(c->inv_s, (size_t)N * sizeof(double)))) return s;
     if ((s = ensure(c->outs, (size_t)N * sizeof(double)))) return s;
     if ((s = ensure(c->partial, (size_t)nchunks * N * sizeof(double)))) return s;
     if (dtype == RS_F64)
         s = colreduce<1>(OpSumSq<double>{(const double *)r}, np, B, nblk, 1.0, c->partial.as<double>(),
-                         c->ss.as<double>(), st);
+                         c->ss.as<double>(), st, nullptr, 0, 1);
     else
         s = colreduce<1>(OpSumSq<float>{(const float *)r}, np, B, nblk, 1.0, c->partial.as<double>(),
-                         c->ss.as<double>(), st);
+                         c->ss.as<double>(), st, nullptr, 0, 1);
     if (s) return s;
     hipLaunchKernelGGL(prescale_kernel, dim3((N + 255) / 256), dim3(256), 0, st, c->ss.as<double>(), sigma,
                        c->params.as<float>(), g->h, np, N, c->inv_s.as<double>(), c->outs.as<double>());
@@ -1551,7 +1554,7 @@ extern "C" rs_status rs_cnn_crops(rs_cnn *c, const rs_grid *g, const void *r, co
     }
     hipStream_t st = (hipStream_t)stream;
     const int64_t np = g->np;
-    const int nchunks = chunk_count(np, B, nblk);
+    const int nchunks = chunk_count(np, B, 1);   // as cnn_precondition
     if ((s = ensure(c->ss, (size_t)N * sizeof(double)))) return s;
     if ((s = ensure(c->inv_s, (size_t)N * sizeof(double)))) return s;
     if ((s = ensure(c->partial, (size_t)nchunks * N * sizeof(double)))) return s;
@@ -1559,10 +1562,10 @@ extern "C" rs_status rs_cnn_crops(rs_cnn *c, const rs_grid *g, const void *r, co
     if ((s = ddesc.upload(std::vector<int32_t>(desc, desc + 4 * (size_t)ncrops)))) return s;
     if (dtype == RS_F64)
         s = colreduce<1>(OpSumSq<double>{(const double *)r}, np, B, nblk, 1.0, c->partial.as<double>(),
-                         c->ss.as<double>(), st);
+                         c->ss.as<double>(), st, nullptr, 0, 1);
     else
         s = colreduce<1>(OpSumSq<float>{(const float *)r}, np, B, nblk, 1.0, c->partial.as<double>(),
-                         c->ss.as<double>(), st);
+                         c->ss.as<double>(), st, nullptr, 0, 1);
     if (s) return s;
     hipLaunchKernelGGL(invs_kernel, dim3((N + 255) / 256), dim3(256), 0, st, c->ss.as<double>(), np, N,
                        c->inv_s.as<double>());

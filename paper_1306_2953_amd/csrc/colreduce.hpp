@@ -121,25 +121,30 @@ colreduce_apply(const double *__restrict__ partial, int nchunks, int N, double d
 }
 
 // Partial sums of all columns, or with bmap (device, nmap entries) of the
-// listed blocks.
+// listed blocks.  The chunks, and with them a sum's rounding, are those of `of`
+// blocks.
 template <int K, typename Op>
 rs_status colreduce_partial(const Op &op, int64_t np, int B, int nblk, double *partial, hipStream_t st,
-                            const int *bmap, int nmap) {
-    const int N = nblk * B, nchunks = chunk_count(np, B, nblk);
+                            const int *bmap, int nmap, int of) {
+    const int N = nblk * B, nchunks = chunk_count(np, B, of);
     hipLaunchKernelGGL((colreduce_kernel<K, Op>), dim3(nchunks, bmap ? nmap : nblk), dim3(256), 0, st, op, np, B,
-                       chunk_points(np, B, nblk), nchunks, N, partial, bmap);
+                       chunk_points(np, B, of), nchunks, N, partial, bmap);
     RS_HIP(hipGetLastError());
     return RS_OK;
 }
 
 // Sums for all nblk * B columns; with bmap (device, nmap entries) only the
 // listed blocks are reduced this time and the other columns' outputs repeat
-// whatever their partial sums last held.
+// whatever their partial sums last held.  A caller that works through parts of
+// a problem gives one `of` for all of them (0: nblk): a column's sum is then the
+// same in any part, and nblk * B * chunk_count(np, B, of) partial sums grow with
+// nblk.
 template <int K, typename Op>
 rs_status colreduce(const Op &op, int64_t np, int B, int nblk, double dv, double *partial, double *out,
-                    hipStream_t st, const int *bmap = nullptr, int nmap = 0) {
-    const int N = nblk * B, nchunks = chunk_count(np, B, nblk);
-    rs_status e = colreduce_partial<K>(op, np, B, nblk, partial, st, bmap, nmap);
+                    hipStream_t st, const int *bmap = nullptr, int nmap = 0, int of = 0) {
+    if (of == 0) of = nblk;
+    const int N = nblk * B, nchunks = chunk_count(np, B, of);
+    rs_status e = colreduce_partial<K>(op, np, B, nblk, partial, st, bmap, nmap, of);
     if (e) return e;
     hipLaunchKernelGGL(colreduce_final, dim3((K * N + 3) / 4), dim3(256), 0, st, partial, K, nchunks, N, dv,
                        out);
@@ -153,7 +158,7 @@ rs_status colreduce_then(const Op &op, int64_t np, int B, int nblk, double dv, d
                          hipStream_t st, const int *bmap = nullptr, int nmap = 0) {
     static_assert(K <= 32, "one row of threads per sum");
     const int N = nblk * B, nchunks = chunk_count(np, B, nblk);
-    rs_status e = colreduce_partial<K>(op, np, B, nblk, partial, st, bmap, nmap);
+    rs_status e = colreduce_partial<K>(op, np, B, nblk, partial, st, bmap, nmap, nblk);
     if (e) return e;
     hipLaunchKernelGGL((colreduce_apply<K, F>), dim3((N + 7) / 8), dim3(256), 0, st, partial, nchunks, N, dv, f);
     RS_HIP(hipGetLastError());

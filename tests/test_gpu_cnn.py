@@ -215,6 +215,30 @@ def test_precondition_matches_oracle(kind, dtype, B):
     assert np.max(np.abs(got - want)) <= 2e-5 * np.max(np.abs(want))
 
 
+def test_fewer_blocks_need_no_new_scratch():
+    """A call with fewer blocks of a grid than one before it allocates nothing
+    (a capture would refuse it), and its replays give the eager results: those of
+    the same blocks in the larger call."""
+    g = rsd.Grid("periodic", 0.25, n=40)
+    net = rsd.Cnn(32, 40 ** 3)
+    net.set_params(_params(23, scale=0.2))
+    gen = torch.Generator(device=DEV).manual_seed(24)
+    r = torch.randn((3, g.np, 32), generator=gen, device=DEV)
+    sig = -0.5 - torch.rand(96, generator=gen, device=DEV, dtype=torch.float64)
+    want = net.precondition(g, r, sig)
+    r2, s2 = r[:2].clone(), sig[:64].clone()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = net.precondition(g, r2, s2)
+    for k in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want[:2]), k
+        net.precondition(g, r[1:], sig[32:].clone())     # the program's own work in between
+
+
 def test_box_follows_the_grid_not_its_address():
     """A grid made after another one was destroyed may get its address; the
     network's box has to be the new grid's (dims only: no field is read)."""
