@@ -191,6 +191,10 @@ rs_status rs_nl_export(const rs_nl *nl, int64_t *sph_ptr, int64_t *sph_idx,
  *   V_nl: eq. (6) when nl != NULL (projections, then the point-centric sum
  *      over the atoms whose sphere holds the point; no atomics).
  * psi [nblk][np][B] and hpsi [nblk][np][B] must not overlap.  Asynchronous.
+ * Bitwise repeatable.  A state's values do not depend on the other states of
+ * the call, nor on how many there are, except in FP64 with blocks of 16, 32 or
+ * 64 real columns: up to 2^21 values of hpsi another kernel runs than above,
+ * and the two differ by rounding.
  * Complex dtypes: H is real, so each complex state is applied as its real
  * and imaginary columns (B <= 32).
  * Errors: RS_EINVAL (B, dtype, pointers, nblk*B real columns > max_states
@@ -368,8 +372,10 @@ void rs_eigensolve_destroy(rs_solver *s);
 /* One step on psi (DEVICE [nblk][np][B], the first nstates states
  * orthonormal and the padding states zero on entry; updated in place).  eig and resnorm (HOST double [nstates], may be NULL) receive
  * the step's Rayleigh-Ritz eigenvalues and residual norms; *nconv (HOST, may
- * be NULL) the number of states with resnorm < tol.  Synchronises the stream
- * once.  Errors: RS_ENOTPOSDEF if the final orthonormalisation fails,
+ * be NULL) the number of states with resnorm < tol.  Bitwise repeatable; the
+ * blocks that the stopping rule leaves active get the values they get when no
+ * block is frozen.  Synchronises the stream once, with block_stop and tol > 0
+ * twice.  Errors: RS_ENOTPOSDEF if the final orthonormalisation fails,
  * RS_ENONFINITE if an eigenvalue or residual is not finite. */
 rs_status rs_eigensolve_step(rs_solver *s, void *psi, double *eig, double *resnorm,
                              int32_t *nconv, void *stream);

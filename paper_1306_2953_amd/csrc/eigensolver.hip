@@ -51,7 +51,7 @@ const int *ctx_info(const rs_ctx *c);
 
 namespace rs {
 rs_status hpsi_apply(const rs_grid *g, const rs_nl *nl, const void *vloc, const void *psi, void *hpsi,
-                     int nblk, int B, int dtype, hipStream_t st);
+                     int nblk, int B, int dtype, hipStream_t st, int of);
 rs_status filter_apply(const rs_grid *g, double alpha, const void *r, void *out, int nblk, int B, int dtype,
                        hipStream_t st, const FilterUpdate *upd = nullptr);
 rs_status kinetic_apply(const rs_grid *g, const void *psi, void *out, int nblk, int B, int dtype,
@@ -799,7 +799,8 @@ rs_status hpsi_blocks(rs_solver *S, const T *x, T *hx, const Blocks &bs, hipStre
     const int64_t bel = S->g->np * S->B;
     for (const auto &run : bs.runs) {
         const int64_t off = run.first * bel;
-        rs_status e = rs::hpsi_apply(S->g, S->nl, S->vloc, x + off, hx + off, run.second, S->B, S->dtype, st);
+        rs_status e = rs::hpsi_apply(S->g, S->nl, S->vloc, x + off, hx + off, run.second, S->B, S->dtype, st,
+                                      S->nblk);
         if (e) return e;
     }
     return RS_OK;
@@ -817,7 +818,7 @@ rs_status step_impl(rs_solver *S, T *psi, hipStream_t st) {
     double *partial = S->partial.as<double>();
     rs_status e;
     // 1. H psi, Rayleigh-Ritz
-    if ((e = hpsi_apply(g, S->nl, S->vloc, psi, h0, nblk, B, S->dtype, st))) return e;
+    if ((e = hpsi_apply(g, S->nl, S->vloc, psi, h0, nblk, B, S->dtype, st, nblk))) return e;
     if ((e = subspace_diag_capped(S->ctx, psi, h0, S->eig.as<double>(), nblk, B, S->dtype, S->prec, S->rr_sweeps,
                                   S->nreal, st)))
         return e;

@@ -1060,9 +1060,12 @@ template <typename T> bool point_kernel(const rs_grid *g, int nblk, int B) {
 // star stencil with first-difference weights w0..w3 (see line_lap); V is
 // vloc, or the constant vconst when vloc is null.  R = 1: nearest
 // neighbours only (w1 = w2 = w3 = 0).  UPD: out is updated as FilterUpdate says.
+// of: the blocks of the problem that the nblk are a part of; the kernel is
+// chosen for them, since the z-marching kernel (FP64) rounds differently from
+// the other two, which agree bit for bit.
 template <typename T, int R = 4, bool UPD = false>
 rs_status launch_stencil(const rs_grid *g, const rs_nl *nl, const T *vloc, T vconst, const T *psi, T *hpsi,
-                         int nblk, int B, double pre_d, const double w[4], hipStream_t st,
+                         int nblk, int B, double pre_d, const double w[4], hipStream_t st, int of,
                          const FilterUpdate &upd = FilterUpdate{}) {
     if (g->nbricks == 0) return RS_OK;
     if ((uint64_t)g->np * 64 * sizeof(T) > kMaxField)
@@ -1082,7 +1085,7 @@ rs_status launch_stencil(const rs_grid *g, const rs_nl *nl, const T *vloc, T vco
     const int nat = with_nl ? nl->nat : 0;
     const int npj = with_nl ? nl->npj : 0;
     const T w0 = (T)w[0], w1 = (T)w[1], w2 = (T)w[2], w3 = (T)w[3];
-    if (point_kernel<T>(g, nblk, B)) {
+    if (point_kernel<T>(g, of, B)) {
         const bool fuse = with_nl && npj == 4;
         const int nwg = (int)((g->nbricks * 64 * B + 255) / 256), nwg_pad = (nwg + 7) & ~7;
         const dim3 grid(nwg_pad, nblk);
@@ -1179,10 +1182,10 @@ rs_status launch_stencil(const rs_grid *g, const rs_nl *nl, const T *vloc, T vco
 // W_j = sum_{m>j} c_m, prefactor -1/(2h^2).
 template <typename T>
 rs_status launch_hpsi(const rs_grid *g, const rs_nl *nl, const T *vloc, const T *psi, T *hpsi,
-                      int nblk, int B, hipStream_t st) {
+                      int nblk, int B, hipStream_t st, int of) {
     const double c1 = 8.0 / 5.0, c2 = -1.0 / 5.0, c3 = 8.0 / 315.0, c4 = -1.0 / 560.0;
     const double w[4] = {c1 + c2 + c3 + c4, c2 + c3 + c4, c3 + c4, c4};
-    return launch_stencil<T>(g, nl, vloc, T(0), psi, hpsi, nblk, B, -0.5 / (g->h * g->h), w, st);
+    return launch_stencil<T>(g, nl, vloc, T(0), psi, hpsi, nblk, B, -0.5 / (g->h * g->h), w, st, of);
 }
 
 rs_status check_fields(const rs_grid *g, const rs_nl *nl, int nblk, int B, int dtype,
@@ -1227,8 +1230,8 @@ extern "C" rs_status rs_hpsi_block(const rs_grid *g, const rs_nl *nl, const void
     if (psi == hpsi) return fail(RS_EINVAL, "rs_hpsi_block: psi and hpsi must not alias");
     hipStream_t s = (hipStream_t)stream;
     if (dtype == RS_F64)
-        return launch_hpsi<double>(g, nl, (const double *)vloc, (const double *)psi, (double *)hpsi, nblk, B, s);
-    return launch_hpsi<float>(g, nl, (const float *)vloc, (const float *)psi, (float *)hpsi, nblk, B, s);
+        return launch_hpsi<double>(g, nl, (const double *)vloc, (const double *)psi, (double *)hpsi, nblk, B, s, nblk);
+    return launch_hpsi<float>(g, nl, (const float *)vloc, (const float *)psi, (float *)hpsi, nblk, B, s, nblk);
 }
 
 extern "C" rs_status rs_project_nl(const rs_grid *g, const rs_nl *nl, const void *psi, void *proj,
@@ -1268,11 +1271,13 @@ extern "C" rs_status rs_apply_nl(const rs_grid *g, const rs_nl *nl, const void *
 
 namespace rs {
 
+// H psi of nblk of a problem's `of` blocks: a state's values do not depend on
+// which part it is called in.
 rs_status hpsi_apply(const rs_grid *g, const rs_nl *nl, const void *vloc, const void *psi, void *hpsi,
-                     int nblk, int B, int dtype, hipStream_t st) {
+                     int nblk, int B, int dtype, hipStream_t st, int of) {
     if (dtype == RS_F64)
-        return launch_hpsi<double>(g, nl, (const double *)vloc, (const double *)psi, (double *)hpsi, nblk, B, st);
-    return launch_hpsi<float>(g, nl, (const float *)vloc, (const float *)psi, (float *)hpsi, nblk, B, st);
+        return launch_hpsi<double>(g, nl, (const double *)vloc, (const double *)psi, (double *)hpsi, nblk, B, st, of);
+    return launch_hpsi<float>(g, nl, (const float *)vloc, (const float *)psi, (float *)hpsi, nblk, B, st, of);
 }
 
 // Filter preconditioner: K r = alpha r + (1 - alpha)/6 (sum of the six nearest
@@ -1287,8 +1292,8 @@ rs_status filter_apply(const rs_grid *g, double alpha, const void *r, void *out,
         typedef decltype(t) T;
         if (upd)
             return launch_stencil<T, 1, true>(g, nullptr, nullptr, T(1), (const T *)r, (T *)out, nblk, B, pre, w, st,
-                                              *upd);
-        return launch_stencil<T, 1>(g, nullptr, nullptr, T(1), (const T *)r, (T *)out, nblk, B, pre, w, st);
+                                              nblk, *upd);
+        return launch_stencil<T, 1>(g, nullptr, nullptr, T(1), (const T *)r, (T *)out, nblk, B, pre, w, st, nblk);
     };
     return dtype == RS_F64 ? go(0.0) : go(0.0f);
 }
@@ -1305,8 +1310,9 @@ rs_status kinetic_apply(const rs_grid *g, const void *psi, void *out, int nblk, 
     const double pre = -0.5 / (g->h * g->h);
     if (dtype == RS_F64)
         return launch_stencil<double>(g, nullptr, nullptr, 0.0, (const double *)psi, (double *)out, nblk, B, pre, w,
-                                      st);
-    return launch_stencil<float>(g, nullptr, nullptr, 0.0f, (const float *)psi, (float *)out, nblk, B, pre, w, st);
+                                      st, nblk);
+    return launch_stencil<float>(g, nullptr, nullptr, 0.0f, (const float *)psi, (float *)out, nblk, B, pre, w, st,
+                                 nblk);
 }
 
 }  // namespace rs

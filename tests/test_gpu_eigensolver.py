@@ -113,6 +113,53 @@ def test_step_with_a_frozen_block_matches_oracle(m):
     assert np.max(np.abs(got - want["psi"])) < 1e-10 * np.max(np.abs(want["psi"]))
 
 
+# two active blocks beside a frozen one; all three make 3.1 and 6.1 million values,
+# two of 16 states 2.0 (H psi of so few, alone, would take another kernel)
+@pytest.mark.parametrize("B,with_net", [(16, False), (32, True)])
+def test_active_blocks_do_not_depend_on_the_frozen_ones(B, with_net):
+    """Periodic box, no potential: the top block holds plane waves of the highest
+    energies, which are eigenvectors, the others smooth states orthogonal to them.
+    With the stopping rule the top block is frozen, without it all run: the other
+    blocks' states come out the same, bit for bit (orthonormalisation takes the
+    states in order, so the top block does not enter them)."""
+    n, h = 40, 0.25
+    g = rsd.Grid("periodic", h, n=n)
+    xyz = np.round(g.xyz() / h).astype(int)
+    pts = torch.from_numpy(xyz).to(DEV).double()
+    waves = []
+    half = n // 2
+    for d in sorted(np.ndindex(4, 4, 4), key=sum):
+        k = torch.tensor([half - q for q in d], device=DEV, dtype=torch.float64)
+        arg = 2.0 * np.pi / n * (pts @ k)
+        waves += [torch.cos(arg)] if not any(d) else [torch.cos(arg), torch.sin(arg)]
+    top = torch.stack(waves[:B], dim=1)
+    rng = np.random.default_rng(31)
+    low = torch.zeros((g.np, 2 * B), device=DEV, dtype=torch.float64)
+    for s in range(2 * B):
+        for _ in range(4):
+            k = torch.from_numpy(rng.integers(-6, 7, 3).astype(float)).to(DEV)
+            low[:, s] += rng.normal() * torch.cos(2.0 * np.pi / n * (pts @ k) + rng.uniform(0.0, 6.0))
+        low[:, s] *= 1.0 + 0.3 * torch.cos(2.0 * np.pi / n * pts[:, s % 3] + s)
+    psi = torch.stack([low[:, :B], low[:, B:], top]).contiguous()
+    net = None
+    if with_net:
+        net = rsd.Cnn(2 * B, g.np)
+        net.set_params(np.random.default_rng(32).normal(scale=0.2, size=rsd.Cnn.NPARAM))
+    out = []
+    for stop in (True, False):
+        solver = rsd.Eigensolver(g, None, torch.zeros(g.np, device=DEV, dtype=torch.float64), 3 * B, B, tol=1e-6,
+                                 block_stop=stop)
+        if net is not None:
+            solver.set_precond(net)
+        x = psi.clone()
+        solver.orthonormalize(x)
+        _, res, _ = solver.step(x)
+        assert solver.stats()["frozen_blocks"] == int(stop)
+        assert np.max(res[2 * B:]) < 1e-6 and np.min(res[:2 * B]) > 1e-6
+        out.append(x[:2].cpu())
+    assert torch.equal(out[0], out[1])
+
+
 def test_converges_harmonic_box():
     """Lowest four levels of the 32^3 harmonic box from random states."""
     w = synthetic.make_workload("box32_harmonic", nstates=4)

@@ -291,3 +291,23 @@ def test_full_size_union_sampled(dtype, tol):
     P = kb.project(H.proj, x64)
     want += kb.apply_projections(H.proj, P, og.np)[:, pts]
     assert _relerr(got[:, pts], want) < tol
+
+
+# 12 blocks of 8 states: one-point and four-point projector adds on either side of
+# their line, and the point kernel against the per-brick one (FP32, 4.0 million
+# values whole and 1.3 in parts)
+@pytest.mark.parametrize("dtype,lmax", [(np.float32, 0), (np.float32, 1), (np.float32, 2), (np.float32, 3),
+                                        (np.float64, 1), (np.float64, 3)])
+@pytest.mark.parametrize("radius,h", [(6.0, 0.28), (8.0, 0.2)])
+def test_values_do_not_depend_on_the_number_of_states(dtype, lmax, radius, h):
+    g = rsd.Grid("sphere", h, radius=radius)
+    rng = np.random.default_rng(41)
+    pos = rng.normal(size=(16, 3))
+    pos *= 0.6 * radius / np.linalg.norm(pos, axis=1, keepdims=True)
+    nl = rsd.NonLocal(g, pos, rng.uniform(0.3, 2.0, (16, (lmax + 1) ** 2)), 2.5, 0.7, max_states=96, lmax=lmax)
+    psi = torch.from_numpy(rng.uniform(-1.0, 1.0, (12, g.np, 8)).astype(dtype)).to(DEV)
+    v = torch.from_numpy(rng.uniform(-3.0, 0.0, g.np).astype(dtype)).to(DEV)
+    whole = rsd.hpsi_block(g, nl, v, psi, torch.empty_like(psi))
+    for a, b in ((0, 1), (1, 5), (5, 12)):
+        x = psi[a:b].clone()
+        assert torch.equal(rsd.hpsi_block(g, nl, v, x, torch.empty_like(x)), whole[a:b]), (a, b)
