@@ -771,18 +771,19 @@ nl_add_kernel(const int32_t *__restrict__ nl_pts, int64_t nnl, const int32_t *__
 // The same with one lane per state of kAddPts consecutive points.  Such points
 // mostly share their atoms, so a lane keeps the D P of the last atom in
 // registers; read for every point they bound the kernel above in large calls
-// (16 of them per block, entry and state against one H psi value).  A lane
-// serves 2 or 4 blocks.  119k points x 32 states in 4 blocks, one point a lane ->
-// four: 4 projectors FP64 83 -> 65 us (55 for its bytes), 16 projectors FP64
-// 191 -> 144, FP32 71 -> 65.
+// (16 of them per block, entry and state against one H psi value).  119k points x
+// 32 states in 4 blocks, one point a lane -> four: 4 projectors FP64 83 -> 65 us
+// (55 for its bytes), 16 projectors FP64 191 -> 144, FP32 71 -> 65.  A lane serves
+// KB blocks: 2 or 4, or 1 where there is no second (registers for blocks it does
+// not have cost waves: 60 atoms, 16 projectors, one FP32 block of 32 on 904k
+// points, the whole call 296 us with 4, 266 with 1, 275 with one point a lane).
 constexpr int kAddPts = 4;
 template <typename T, int NPJ> constexpr int add_blocks() { return sizeof(T) * NPJ > 64 ? 2 : 4; }
-template <typename T, int NPJ>
+template <typename T, int NPJ, int KB>
 __global__ void __launch_bounds__(256)
 nl_add_run_kernel(const int32_t *__restrict__ nl_pts, int64_t nnl, const int32_t *__restrict__ pt_ptr,
               const int32_t *__restrict__ ent_atom, const T *__restrict__ ent_gamma, const T *__restrict__ dp,
               T *__restrict__ hpsi, int64_t np, int B, int nat, int nblk) {
-    constexpr int KB = add_blocks<T, NPJ>();
     const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
     const int64_t j0 = (int64_t)(idx / (uint32_t)B) * kAddPts;
     if (j0 >= nnl) return;
@@ -1025,8 +1026,10 @@ rs_status launch_nl_add(const rs_grid *g, const rs_nl *nl, T *hpsi, int nblk, in
         (const T *)nl->dp.p, hpsi, g->np, B, nl->nat, nblk
 #define RS_NLADD(NPJ)                                                                                      \
     case NPJ:                                                                                              \
-        if (four)                                                                                          \
-            hipLaunchKernelGGL((nl_add_run_kernel<T, NPJ>),                                                \
+        if (four && nblk == 1)                                                                             \
+            hipLaunchKernelGGL((nl_add_run_kernel<T, NPJ, 1>), dim3(gx, 1), RS_NLADD_ARGS);                \
+        else if (four)                                                                                     \
+            hipLaunchKernelGGL((nl_add_run_kernel<T, NPJ, add_blocks<T, NPJ>()>),                          \
                                dim3(gx, (nblk + add_blocks<T, NPJ>() - 1) / add_blocks<T, NPJ>()), RS_NLADD_ARGS); \
         else                                                                                               \
             hipLaunchKernelGGL((nl_add_kernel<T, NPJ>), one, RS_NLADD_ARGS);                               \

@@ -311,3 +311,21 @@ def test_values_do_not_depend_on_the_number_of_states(dtype, lmax, radius, h):
     for a, b in ((0, 1), (1, 5), (5, 12)):
         x = psi[a:b].clone()
         assert torch.equal(rsd.hpsi_block(g, nl, v, x, torch.empty_like(x)), whole[a:b]), (a, b)
+
+
+# one block alone (its own four-point projector add) against the same one of three
+@pytest.mark.parametrize("dtype,lmax", [(np.float32, 0), (np.float32, 2), (np.float32, 3), (np.float64, 0),
+                                        (np.float64, 1), (np.float64, 2), (np.float64, 3)])
+def test_projector_add_of_one_large_block(dtype, lmax):
+    g = rsd.Grid("sphere", 0.2, radius=8.0)
+    rng = np.random.default_rng(43)
+    pos = rng.normal(size=(16, 3))
+    pos *= 5.0 / np.linalg.norm(pos, axis=1, keepdims=True)
+    nl = rsd.NonLocal(g, pos, rng.uniform(0.3, 2.0, (16, (lmax + 1) ** 2)), 2.5, 0.7, max_states=96, lmax=lmax)
+    gen = torch.Generator(device=DEV).manual_seed(44)
+    psi = torch.rand((3, g.np, 32), generator=gen, device=DEV).to(torch.from_numpy(np.zeros(1, dtype)).dtype) - 0.5
+    v = torch.from_numpy(rng.uniform(-3.0, 0.0, g.np).astype(dtype)).to(DEV)
+    whole = rsd.hpsi_block(g, nl, v, psi, torch.empty_like(psi))
+    assert not torch.equal(whole, rsd.hpsi_block(g, None, v, psi, torch.empty_like(psi)))
+    x = psi[1:2].clone()
+    assert torch.equal(rsd.hpsi_block(g, nl, v, x, torch.empty_like(x)), whole[1:2])
