@@ -865,11 +865,8 @@ nl_partial_kernel(const int32_t *__restrict__ chunk_beg, const int32_t *__restri
     // end the last entry is read again and counts as zero.  Loads of one batch
     // of 4 at a time took 38.6 us for 60 spheres of 950 points with 16
     // projectors and 128 FP32 columns, this 23; for 8 spheres, 4 projectors and 32
-    // FP64 columns 15.5 -> 11.  Large batches of wide entries cost the waves that
-    // hide the rest: 60 spheres of 2145 points, 128 FP64 columns, 4 projectors,
-    // batches of 4 / 8: 33.6 / 40.2 us; 8 such spheres, 64 columns, 16 projectors,
-    // 2 / 4: 38.5 / 42.5 (batches of 4 loaded at once: 33.8 and 41.5).
-    constexpr int U = sizeof(T) * NPJ <= 16 ? 8 : sizeof(T) * NPJ <= 64 ? 4 : 2;
+    // FP64 columns 15.5 -> 11.
+    constexpr int U = NPJ <= 4 ? 8 : 4;
     if (e0 < e1) {
         int id[U];
         T x[U], xn[U];
