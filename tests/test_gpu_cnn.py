@@ -70,6 +70,71 @@ def test_forward_at_column_edges(n, dims, periodic):
         assert np.max(np.abs(f[i] - want)) <= 1e-5 * np.max(np.abs(want))
 
 
+# layer 3 in columns of 8 planes, more than one tile in x and y
+@pytest.mark.parametrize("periodic", [False, True])
+def test_forward_in_columns_of_several_tiles(periodic):
+    n, dims = 300, (9, 17, 18)
+    p = _params(25)
+    net = rsd.Cnn(n, int(np.prod(dims)))
+    net.set_params(p)
+    u = np.random.default_rng(26).normal(size=(n,) + dims).astype(np.float32)
+    f = net.forward(_dev(u), periodic=periodic).cpu().numpy()
+    for i in (0, 1, 149, 298, 299):
+        want, _ = ocnn.forward(p, u[i].astype(np.float64), np.ones(dims), "wrap" if periodic else "zero")
+        # as above: layer 2's split products carry about 2^-16 per term
+        assert np.max(np.abs(f[i] - want)) <= 1e-5 * np.max(np.abs(want))
+
+
+# the application of the trained network with a mask (or across faces) in columns
+# of 8 planes: boxes of 33^3, 21 x 32 x 33 and 32^3, 32 and 64 of them at once
+@pytest.mark.parametrize("kind,blocks", [("sphere", 1), ("union", 2), ("periodic", 2)])
+def test_precondition_in_masked_columns(kind, blocks):
+    kw = {"sphere": dict(radius=4.8), "periodic": dict(n=32),
+          "union": dict(radius=3.0, centres=np.array([[0.0, 0.0, 0.0], [3.6, 1.8, 0.0], [0.3, 3.6, 0.1]]))}[kind]
+    og, g = ogrid.build_grid(kind, 0.3, **kw), rsd.Grid(kind, 0.3, **kw)
+    p = _params(27, scale=0.2)
+    B, N = 32, 32 * blocks
+    dims = ocnn.box_of(og)[1]
+    net = rsd.Cnn(N, int(np.prod(dims)))
+    net.set_params(p)
+    assert net.box(g) == tuple(dims)
+    rng = np.random.default_rng(28)
+    r = rng.normal(size=(N, og.np)).astype(np.float32)
+    sig = -rng.uniform(0.5, 4.0, size=N)
+    out = net.precondition(g, _dev(rsd.to_blocks(r, B)), _dev(sig))
+    some = [0, 13, N - 1]
+    got = rsd.from_blocks(out.cpu().numpy()).astype(np.float64)[some]
+    want = ocnn.precondition(p, og, r[some].astype(np.float64), sig[some])
+    assert np.max(np.abs(got - want)) <= 2e-5 * np.max(np.abs(want))
+
+
+def test_tanh_accuracy():
+    """Layer 1's tanh against FP64: with one point, input 1 and layer 2's weights
+    zero, the gradient of w2[0][c] at the centre is tanh(w1[c]) times a common
+    factor, which channel 7 (tanh 1) gives.  tanh errs by 1.38 units in the last
+    place at most, the product's rounding by one of tanh's."""
+    rng = np.random.default_rng(29)
+    x = np.concatenate([2.0 ** rng.uniform(-20, 4.3, 1300), rng.uniform(0.8, 1.1, 400), rng.uniform(0.0, 10.0, 400)])
+    x = (x * rng.choice([-1.0, 1.0], x.size)).astype(np.float32)
+    net = rsd.Cnn(1, 1)
+    one = torch.ones((1, 1, 1, 1), device=DEV)
+    sig = torch.full((1,), -1.0, device=DEV, dtype=torch.float64)
+    got = np.empty(x.size)
+    for k in range(0, x.size, 7):
+        p = np.zeros(ocnn.NP, np.float32)
+        p[13:216:27][:7], p[13:216:27][7] = x[k:k + 7], 20.0
+        p[1944:2160] = 0.7
+        net.set_params(p)
+        _, grad, _ = net.loss_grad(one, one, sig, 0.25, 0)
+        d = grad[216 + 13:216 + 216:27].astype(np.float64)
+        assert d[7] != 0.0
+        got[k:k + 7] = d[:7] / d[7]
+    want = np.tanh(x.astype(np.float64))
+    err = np.abs(got - want) / np.spacing(np.abs(want).astype(np.float32)).astype(np.float64)
+    assert np.max(err) <= 2.4, (np.max(err), x[np.argmax(err)])
+    assert np.sqrt(np.mean(err ** 2)) <= 0.6
+
+
 # columns of 8 and of 16 rows: both sides of the line, alone and after whole ones,
 # shallow and deep, and more shallow ones than work-groups
 @pytest.mark.parametrize("n,dims,periodic", [(2, (4, 8, 17), True), (2, (5, 9, 5), False), (1, (4, 24, 16), False),
