@@ -306,10 +306,11 @@ rs_status rs_subspace_diag(rs_ctx *c, void *psi, void *hpsi, double *eig, int32_
  * N > (extent - 1) + R_c / h on every axis (the box then keeps every
  * periodic image of the density more than R_c from the domain), at least
  * 16 and at most 512 (RS_ENOTSUP beyond).  FP64 throughout.  Finite grids
- * only (RS_EINVAL for periodic ones).  The handle owns the half spectra over
- * the domain's extent (about 8 N^2 times its z extent bytes), the kernel's
- * table (N^3 bytes) and the point table; it holds a pointer to the grid,
- * which must outlive it. */
+ * only (RS_EINVAL for periodic ones).  With a domain of ex x ey x ez points
+ * the handle owns the half spectra (about 8 N (N + ey) ez bytes; 94 MB for
+ * 121^3 points and N = 256), the kernel's table (about N^3 bytes) and the
+ * point table (4 ex ey ez bytes); it holds a pointer to the grid, which must
+ * outlive it. */
 typedef struct rs_poisson rs_poisson;
 rs_status rs_poisson_create(const rs_grid *g, rs_poisson **out);
 void rs_poisson_destroy(rs_poisson *p);

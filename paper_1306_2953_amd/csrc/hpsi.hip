@@ -1007,7 +1007,10 @@ rs_status launch_project(const rs_grid *g, const rs_nl *nl, const T *psi, T *pro
 // The projector term added to a finished H psi (nl_add_kernel), for the
 // set's projector count; the projections must be in nl->dp.
 // Four points a lane pay where enough lanes remain: 3.8M (point, state, group
-// of 4 blocks) items 71 -> 65 us, but 1.1M 31 -> 39 (16 projectors, FP32).
+// of 4 blocks) items 71 -> 65 us, but 1.1M 31 -> 39 (16 projectors, FP32).  Above
+// the line, 1 to 16 projectors of both types, 12 to 60 atoms, 1 to 8 blocks, whole
+// H psi calls against one point a lane everywhere: from 17 % less to 3 % more time,
+// 5 % more in one of 252 (9 FP32 projectors, 60 spheres on 904k points, 4 blocks of 8).
 constexpr int64_t kAddWide = 2 << 20;
 template <typename T>
 rs_status launch_nl_add(const rs_grid *g, const rs_nl *nl, T *hpsi, int nblk, int B, hipStream_t st) {
@@ -1052,6 +1055,8 @@ rs_status launch_nl_add(const rs_grid *g, const rs_nl *nl, T *hpsi, int nblk, in
 //    blocks the z-marching kernel does not take): its 64 lanes are columns.
 //    262k points, FP64 8 columns 118 -> 28, 64 columns 146 -> 200; FP32 8
 //    columns 47 -> 23, 16 columns 46-55 -> 44-46, 32 columns 47-55 -> 84.
+// The 7-point filter goes by the same line; whole steps of 1 to 64 states on 32^3
+// to 80^3 points are nowhere slower with it than with the per-brick filter.
 template <typename T> bool point_kernel(const rs_grid *g, int nblk, int B) {
     const int64_t cols = (int64_t)nblk * B, outputs = g->np * cols;
     if (g->nbricks * 64 * B >= (1ll << 31)) return false;   // 32-bit thread numbers
