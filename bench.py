@@ -182,7 +182,7 @@ def _counter_means(path, counter):
 
 # the kernels of one H psi call besides the projections: the z-marching
 # stencil (FP64) or the per-brick stencil (FP32), and the projector add
-STENCIL_KERNELS = ("hpsi_march_kernel", "hpsi_brick_kernel", "nl_add_kernel")
+STENCIL_KERNELS = ("hpsi_march_kernel", "hpsi_brick_kernel", "nl_add_")
 
 
 def traffic_record(w, dtype, fetch_csv, write_csv):
