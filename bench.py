@@ -720,7 +720,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": r["achieved_gbs"], "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": r["frac"],
                      "traffic": measured_traffic(w.name, dtype),
-                     "kernel": ("hpsi_march_kernel (full + partial chunk launches) + nl_add_kernel, "
+                     "kernel": ("hpsi_march_kernel (full + partial chunk launches) + nl_add_run_kernel, "
                                 "one H psi call" if dtype == "f64" else
                                 "hpsi_brick_kernel (interior + surface launches), one H psi call"),
                      "bytes_per_launch": r["bytes_kernel"],
